@@ -29,9 +29,8 @@ struct ile_geom {
     int n_det, n_lm, n_t, half;      // half = (n_t - 1) / 2
     int n_q;                         // length of each Q series
     int s_max;                       // largest valid window start, n_q - n_t
-    // phased matrix-core engine: positions of one detector's G block (the
-    // union of a chunk's windows) and the LDS row stride of that block; set
-    // per launch from the LDS budget
+    // phased matrix-core engine: bins of a chunk and the LDS stride of a
+    // sample's row of them (one more); set per launch from the LDS budget
     int wcap, wrow;
     double t0;                       // time of Q[0]
     double dt;                       // 1 / srate
@@ -220,8 +219,10 @@ hipError_t ile_launch_identity(int32_t *perm, int64_t N, hipStream_t st);
 // 16 f + r % 16], r = i - t0, t0 the first position of the launch (a
 // tile's fields are contiguous): q (the quadratic term), a validity flag (1
 // or 0), (d_ref/D) F_k (re, im) for each detector, -2Y_lm (re, im) for
-// each mode, then the window start of each detector; q, the F_k and the
-// window starts are zero for an invalid sample.
+// each mode, then for each detector a pair of integers: the sample's window
+// start less its tile's smallest, and (first two positions of a tile) that
+// smallest start and the spread of the tile's starts; q, the F_k and the
+// windows are zero for an invalid sample.  Whole tiles are written.
 int ile_terms_fields(const ile_geom &g);
 bool ile_contract_uses_terms(ile_precision prec, const ile_tune &tu);
 // The terms of positions 0 .. N-1 of one point into terms (16 F round16(N)

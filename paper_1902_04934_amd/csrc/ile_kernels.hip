@@ -26,6 +26,7 @@
 #include <math.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "ile_internal.h"
 #include "ile_rng.h"
@@ -945,7 +946,10 @@ __device__ __forceinline__ void tile_prologue(
 // host packs the upper triangles row by row, entry (a, b >= a) at
 // 4 (a nl - a (a - 1) / 2 + b - a) as (Re U_h, Im U_h, Re V_s, Im V_s).
 // Output: tile-major, field f of position t0 + r at
-// terms[16 F (r / 16) + 16 f + r % 16].
+// terms[16 F (r / 16) + 16 f + r % 16]; the last n_det fields are integer
+// pairs, the sample's window start less the smallest of its tile, and in the
+// tile's first two positions that smallest start and the tile's spread.
+__host__ __device__ inline int terms_fields(int nd, int nl) { return 2 + 3 * nd + 2 * nl; }
 
 // One lane's sample: its validity, window starts, the sines and cosines of
 // the antenna angles, d_ref/D, and the tables the harmonics are read from:
@@ -961,7 +965,8 @@ struct TermsSample {
 __device__ __forceinline__ void terms_intake(const ile_geom &g, const double *__restrict__ smp,
                                              int64_t N, const int32_t *__restrict__ perm,
                                              const int32_t *__restrict__ shifts, int64_t i,
-                                             bool in_order, TermsSample &S, double (&cp)[kPw],
+                                             bool in_order, bool live, TermsSample &S,
+                                             double (&cp)[kPw],
                                              double (&sp)[kPw], double (&er)[kPw],
                                              double (&ei)[kPw])
 {
@@ -975,7 +980,7 @@ __device__ __forceinline__ void terms_intake(const ile_geom &g, const double *__
     for (int p = 0; p < 7; p++) th[p] = smp[(int64_t)p * N + src];
 #pragma unroll
     for (int k = 0; k < ILE_MAX_DET; k++) S.sd[k] = k < nd ? shifts[(int64_t)k * N + src] : 0;
-    bool ok = sample_ok(g, th);
+    bool ok = live && sample_ok(g, th);
 #pragma unroll
     for (int k = 0; k < ILE_MAX_DET; k++)
         ok = ok & (k >= nd || (S.sd[k] >= 0 && S.sd[k] <= g.s_max));
@@ -1051,20 +1056,37 @@ __device__ __forceinline__ void terms_mac(double2 Yb, double4 e, double &ur, dou
     vi = fma(e.z, Yb.y, fma(e.w, Yb.x, vi));
 }
 
+// Smallest (or largest) of a 16-lane row, in every lane, by DPP row rotations.
+template <bool MIN> __device__ __forceinline__ int row_red(int x)
+{
+    const auto f = [](int a, int b) { return MIN ? min(a, b) : max(a, b); };
+    x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x128, 0xF, 0xF, false));
+    x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x124, 0xF, 0xF, false));
+    x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x122, 0xF, 0xF, false));
+    return f(x, __builtin_amdgcn_update_dpp(0, x, 0x121, 0xF, 0xF, false));
+}
+
 __device__ __forceinline__ void terms_store(const ile_geom &g, const TermsSample &S, double q,
                                             double *tp)
 {
     const int nd = g.n_det, nl = g.n_lm;
     tp[0] = 0.25 * S.kap * S.kap * q;
     tp[16] = S.ok ? 1.0 : 0.0;
+    const int r = __lane_id() & 15;
 #pragma unroll
     for (int k = 0; k < ILE_MAX_DET; k++)
-        if (k < nd) tp[(2 + 2 * nd + 2 * nl + k) * 16] = S.ok ? (double)S.sd[k] : 0.0;
+        if (k < nd) {
+            const int lo = row_red<true>(S.ok ? S.sd[k] : 0x7fffffff);
+            const int hi = row_red<false>(S.ok ? S.sd[k] : -1);
+            const int2 w = make_int2(S.ok ? S.sd[k] - lo : 0,
+                                     hi < 0 || r > 1 ? 0 : r == 0 ? lo : hi - lo);
+            *reinterpret_cast<int2 *>(tp + (2 + 2 * nd + 2 * nl + k) * 16) = w;
+        }
 }
 
 __device__ __forceinline__ double *terms_slot(const ile_geom &g, double *terms, int64_t r)
 {
-    return terms + (r >> 4) * (16 * (int64_t)(2 + 3 * g.n_det + 2 * g.n_lm)) + (r & 15);
+    return terms + (r >> 4) * (16 * (int64_t)terms_fields(g.n_det, g.n_lm)) + (r & 15);
 }
 
 // Entry i of the triangles by vector loads at a uniform address (one cache
@@ -1092,7 +1114,9 @@ __global__ __launch_bounds__(kTermsT) void k_terms(
     extern __shared__ __align__(16) unsigned char dyn_lds[];
     const int lane = threadIdx.x;
     const int64_t r = (int64_t)blockIdx.x * kTermsT + lane;   // position t0 + r
-    if (r >= n) return;
+    // the last tile's positions past n are written too, as invalid samples
+    // (terms holds whole tiles), so that a tile's 16 lanes are all active
+    if (r >= ((n + 15) & ~(int64_t)15)) return;
     const int nd = g.n_det, nl = g.n_lm, ntri = nl * (nl + 1) / 2;
     double2 *Yl = reinterpret_cast<double2 *>(dyn_lds);   // [nl][64]
     const __amdgpu_buffer_rsrc_t rt = __builtin_amdgcn_make_buffer_rsrc(
@@ -1100,7 +1124,7 @@ __global__ __launch_bounds__(kTermsT) void k_terms(
     double *tp = terms_slot(g, terms, r);
     TermsSample S;
     double cp[kPw], sp[kPw], er[kPw], ei[kPw];
-    terms_intake(g, smp, N, perm, shifts, t0 + r, in_order, S, cp, sp, er, ei);
+    terms_intake(g, smp, N, perm, shifts, t0 + min(r, n - 1), in_order, r < n, S, cp, sp, er, ei);
     for (int a = 0; a < nl; a++) {
         const double2 y = terms_harmonic(g, S, a, cp, sp, er, ei);
         Yl[a * kTermsT + lane] = y;
@@ -1521,112 +1545,140 @@ __device__ inline __amdgpu_buffer_rsrc_t q_rsrc(const TQ *Qk, int bytes)
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<TQ *>(Qk), (short)0, bytes, 0x00020000);
 }
 
-// NU N-tiles t[u] of detector k, computed together so that NU accumulations
-// are in flight: lane l supplies A[l%16][l/16] (the detector's
-// coefficients, LDS; one read per k-step serves all NU tiles) and
-// B[l/16][l%16] = Qm_k[4 ks + l/16][P0 + 16 t + l%16] by buffer loads, the
-// lane's offset in a VGPR and the k-step's in an SGPR, so a load costs no
-// vector instruction.  Columns past the end of Q are clamped (past every
-// sample's window: never moved to X).  Operands are double-buffered: the
-// loads of k-step ks + 1 are issued before the products of k-step ks.  The
-// result D[alpha][16 t + c] goes to X[alpha][16 t + c - dd[v]] (alpha =
-// row(lane / 16, v), dd its window start minus smin_k) when that bin is in
-// [0, Jc): stored when `add` is false, else added.  Each (alpha, bin) comes
-// from exactly one lane of one tile.  BF: the stores without branches, into
-// X's one element past its 16 rows of xrow bins when out of range.
-template <typename TQ, int NU, bool BF>
-__device__ inline void ph_tiles(TQ *X, int xrow, const TQ *coefk, __amdgpu_buffer_rsrc_t rs,
-                                int qrow0, int nq, int KSP, int P0, const int (&t)[4],
-                                const int (&dd)[4], int Jc, bool add, int lane)
+template <typename TQ> struct lds_ptr {
+    using type = __attribute__((address_space(3))) TQ;
+    static __device__ inline int addr(const TQ *p)
+    {
+        return (int)(unsigned)(uintptr_t)(type *)const_cast<TQ *>(p);
+    }
+    static __device__ inline type *at(int a) { return (type *)(uintptr_t)(unsigned)a; }
+};
+
+__device__ __forceinline__ int med3(int x, int lo, int hi)
+{
+    int d;
+    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(d) : "v"(x), "v"(lo), "v"(hi));
+    return d;
+}
+
+// The products of NU N-tiles tb, tb + NW, ... of one detector, computed
+// together so that NU accumulations are in flight: lane l supplies
+// A[l%16][l/16] (the detector's coefficients, LDS; one read per k-step serves
+// all NU tiles) and B[l/16][l%16] = Qm_k[4 ks + l/16][P + 16 t + l%16] by
+// buffer loads, the lane's offset in a VGPR and the k-step's in an SGPR, so a
+// load costs no vector instruction.  Columns past the end of Q are clamped
+// (past every sample's window: never moved to a bin).  Operands are
+// double-buffered: the loads of k-step ks + 1 are issued before the products
+// of k-step ks; the first k-step's products take the zero of their
+// accumulators as a constant.
+template <typename TQ, int NU, int NW>
+__device__ __forceinline__ void ph_products(typename mfma_acc<TQ>::type (&acc)[NU],
+                                            const TQ *coefk, __amdgpu_buffer_rsrc_t rs,
+                                            int qrow0, int nq, int KSP, int P, int tb, int lane)
 {
     using M = mfma_acc<TQ>;
-    const int row = lane >> 4, col = lane & 15;
-    typename M::type acc[NU];
+    const int rb = (qrow0 + (lane >> 4)) * nq, p = P + 16 * tb + (lane & 15);
     int vo[NU];
 #pragma unroll
-    for (int u = 0; u < NU; u++) {
-        acc[u] = typename M::type{0, 0, 0, 0};
-        vo[u] = ((qrow0 + row) * nq + min(P0 + 16 * t[u] + col, nq - 1)) * (int)sizeof(TQ);
-    }
+    for (int u = 0; u < NU; u++) vo[u] = (rb + min(p + 16 * NW * u, nq - 1)) * (int)sizeof(TQ);
     const int kstep = 4 * nq * (int)sizeof(TQ);
     TQ a0 = coefk[lane], a1, b0[NU], b1[NU];
 #pragma unroll
     for (int u = 0; u < NU; u++) b0[u] = qload<TQ>::ld(rs, vo[u], 0);
     // k-steps in pairs with every load and product unconditional (a load
     // under a branch is sunk next to its use); an odd last step follows
-    int ks = 0;
+    const auto load = [&](TQ &a, TQ (&b)[NU], int ks) {
+        const int kc = min(ks, KSP - 1);
+        a = coefk[kc * 64 + lane];
+#pragma unroll
+        for (int u = 0; u < NU; u++) b[u] = qload<TQ>::ld(rs, vo[u], kc * kstep);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    const auto step = [&](TQ a, const TQ (&b)[NU]) {
+#pragma unroll
+        for (int u = 0; u < NU; u++) acc[u] = M::step(a, b[u], acc[u]);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    load(a1, b1, 1);
+#pragma unroll
+    for (int u = 0; u < NU; u++) acc[u] = M::step(a0, b0[u], typename M::type{0, 0, 0, 0});
+    __builtin_amdgcn_sched_barrier(0);
+    if (KSP == 1) return;
+    load(a0, b0, 2);
+    step(a1, b1);
+    int ks = 2;
     for (; ks + 1 < KSP; ks += 2) {
-        const int k2 = min(ks + 2, KSP - 1);
-        a1 = coefk[(ks + 1) * 64 + lane];
-#pragma unroll
-        for (int u = 0; u < NU; u++) b1[u] = qload<TQ>::ld(rs, vo[u], (ks + 1) * kstep);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < NU; u++) acc[u] = M::step(a0, b0[u], acc[u]);
-        __builtin_amdgcn_sched_barrier(0);
-        a0 = coefk[k2 * 64 + lane];
-#pragma unroll
-        for (int u = 0; u < NU; u++) b0[u] = qload<TQ>::ld(rs, vo[u], k2 * kstep);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < NU; u++) acc[u] = M::step(a1, b1[u], acc[u]);
-        __builtin_amdgcn_sched_barrier(0);
+        load(a1, b1, ks + 1);
+        step(a0, b0);
+        load(a0, b0, ks + 2);
+        step(a1, b1);
     }
-    if (ks < KSP) {
+    if (ks < KSP) step(a0, b0);
+}
+
+// Where a lane's results of one detector go: result v of tile t belongs at
+// LDS byte xb[v] + 16 t elements, its sample's bin 16 t + c - dd (dd the
+// sample's window start minus the detector's smallest); lo[v] is the slot
+// before the sample's first bin.
+struct ph_row {
+    int xb[4], lo[4];
+};
+
+// e^d where the reference moves, kept out of line: inlined, its constants are
+// held in some twenty vector registers across the whole tile (FP64 119 against
+// 100, and FP32 tiles then spill below the 85 that three workgroups per CU
+// leave: 0.805 against 0.774 ms on 2e5 samples, 13 modes, 1103 bins).
+__device__ __attribute__((noinline)) double exp_rescale(double d) { return exp(d); }
+
+// The group's results to their samples' bins: stored when `add` is false,
+// else added.  Each (alpha, bin) comes from exactly one lane of one tile.  A
+// tile whose every result has a bin in the chunk (16 t >= spread, 16 t + 15 <
+// Jc) takes its addresses by constant offsets; in the others a result
+// outside the chunk is held to the slot just before or just past its row's
+// bins (cb bytes after lo), which is never read as a bin: one add and one
+// med3 in place of the add, compare, select and shift of a bounds test.
+template <typename TQ, int NU, int NW>
+__device__ __forceinline__ void ph_store(const typename mfma_acc<TQ>::type (&acc)[NU],
+                                         const ph_row &R, int cb, int tb, int spread, int Jc,
+                                         bool add)
+{
+    using P = lds_ptr<TQ>;
+    constexpr int TB = 16 * (int)sizeof(TQ);
+    int base[4];
 #pragma unroll
-        for (int u = 0; u < NU; u++) acc[u] = M::step(a0, b0[u], acc[u]);
-    }
-    if constexpr (BF) {
-        // without branches: a value whose bin is outside [0, Jc) goes to the
-        // slot past the 16 rows (never read as a bin); when adding, every
-        // load is issued before the first sum
-        int a[NU][4];
+    for (int v = 0; v < 4; v++) base[v] = R.xb[v] + tb * TB;
 #pragma unroll
-        for (int u = 0; u < NU; u++) {
-            const int c = 16 * t[u] + col;
+    for (int u = 0; u < NU; u++) {
+        const auto put = [&](auto at) {
+            if (add) {
+                TQ o[4];
 #pragma unroll
-            for (int v = 0; v < 4; v++) {
-                const int jj = c - dd[v];
-                a[u][v] = (unsigned)jj < (unsigned)Jc ? M::row(row, v) * xrow + jj : 16 * xrow;
+                for (int v = 0; v < 4; v++) o[v] = *at(v);
+#pragma unroll
+                for (int v = 0; v < 4; v++) *at(v) = o[v] + (TQ)acc[u][v];
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; v++) *at(v) = (TQ)acc[u][v];
             }
-        }
-        if (add) {
-            TQ o[NU][4];
-#pragma unroll
-            for (int u = 0; u < NU; u++)
-#pragma unroll
-                for (int v = 0; v < 4; v++) o[u][v] = X[a[u][v]];
-#pragma unroll
-            for (int u = 0; u < NU; u++)
-#pragma unroll
-                for (int v = 0; v < 4; v++) X[a[u][v]] = o[u][v] + (TQ)acc[u][v];
+        };
+        const int c0 = 16 * (tb + u * NW);
+        if (c0 >= spread && c0 + 15 < Jc) {
+            put([&](int v) { return P::at(base[v] + u * NW * TB); });
         } else {
+            int a[4];
 #pragma unroll
-            for (int u = 0; u < NU; u++)
-#pragma unroll
-                for (int v = 0; v < 4; v++) X[a[u][v]] = (TQ)acc[u][v];
-        }
-    } else {
-        // the branch form needs fewer registers (FP32 tiles run three
-        // workgroups per CU; the series form holds more state)
-#pragma unroll
-        for (int u = 0; u < NU; u++) {
-#pragma unroll
-            for (int v = 0; v < 4; v++) {
-                const int jj = 16 * t[u] + col - dd[v];
-                if (jj >= 0 && jj < Jc) {
-                    TQ *x = X + M::row(row, v) * xrow + jj;
-                    *x = add ? *x + (TQ)acc[u][v] : (TQ)acc[u][v];
-                }
-            }
+            for (int v = 0; v < 4; v++)
+                a[v] = med3(base[v] + u * NW * TB, R.lo[v], R.lo[v] + cb);
+            put([&](int v) { return P::at(a[v]); });
         }
     }
 }
 
 // LDS of the phased tile beyond its static arrays: coefficients
-// [nd][KSP][64], then the chunk bins X [TS][xrow] and one 16-byte slot that
-// takes the FP64 tiles' stores of bins outside the chunk (the prologue's
-// scratch lives there first).
+// [nd][KSP][64], then 16 bytes (the slot before the first row's first bin)
+// and the chunk bins X [TS][xrow], the last of a row's xrow elements being the
+// slot past its bins (a tile that forms its own terms has their scratch there
+// first).
 __host__ __device__ inline size_t ph_dyn_bytes(int ts, int nd, int nl, int wrow, size_t e)
 {
     const size_t gb = (size_t)ts * wrow * e + 16;
@@ -1660,7 +1712,7 @@ __device__ __forceinline__ void ph_lphase(const TQ *X, int Jc, int o, double &m,
     const auto fold = [&](double x) {
         double d = x - m;
         if (d > kLseSlack) {
-            ssum = m == -INFINITY ? 0.0 : ssum * exp(m - x);
+            ssum = m == -INFINITY ? 0.0 : ssum * exp_rescale(m - x);
             m = x;
             d = 0.0;
         }
@@ -1687,6 +1739,15 @@ __device__ __forceinline__ void ph_lphase(const TQ *X, int Jc, int o, double &m,
 // PRE: the per-sample terms come from k_terms (the tile's block of the
 // terms, tile-major from position t0), else the tile forms them
 // (tile_prologue).
+// What bounds it: the FP64 matrix steps themselves (a variant without stores
+// and log-sum-exp runs its chunks at the matrix rate, 0.82 ms per chunk of 463
+// bins for 5e5 samples at 3 detectors and 21 modes), then, since they do not
+// overlap them, the vector instructions of the stores and of the log-sum-exp,
+// and the prologue's latency (one workgroup of the two on a CU waits in it).
+// Stores by constant offsets or med3, the zero accumulators as a constant and
+// the prologue in one round of loads (windows relative to the tile already
+// in the terms) took a 1e6-sample call from 11.01 to 10.37 ms, and 2e5 FP32
+// samples (13 modes, 1103 bins) from 0.835 to 0.743 ms.
 template <typename TQ, int TS, int NT, bool DUMP, bool PRE>
 __device__ __forceinline__ void contract_tile_ph(
     const ile_geom &g, int64_t base, const double *__restrict__ smp, int64_t N,
@@ -1711,114 +1772,114 @@ __device__ __forceinline__ void contract_tile_ph(
     const int wcap = g.wcap, wrow = g.wrow;
     TQ *coef = reinterpret_cast<TQ *>(dyn_lds);   // [nd][KSP][64]
     TQ *G = reinterpret_cast<TQ *>(dyn_lds + coef_bytes<ENG_MFMA>(TS, nd, nl, sizeof(TQ)));
-    const size_t gbytes = (size_t)TS * wrow * sizeof(TQ);
-    const size_t sbytes = prologue_scratch_bytes(TS, nd, nl);
     // one buffer resource over all of Q (the host keeps it below 2 GiB)
     const __amdgpu_buffer_rsrc_t rs = q_rsrc<TQ>(Q, nd * RP * nq * (int)sizeof(TQ));
 
     if constexpr (PRE) {
-        // samples, validity, window starts and q of the tile; the
-        // coefficients c = (d_ref/D) F_k Y_lm in the matrix-core A layout
-        // (modes a in [nl, 2 KSP) are the zero padding of K)
-        const double *tb = terms + ((base - t0) >> 4) * (16 * (int64_t)(2 + 3 * nd + 2 * nl));
+        // one round of loads: samples, validity, windows and q of the tile,
+        // and the factors of the coefficients c = (d_ref/D) F_k Y_lm, written
+        // in the matrix-core A layout (modes a in [nl, 2 KSP) are the zero
+        // padding of K)
+        const double *tb = terms + ((base - t0) >> 4) * (16 * (int64_t)terms_fields(nd, nl));
+        const int2 *tw = reinterpret_cast<const int2 *>(tb + (2 + 2 * nd + 2 * nl) * TS);
         if (tid < TS) {
             const int64_t i = base + tid;
-            int idx = -1, ok = 0;
-            double q = 0.0;
-            if (i < N) {
-                const double *tk = tb + tid;
-                idx = perm[i];
-                ok = tk[16] != 0.0;
-                q = tk[0];
-                for (int k = 0; k < nd; k++) s_d[k][tid] = (int)tk[(2 + 2 * nd + 2 * nl + k) * 16];
-            } else {
-                for (int k = 0; k < nd; k++) s_d[k][tid] = 0;
-            }
-            s_idx[tid] = idx;
-            s_ok[tid] = ok;
-            s_q[tid] = q;
+            s_idx[tid] = i < N ? perm[i] : -1;
+            s_ok[tid] = tb[TS + tid] != 0.0;
+            s_q[tid] = tb[tid];
+        } else if (tid >= 64 && tid < 64 + TS * nd) {
+            const int t = tid - 64;
+            const int2 w = tw[t];
+            s_d[t / TS][t % TS] = w.x;
+            if (t % TS == 0) s_smin[t / TS] = w.y;
+            if (t % TS == 1) s_spread[t / TS] = w.y;
         }
-        // the factors (d_ref/D) F_k and -2Y_lm of the tile's samples to LDS
-        // (the free G blocks) in one round of loads, then the products
-        double *s_fy = reinterpret_cast<double *>(G);   // [2 (nd + nl)][TS]
-        const int nfy = 2 * (nd + nl);
-        for (int t = tid; t < TS * nfy; t += NT)
-            s_fy[t] = base + t % TS < N ? tb[2 * TS + t] : 0.0;
-        __syncthreads();
-        const int nlp = 2 * KSP;
-        for (int t = tid; t < TS * nd * nlp; t += NT) {
-            const int al = t % TS, r = t / TS, k = r / nlp, a = r - k * nlp;
-            double cx = 0.0, cy = 0.0;
-            if (a < nl) {
-                const double fr = s_fy[(2 * k) * TS + al], fi = s_fy[(2 * k + 1) * TS + al];
-                const double yr = s_fy[(2 * nd + 2 * a) * TS + al];
-                const double yi = s_fy[(2 * nd + 2 * a + 1) * TS + al];
-                cx = fr * yr - fi * yi;
-                cy = fr * yi + fi * yr;
+        for (int t = tid; t < TS * 2 * KSP; t += NT) {
+            const int al = t % TS, a = t / TS;
+            // every load unconditional, so that they are one round
+            const double *yp = tb + (2 + 2 * nd + 2 * min(a, nl - 1)) * TS + al;
+            double yr = yp[0], yi = yp[TS], fr[ILE_MAX_DET], fi[ILE_MAX_DET];
+#pragma unroll
+            for (int k = 0; k < ILE_MAX_DET; k++) {
+                const double *fp = tb + (2 + 2 * min(k, nd - 1)) * TS + al;
+                fr[k] = fp[0];
+                fi[k] = fp[TS];
             }
-            const int r0 = 2 * a;
-            coef[(k * KSP + (r0 >> 2)) * 64 + (r0 & 3) * 16 + al] = (TQ)cx;
-            coef[(k * KSP + (r0 >> 2)) * 64 + ((r0 & 3) + 1) * 16 + al] = (TQ)cy;
+            if (a >= nl) yr = yi = 0.0;
+            TQ *ca = coef + (a >> 1) * 64 + (a & 1) * 32 + al;
+#pragma unroll
+            for (int k = 0; k < ILE_MAX_DET; k++)
+                if (k < nd) {
+                    ca[k * KSP * 64] = (TQ)fma(fr[k], yr, -(fi[k] * yi));
+                    ca[k * KSP * 64 + 16] = (TQ)fma(fi[k], yr, fr[k] * yi);
+                }
         }
-        (void)gbytes;
-        (void)sbytes;
         __syncthreads();
     } else {
+        const size_t gbytes = (size_t)TS * wrow * sizeof(TQ);
+        const size_t sbytes = prologue_scratch_bytes(TS, nd, nl);
         tile_prologue<TQ, TS, NT, ENG_MFMA>(g, base, smp, N, perm, shifts, U, V,
                                             reinterpret_cast<double *>(G),
                                             gbytes > sbytes ? gbytes : sbytes, coef, s_q,
                                             s_idx, s_ok, s_d);
     }
 
-    // window range of each detector over the tile's valid samples
-    if (tid < TS) {
-        const bool v = s_ok[tid];
-        for (int k = 0; k < nd; k++) {
-            int lo = v ? s_d[k][tid] : 0x7fffffff, hi = v ? s_d[k][tid] : -1;
-            for (int off = 8; off > 0; off >>= 1) {
-                lo = min(lo, __shfl_xor(lo, off, 16));
-                hi = max(hi, __shfl_xor(hi, off, 16));
-            }
-            if (tid == 0) {
-                s_smin[k] = hi >= 0 ? lo : 0;
-                s_spread[k] = hi >= 0 ? hi - lo : 0;
+    // window range of each detector over the tile's valid samples, the
+    // windows then relative to its start
+    if (!PRE) {
+        if (tid < TS) {
+            const bool v = s_ok[tid];
+            for (int k = 0; k < nd; k++) {
+                int lo = v ? s_d[k][tid] : 0x7fffffff, hi = v ? s_d[k][tid] : -1;
+                for (int off = 8; off > 0; off >>= 1) {
+                    lo = min(lo, __shfl_xor(lo, off, 16));
+                    hi = max(hi, __shfl_xor(hi, off, 16));
+                }
+                if (tid == 0) {
+                    s_smin[k] = hi >= 0 ? lo : 0;
+                    s_spread[k] = hi >= 0 ? hi - lo : 0;
+                }
+                s_d[k][tid] = v ? s_d[k][tid] - lo : 0;
             }
         }
+        __syncthreads();
     }
-    __syncthreads();
 
     using MA = mfma_acc<TQ>;
-    // FP64 tiles store without branches (measured faster), the others with
-    constexpr bool BF = sizeof(TQ) == 8 && !DUMP;
-    const int al = tid / LPS, sub = tid % LPS, row = lane >> 4;
+    const int al = tid / LPS, sub = tid % LPS, row = lane >> 4, col = lane & 15;
     const bool mem = s_ok[al];
-    TQ *X = G;   // [TS][wrow], the chunk's bins of every sample
+    TQ *X = G + 16 / sizeof(TQ);   // [TS][wrow], the chunk's bins of every sample
+    const int xaddr = (int)lds_ptr<TQ>::addr(X);
     double m = -INFINITY, ssum = 0.0;
-    const int J = wcap;   // a multiple of 16, at most wrow
+    const int J = wcap;   // below wrow: the slot after a row's last bin is free
     for (int j0 = 0; j0 < n_t; j0 += J) {
         const int Jc = min(J, n_t - j0);
         // G phase, detector by detector: N-tiles wv, wv + NW, ..., four at
         // a time
         for (int k = 0; k < nd; k++) {
-            const int smin = s_smin[k];
-            const int T = (Jc + s_spread[k] + 15) >> 4;
-            int dd[4];
+            const int smin = __builtin_amdgcn_readfirstlane(s_smin[k]);
+            const int spread = __builtin_amdgcn_readfirstlane(s_spread[k]);
+            const int T = (Jc + spread + 15) >> 4;
+            ph_row R;
 #pragma unroll
-            for (int v = 0; v < 4; v++) dd[v] = s_d[k][MA::row(row, v)] - smin;
+            for (int v = 0; v < 4; v++) {
+                const int r = MA::row(row, v);
+                R.lo[v] = xaddr + (r * wrow - 1) * (int)sizeof(TQ);
+                R.xb[v] = R.lo[v] + (1 + col - s_d[k][r]) * (int)sizeof(TQ);
+            }
             const TQ *coefk = coef + k * KSP * 64;
+            const auto group = [&](auto NUc, int tb) {
+                constexpr int NU = decltype(NUc)::value;
+                typename MA::type acc[NU];
+                ph_products<TQ, NU, NW>(acc, coefk, rs, k * RP, nq, KSP, smin + j0, tb, lane);
+                ph_store<TQ, NU, NW>(acc, R, (Jc + 1) * (int)sizeof(TQ), tb, spread, Jc, k > 0);
+            };
             for (int tb = wv; tb < T; tb += 4 * NW) {
-                int t[4], nu = 0;
-#pragma unroll
-                for (int u = 0; u < 4; u++) {
-                    const int tt = tb + u * NW;
-                    t[u] = tt < T ? tt : tb;
-                    nu += tt < T;
-                }
-                switch (__builtin_amdgcn_readfirstlane(nu)) {
-                case 4: ph_tiles<TQ, 4, BF>(X, wrow, coefk, rs, k * RP, nq, KSP, smin + j0, t, dd, Jc, k > 0, lane); break;
-                case 3: ph_tiles<TQ, 3, BF>(X, wrow, coefk, rs, k * RP, nq, KSP, smin + j0, t, dd, Jc, k > 0, lane); break;
-                case 2: ph_tiles<TQ, 2, BF>(X, wrow, coefk, rs, k * RP, nq, KSP, smin + j0, t, dd, Jc, k > 0, lane); break;
-                default: ph_tiles<TQ, 1, BF>(X, wrow, coefk, rs, k * RP, nq, KSP, smin + j0, t, dd, Jc, k > 0, lane); break;
+                switch (min(4, (T - tb + NW - 1) / NW)) {
+                case 4: group(std::integral_constant<int, 4>{}, tb); break;
+                case 3: group(std::integral_constant<int, 3>{}, tb); break;
+                case 2: group(std::integral_constant<int, 2>{}, tb); break;
+                default: group(std::integral_constant<int, 1>{}, tb); break;
                 }
             }
             __syncthreads();
@@ -1857,12 +1918,17 @@ __device__ __forceinline__ void run_tile(
 }
 
 // Waves per SIMD the register allocation must allow (the second bound of
-// __launch_bounds__): two eight-wave phased workgroups per CU, as many as
-// their LDS admits, are four waves per SIMD.
-template <int NT, int ENG> constexpr int contract_min_waves() { return ENG == ENG_PH && NT == 512 ? 4 : 1; }
+// __launch_bounds__): the eight-wave phased workgroups per CU that their LDS
+// admits, two for FP64 and three for FP32, are four and six waves per SIMD
+// (tiles that form the per-sample terms themselves need more registers than
+// six waves leave).
+template <typename TQ, int NT, int ENG, bool PRE = false> constexpr int contract_min_waves()
+{
+    return ENG == ENG_PH && NT == 512 ? (sizeof(TQ) == 4 && PRE ? 6 : 4) : 1;
+}
 
 template <typename TQ, int TS, int NT, int ENG, bool DUMP>
-__global__ __launch_bounds__(NT, (contract_min_waves<NT, ENG>())) void k_contract(
+__global__ __launch_bounds__(NT, (contract_min_waves<TQ, NT, ENG>())) void k_contract(
     ile_geom g, const double *__restrict__ smp, int64_t N,
     const int32_t *__restrict__ perm, const int32_t *__restrict__ shifts,
     const TQ *__restrict__ Q, const double2 *__restrict__ U,
@@ -1877,7 +1943,7 @@ __global__ __launch_bounds__(NT, (contract_min_waves<NT, ENG>())) void k_contrac
 // (point, tile) items from a queue in list order (the host sorts the list by
 // decreasing cost) until it is empty; every wave reaches the exit.
 template <typename TQ, int TS, int NT, int ENG>
-__global__ __launch_bounds__(NT, (contract_min_waves<NT, ENG>())) void k_contract_batched(
+__global__ __launch_bounds__(NT, (contract_min_waves<TQ, NT, ENG>())) void k_contract_batched(
     const ile_geom *__restrict__ geoms, const ile_point_dev *__restrict__ pts,
     const int2 *__restrict__ items, int n_items, unsigned *counter)
 {
@@ -1905,7 +1971,7 @@ __global__ __launch_bounds__(NT, (contract_min_waves<NT, ENG>())) void k_contrac
 // are read through the scalar unit instead of being held in registers
 // across a queue loop.
 template <typename TQ, int TS, int NT, bool PRE>
-__global__ __launch_bounds__(NT, (contract_min_waves<NT, ENG_PH>())) void k_contract_items(
+__global__ __launch_bounds__(NT, (contract_min_waves<TQ, NT, ENG_PH, PRE>())) void k_contract_items(
     const ile_geom *__restrict__ geoms, const ile_point_dev *__restrict__ pts,
     const int2 *__restrict__ items)
 {
@@ -1925,7 +1991,7 @@ __global__ __launch_bounds__(NT, (contract_min_waves<NT, ENG_PH>())) void k_cont
 // tiles of tile positions t0 + 16 blockIdx.x .. (below N), their terms
 // tile-major from position t0.
 template <typename TQ, int NT, bool DUMP>
-__global__ __launch_bounds__(NT, (contract_min_waves<NT, ENG_PH>())) void k_contract_ph(
+__global__ __launch_bounds__(NT, (contract_min_waves<TQ, NT, ENG_PH, true>())) void k_contract_ph(
     ile_geom g, const double *__restrict__ smp, int64_t N, const int32_t *__restrict__ perm,
     const int32_t *__restrict__ shifts, const TQ *__restrict__ Q,
     const double *__restrict__ terms, int64_t t0, double *__restrict__ out,
@@ -2372,7 +2438,8 @@ void ile_contract_prepare(ile_geom &g, ile_precision prec, const ile_tune &tu)
 {
     if (tu.engine == ENG_PH && prec != ILE_BF16) {
         const size_t e = prec == ILE_FP64 ? 8 : 4;
-        g.wrow = g.wcap = ph_wrow(g.n_det, g.n_lm, e, ph_budget(tu, e));
+        g.wrow = ph_wrow(g.n_det, g.n_lm, e, ph_budget(tu, e));
+        g.wcap = g.wrow - 1;   // the slot past a row's last bin takes what lies outside
     } else {
         g.wrow = g.wcap = 0;
     }
@@ -2416,7 +2483,7 @@ bool ile_tune_supported(ile_precision prec, const ile_tune &tu)
     return tu.engine == ENG_MFMA || tu.engine == ENG_VALU;
 }
 
-int ile_terms_fields(const ile_geom &g) { return 2 + 3 * g.n_det + 2 * g.n_lm; }
+int ile_terms_fields(const ile_geom &g) { return terms_fields(g.n_det, g.n_lm); }
 
 hipError_t ile_launch_terms(const ile_geom &g, const double *smp, int64_t N,
                             const int32_t *perm, const int32_t *shifts, const double *uvt,
@@ -2445,7 +2512,7 @@ hipError_t ile_launch_contract(const ile_geom &g, ile_precision prec,
     if (tu.engine == ENG_PH) {
         ile_geom gp = g;
         ile_contract_prepare(gp, prec, tu);
-        if (gp.wcap < 16) return hipErrorInvalidValue;
+        if (gp.wrow < 16) return hipErrorInvalidValue;
         if (!uvt || !terms || cap < 16 || cap % 16) return hipErrorInvalidValue;
         if (terms_lds_bytes(g) > 64 * 1024) return hipErrorInvalidValue;
         const size_t e = prec == ILE_FP64 ? 8 : 4;
