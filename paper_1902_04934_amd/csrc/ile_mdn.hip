@@ -104,6 +104,24 @@ __device__ inline float gsum(float x)
     return x + row_ror<1>(x);
 }
 
+// Inclusive prefix sums over a 16-lane row, in the order of a shift by 1, 2, 4
+// and 8 lanes (a lane with no source adds 0, which leaves it unchanged), and
+// the row's last value in every lane.
+template <int CTRL>
+__device__ inline float row_dpp(float x)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+        0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, false));
+}
+__device__ inline float row_scan(float x)
+{
+    x += row_dpp<0x111>(x);   // row_shr
+    x += row_dpp<0x112>(x);
+    x += row_dpp<0x114>(x);
+    return x + row_dpp<0x118>(x);
+}
+__device__ inline float row_last(float x) { return row_dpp<0x15F>(x); }   // row_newbcast:15
+
 // Ordering point for LDS data handed between lanes of one wave: a wave's
 // LDS accesses are performed in issue order, so it is enough that the
 // compiler moves no access across this point (no workgroup barrier).
@@ -147,47 +165,53 @@ __device__ inline double to_unit(const ile_mdn_tr &T, int d, double x, double &l
     }
 }
 
-// inverse of to_unit; periodic parameters wrapped into their prior range
-__device__ inline double from_unit(const ile_mdn_tr &T, int d, double u)
+// inverse of to_unit; periodic parameters wrapped into their prior range (the
+// product rounded before the sum, then one fused step, whatever code
+// surrounds it, so that a seed's draws do not depend on it)
+__device__ inline double wrap_unit(double origin, double u, double period)
 {
     double x;
+    {
+#pragma clang fp contract(off)
+        x = origin + (u - 0.5) * period;
+    }
+    return fma(-period, floor(x / period), x);
+}
+__device__ inline double from_unit(const ile_mdn_tr &T, int d, double u)
+{
     switch (d) {
-    case 0:
-        x = T.origin[0] + (u - 0.5) * kTwoPi;
-        return x - kTwoPi * floor(x / kTwoPi);
+    case 0: return wrap_unit(T.origin[0], u, kTwoPi);
     case 1: return asin(2.0 * u - 1.0);
-    case 2:
-        x = T.origin[1] + (u - 0.5) * kPi;
-        return x - kPi * floor(x / kPi);
-    case 3:
-        x = T.origin[2] + (u - 0.5) * kTwoPi;
-        return x - kTwoPi * floor(x / kTwoPi);
+    case 2: return wrap_unit(T.origin[1], u, kPi);
+    case 3: return wrap_unit(T.origin[2], u, kTwoPi);
     case 4: return 2.0 * u - 1.0;
     case 5: return T.d_min + u * (T.d_max - T.d_min);
     default: return (2.0 * u - 1.0) * T.t_ref_max;
     }
 }
 
-// x -> z~ (FP32 network inputs); returns sum_d ln |dz~_d/dx_d|, or -inf when
-// a u is 0 or 1 (z~ is then 0 in that dimension)
+// x_d -> z~_d (FP32 network input); returns ln |dz~_d/dx_d|, or -inf when u
+// is 0 or 1 (z~ is then 0)
+__device__ inline double to_z_dim(const ile_mdn_tr &T, int d, double x, float &z)
+{
+    double ldu;
+    const double u = to_unit(T, d, x, ldu);
+    if (!(u > 0.0 && u < 1.0)) {
+        z = 0.f;
+        return -INFINITY;
+    }
+    const double lu = log(u), l1u = log1p(-u);
+    z = (float)((lu - l1u - T.mean[d]) / T.scale[d]);
+    return -log(T.scale[d]) - lu - l1u + ldu;
+}
+
+// all dimensions; returns the sum of their ln |dz~/dx| in order
 __device__ inline double to_z(const ile_mdn_tr &T, const double x[7], float z[7])
 {
     double lj = 0.0;
-    bool ok = true;
 #pragma unroll
-    for (int d = 0; d < D; d++) {
-        double ldu;
-        const double u = to_unit(T, d, x[d], ldu);
-        if (!(u > 0.0 && u < 1.0)) {
-            ok = false;
-            z[d] = 0.f;
-            continue;
-        }
-        const double lu = log(u), l1u = log1p(-u);
-        z[d] = (float)((lu - l1u - T.mean[d]) / T.scale[d]);
-        lj += -log(T.scale[d]) - lu - l1u + ldu;
-    }
-    return ok ? lj : -INFINITY;
+    for (int d = 0; d < D; d++) lj += to_z_dim(T, d, x[d], z[d]);
+    return lj;
 }
 
 __device__ inline double logaddexp(double a, double b)
@@ -226,23 +250,6 @@ __device__ inline void layer1(const float *W1, int w1ld, const float *b1, const 
     }
 }
 
-// Pre-activations of layer 2: acc[t][v] = a2[sample 4g+v][unit 16t+r].
-// W2 is [o][k] with row stride ld (LDS or global).
-__device__ inline void layer2(const v8bf A[4], const __bf16 *W2, int ld, int r, int g,
-                              v4f acc[8])
-{
-#pragma unroll
-    for (int t = 0; t < 8; t++) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < 4; ks++) {
-#pragma unroll
-        for (int t = 0; t < 8; t++) {
-            const v8bf b = *(const v8bf *)(W2 + (16 * t + r) * ld + 32 * ks + 8 * g);
-            acc[t] = mfma(A[ks], b, acc[t]);
-        }
-    }
-}
-
 // B fragments of the three layer-3 output tiles of dimension d, [4 ks][3 j].
 __device__ inline void load_w3_dim(const __bf16 *W3, int ld, int d, int r, int g, v8bf B[12])
 {
@@ -251,22 +258,6 @@ __device__ inline void load_w3_dim(const __bf16 *W3, int ld, int d, int r, int g
 #pragma unroll
         for (int j = 0; j < 3; j++)
             B[3 * ks + j] = *(const v8bf *)(W3 + (48 * d + 16 * j + r) * ld + 32 * ks + 8 * g);
-}
-
-// Three output tiles 3d, 3d+1, 3d+2 (dimension d) of layer 3.
-__device__ inline void layer3_dim(const v8bf A2[4], const __bf16 *W3, int ld, int d, int r,
-                                  int g, v4f t3[3])
-{
-#pragma unroll
-    for (int j = 0; j < 3; j++) t3[j] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < 4; ks++) {
-#pragma unroll
-        for (int j = 0; j < 3; j++) {
-            const v8bf b = *(const v8bf *)(W3 + (48 * d + 16 * j + r) * ld + 32 * ks + 8 * g);
-            t3[j] = mfma(A2[ks], b, t3[j]);
-        }
-    }
 }
 
 // ln q_d of one sample from its component (lane r of the group): returns
@@ -299,62 +290,156 @@ __device__ inline float mix_lnq_fast(float a, float mu, float rho, float z, floa
 }
 
 // ----------------------------------------------------------- inference
-// Persistent: each workgroup stages the BF16 weights in LDS once and loops
-// over tiles of 64 samples (4 waves x 16).  SAMPLE: ancestral draw of z~,
-// one dimension per pass, then the density of the drawn x by the same code
-// as LOGPDF, so the returned ln q is exactly what logpdf gives for it.
+// LDS image of a [rows][128] bf16 array in rows of 256 bytes without padding:
+// 16-byte chunk c of row m is at chunk c ^ (m mod 16), so that the 16 rows
+// one fragment load touches lie in 16 different bank groups.
+__device__ inline int swz(int m, int c) { return m * H + ((c ^ (m & 15)) << 3); }
+
+constexpr int IW = 8;            // waves per workgroup
+constexpr int IT = 64 * IW;
+constexpr int W3ROWS = O - 48;   // dimension 0 has no weights
+
+// The FP64 parts of a tile, out of line: inlined, the constants of their
+// exponentials and logarithms are held in registers across the tiles and the
+// kernel spills.
+struct zterm {
+    double lj;
+    float z;
+};
+__device__ __attribute__((noinline)) zterm to_z_call(const ile_mdn_tr &T, int d, double x)
+{
+    zterm t;
+    t.lj = to_z_dim(T, d, x, t.z);
+    return t;
+}
+__device__ __attribute__((noinline)) double from_z_call(const ile_mdn_tr &T, int d, float z)
+{
+    const double zz = T.mean[d] + T.scale[d] * (double)z;
+    return from_unit(T, d, 1.0 / (1.0 + exp(-zz)));
+}
+__device__ __attribute__((noinline)) double ln_prior_call(const ile_mdn_tr &T, double dec, double D_)
+{
+    return ile_rng::ln_prior(dec, D_, T.d_min, T.d_max, T.t_ref_max);
+}
+__device__ __attribute__((noinline)) double ln_hist_call(const double *P, int nb, double ra,
+                                                         double dec)
+{
+    return ln_hist_ratio(P, nb, ra, dec);
+}
+__device__ __attribute__((noinline)) double ln_mix_call(double eps, double lnn, double lqa)
+{
+    return logaddexp(log1p(-eps) + lnn, log(eps) + lqa);
+}
+__device__ __attribute__((noinline)) void hist_call(const double *P, const double *C, int nb,
+                                                    uint64_t seed, uint64_t i,
+                                                    const ile_mdn_tr &T, double *X)
+{
+    double x[7];
+    uint32_t wd[16];
+    ile_rng::prior_words(seed, i, wd);
+    int br, bs;
+    (void)ile_rng::hist_sample(P, C, nb, wd, T.d_min, T.d_max, T.t_ref_max, x, br, bs);
+#pragma unroll
+    for (int d = 0; d < D; d++) X[d] = x[d];
+}
+
+// Persistent: each workgroup stages W3 in LDS once and its waves loop over
+// tiles of 16 samples, one wave a tile, with no barrier between waves.
+// SAMPLE: ancestral draw of z~, one dimension per pass, then the density of
+// the drawn x by the same code as LOGPDF, so the returned ln q is exactly
+// what logpdf gives for it.
+//
+// The ancestral passes use the masks: a unit of degree e (k mod 6) sees
+// z~_0 .. z~_e only, so it is final after pass e, and dimension d needs the
+// units of degree below d.  Pass d therefore evaluates the 21 or 22 units of
+// degree d - 1 of each layer and no other: their hidden values join those of
+// the earlier passes in LDS, and the products run over all 128 units as ever
+// (in the same order; the units not yet known have weights of zero, and hold
+// zeros or the wave's previous values, which are finite).  All seven passes
+// together are one forward evaluation where they were six, which is what the
+// kernel's time was: its tanh and exponentials, a chain a lane waits for at
+// one wave per SIMD.  W2 comes from global memory, fetched ahead of the
+// layer that uses it, so that LDS holds two waves per SIMD.
+// 1e5 draws of the mixture take 241 us (596 with a full evaluation per pass and
+// one wave per SIMD; the draws are the same bit for bit).
 template <bool SAMPLE>
-__global__ __launch_bounds__(256) void k_mdn_infer(
+__global__ __launch_bounds__(IT, 2) void k_mdn_infer(
     const float *__restrict__ theta, const __bf16 *__restrict__ W2b,
     const __bf16 *__restrict__ W3b, const ile_mdn_tr *__restrict__ trp, ile_mdn_mix mix,
     uint64_t seed, int64_t first, int64_t n, double *x_io, int64_t ld, double *ln_p,
     double *ln_q)
 {
-    __shared__ __attribute__((aligned(16))) __bf16 sW2[H * WLD];
-    __shared__ __attribute__((aligned(16))) __bf16 sW3[O * WLD];
+    __shared__ __attribute__((aligned(16))) __bf16 sW3[W3ROWS * H];
+    __shared__ __attribute__((aligned(16))) __bf16 sH1[SAMPLE ? IW : 1][SAMPLE ? 16 * H : 8];
+    __shared__ __attribute__((aligned(16))) __bf16 sH2[IW][16 * H];
     __shared__ float sW1[H * 8];
     __shared__ float sb1[H], sb2[H], sb3[O];
-    __shared__ __attribute__((aligned(16))) __bf16 sH[4][16 * WLD];
-    __shared__ float sZ[4][16 * 8];
-    __shared__ float sR[4][16 * 16];
-    __shared__ float sLq[4][16];
+    __shared__ float sZ[IW][16 * 8];
+    // per sample 16 uniforms, later 8 doubles: x, then ln |dz~/dx|
+    __shared__ __attribute__((aligned(16))) float sR[IW][16 * 16];
+    __shared__ float sLq[IW][16];
     __shared__ double sP[2 * MAXB], sC[2 * (MAXB + 1)];
     __shared__ ile_mdn_tr sT;
 
-    const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, r0 = lane & 15, g0 = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    for (int c = tid; c < H * 16; c += 256) {
+    for (int c = tid; c < W3ROWS * 16; c += IT) {
         const int row = c >> 4, col = c & 15;
-        *(v8bf *)(sW2 + row * WLD + 8 * col) = *(const v8bf *)(W2b + row * H + 8 * col);
+        *(v8bf *)(sW3 + swz(row, col)) = *(const v8bf *)(W3b + (48 + row) * H + 8 * col);
     }
-    for (int c = tid; c < O * 16; c += 256) {
-        const int row = c >> 4, col = c & 15;
-        *(v8bf *)(sW3 + row * WLD + 8 * col) = *(const v8bf *)(W3b + row * H + 8 * col);
-    }
-    for (int j = tid; j < H * 8; j += 256) {
+    for (int j = tid; j < H * 8; j += IT) {
         const int k = j >> 3, d = j & 7;
         sW1[j] = d < D ? theta[OFF_W1 + k * D + d] : 0.f;
     }
-    for (int j = tid; j < H; j += 256) {
+    for (int j = tid; j < H; j += IT) {
         sb1[j] = theta[OFF_B1 + j];
         sb2[j] = theta[OFF_B2 + j];
     }
-    for (int j = tid; j < O; j += 256) sb3[j] = theta[OFF_B3 + j];
+    for (int j = tid; j < O; j += IT) sb3[j] = theta[OFF_B3 + j];
     const bool mixed = mix.nb > 0 && mix.eps > 0.0;
     if (mixed) {
-        for (int j = tid; j < 2 * mix.nb; j += 256) sP[j] = mix.P[j];
-        for (int j = tid; j < 2 * (mix.nb + 1); j += 256) sC[j] = mix.C[j];
+        for (int j = tid; j < 2 * mix.nb; j += IT) sP[j] = mix.P[j];
+        for (int j = tid; j < 2 * (mix.nb + 1); j += IT) sC[j] = mix.C[j];
     }
     if (tid == 0) sT = *trp;
+    __bf16 *H1s = sH1[SAMPLE ? w : 0], *H2s = sH2[w];
+    if (SAMPLE) {
+        v8bf zero;
+#pragma unroll
+        for (int i = 0; i < 8; i++) zero[i] = (__bf16)0.f;
+        for (int c = lane; c < 16 * 16; c += 64) {
+            *(v8bf *)(H1s + 8 * c) = zero;
+            *(v8bf *)(H2s + 8 * c) = zero;
+        }
+    }
     __syncthreads();
     const float sfloor = (float)sT.sigma_floor, kappa = (float)sT.sigma_scale;
-    __bf16 *Hs = sH[w];
     float *Zs = sZ[w], *Rs = sR[w];
-
-    for (int64_t tile = blockIdx.x; tile * 64 < n; tile += gridDim.x) {
-        const int64_t i = tile * 64 + 16 * w + r;   // sample of lane r (group 0 owns it)
+    double *Xs = reinterpret_cast<double *>(Rs);   // [16][8]
+    // tile t goes to workgroup t mod grid, its waves in turn
+    for (int64_t tile = blockIdx.x + (int64_t)gridDim.x * w; tile * 16 < n;
+         tile += (int64_t)gridDim.x * IW) {
+        // the lane's place through a value the compiler cannot see, or it
+        // would hold every weight fragment in registers across the tiles
+        int zero_ = 0;
+        asm volatile("" : "+s"(zero_));
+        const int r = r0 + zero_, g = g0 + zero_;
+        const auto frag = [&](const __bf16 *A, int ks) {   // row r, units 32 ks + 8 g ..
+            return *(const v8bf *)(A + swz(r, 4 * ks + g));
+        };
+        // outputs of dimension d >= 1 for samples 4 g + v, component r
+        const auto layer3 = [&](const v8bf (&A2)[4], int d, v4f (&t3)[3]) {
+#pragma unroll
+            for (int j = 0; j < 3; j++) t3[j] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < 4; ks++)
+#pragma unroll
+                for (int j = 0; j < 3; j++)
+                    t3[j] = mfma(A2[ks], *(const v8bf *)(sW3 + swz(48 * (d - 1) + 16 * j + r, 4 * ks + g)),
+                                 t3[j]);
+        };
+        const int64_t i = tile * 16 + r;   // sample of the lanes of column r
         const bool valid = i < n;
-        double x[7] = {1.0, 0.1, 1.0, 1.0, 0.1, 0.5 * (sT.d_min + sT.d_max), 0.0};
         if (SAMPLE) {
             // 16 uniforms per sample: group g computes Philox blocks 2g, 2g+1
 #pragma unroll
@@ -364,45 +449,66 @@ __global__ __launch_bounds__(256) void k_mdn_infer(
                 Rs[r * 16 + 4 * g + 2 * bb] = (float)ile_rng::u53(q[0], q[1]);
                 Rs[r * 16 + 4 * g + 2 * bb + 1] = (float)ile_rng::u53(q[2], q[3]);
             }
-            if (g == 0)
-                for (int d = 0; d < 8; d++) Zs[r * 8 + d] = 0.f;
-            __syncthreads();
+            wave_lds_sync();
             // uniforms 0..6: component choices; 7..14 -> 8 normals (Box-Muller);
             // 15: which member of the defensive mixture draws the sample
-            if (g == 0) {
-                for (int j = 0; j < 4; j++) {
-                    const float a = Rs[r * 16 + 7 + 2 * j], b = Rs[r * 16 + 8 + 2 * j];
-                    const float rad = sqrtf(-2.f * logf(a));
-                    float sn, cs;
-                    sincosf(6.28318530717958648f * b, &sn, &cs);
-                    Rs[r * 16 + 7 + 2 * j] = rad * cs;
-                    Rs[r * 16 + 8 + 2 * j] = rad * sn;
-                }
+            {
+                const float a = Rs[r * 16 + 7 + 2 * g], b = Rs[r * 16 + 8 + 2 * g];
+                const float rad = sqrtf(-2.f * logf(a));
+                float sn, cs;
+                sincosf(6.28318530717958648f * b, &sn, &cs);
+                Rs[r * 16 + 7 + 2 * g] = rad * cs;
+                Rs[r * 16 + 8 + 2 * g] = rad * sn;
             }
-            __syncthreads();
+            wave_lds_sync();
+#pragma unroll 1
             for (int d = 0; d < D; d++) {
                 v4f t3[3];
                 if (d > 0) {
+                    const int e = d - 1;             // the degree that is new
+                    const int ne = e < 2 ? 22 : 21;  // its units: e, e + 6, ...
+                    // layer-2 rows of those units, in flight during layer 1
+                    v8bf B[2][4];
+#pragma unroll
+                    for (int t = 0; t < 2; t++) {
+                        const int k2 = e + 6 * min(16 * t + r, ne - 1);
+#pragma unroll
+                        for (int ks = 0; ks < 4; ks++)
+                            B[t][ks] = *(const v8bf *)(W2b + k2 * H + 32 * ks + 8 * g);
+                    }
                     float z[7];
 #pragma unroll
-                    for (int e = 0; e < D; e++) z[e] = Zs[r * 8 + e];
-                    v8bf A1[4];
-                    layer1(sW1, 8, sb1, z, g, A1);
-                    v4f acc[8];
-                    layer2(A1, sW2, WLD, r, g, acc);
+                    for (int c = 0; c < D; c++) z[c] = c < d ? Zs[r * 8 + c] : 0.f;
 #pragma unroll
-                    for (int t = 0; t < 8; t++) {
-                        const float bb = sb2[16 * t + r];
+                    for (int j0 = 0; j0 < 24; j0 += 4) {
+                        const int j = j0 + g, k = e + 6 * min(j, ne - 1);
+                        float a = sb1[k];
+#pragma unroll
+                        for (int c = 0; c < D - 1; c++) a = fmaf(sW1[k * 8 + c], z[c], a);
+                        H1s[swz(r, k >> 3) + (k & 7)] = (__bf16)tanhf(a);
+                    }
+                    wave_lds_sync();
+                    v4f acc[2];
+                    acc[0] = acc[1] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int ks = 0; ks < 4; ks++) {
+                        const v8bf A = frag(H1s, ks);
+#pragma unroll
+                        for (int t = 0; t < 2; t++) acc[t] = mfma(A, B[t][ks], acc[t]);
+                    }
+#pragma unroll
+                    for (int t = 0; t < 2; t++) {
+                        const int k2 = e + 6 * min(16 * t + r, ne - 1);
+                        const float bb = sb2[k2];
 #pragma unroll
                         for (int v = 0; v < 4; v++)
-                            Hs[(4 * g + v) * WLD + 16 * t + r] = (__bf16)tanhf(acc[t][v] + bb);
+                            H2s[swz(4 * g + v, k2 >> 3) + (k2 & 7)] = (__bf16)tanhf(acc[t][v] + bb);
                     }
-                    __syncthreads();
+                    wave_lds_sync();
                     v8bf A2[4];
 #pragma unroll
-                    for (int ks = 0; ks < 4; ks++)
-                        A2[ks] = *(const v8bf *)(Hs + r * WLD + 32 * ks + 8 * g);
-                    layer3_dim(A2, sW3, WLD, d, r, g, t3);
+                    for (int ks = 0; ks < 4; ks++) A2[ks] = frag(H2s, ks);
+                    layer3(A2, d, t3);
                 } else {
                     // dimension 0 sees no hidden unit: its outputs are the biases
 #pragma unroll
@@ -417,72 +523,106 @@ __global__ __launch_bounds__(256) void k_mdn_infer(
                     // categorical draw: first component whose cumulative weight
                     // exceeds u times the total
                     const float ma = gmax(al);
-                    float cum = expf(al - ma);
-#pragma unroll
-                    for (int off = 1; off < 16; off <<= 1) {
-                        const float tt = __shfl_up(cum, off, 16);
-                        if (r >= off) cum += tt;
-                    }
-                    const float tot = __shfl(cum, 15, 16);
+                    const float cum = row_scan(expf(al - ma));
+                    const float tot = row_last(cum);
                     const unsigned long long bal = __ballot(cum > Rs[s * 16 + d] * tot);
                     const unsigned bits = (unsigned)(bal >> (16 * g)) & 0xffffu;
                     const int cs = bits ? __ffs(bits) - 1 : 15;
                     const float sig = kappa * (sfloor + softplusf(rho));
-                    const float mus = __shfl(mu, cs, 16), sgs = __shfl(sig, cs, 16);
-                    if (r == 0) Zs[s * 8 + d] = mus + sgs * Rs[s * 16 + 7 + d];
+                    if (r == cs) Zs[s * 8 + d] = mu + sig * Rs[s * 16 + 7 + d];
                 }
-                __syncthreads();
+                wave_lds_sync();
             }
-            if (g == 0) {
-                if (mixed && Rs[r * 16 + 15] < (float)mix.eps) {
-                    uint32_t wd[16];
-                    ile_rng::prior_words(seed, (uint64_t)(first + i), wd);
-                    int br, bs;
-                    (void)ile_rng::hist_sample(sP, sC, mix.nb, wd, sT.d_min, sT.d_max,
-                                               sT.t_ref_max, x, br, bs);
-                } else {
-                    for (int d = 0; d < D; d++) {
-                        const double zz = sT.mean[d] + sT.scale[d] * (double)Zs[r * 8 + d];
-                        x[d] = from_unit(sT, d, 1.0 / (1.0 + exp(-zz)));
-                    }
-                }
-            }
-        } else if (g == 0 && valid) {
-            for (int d = 0; d < D; d++) x[d] = x_io[d * ld + i];
         }
+        // ---- x: lane (r, g) holds dimensions g and g + 4 of sample r
+        bool hist = false;
+        if (SAMPLE) {
+            hist = mixed && Rs[r * 16 + 15] < (float)mix.eps;
+            wave_lds_sync();   // Xs takes the place of Rs
+            if (hist && g == 0)
+                hist_call(sP, sC, mix.nb, seed, (uint64_t)(first + i), sT, Xs + r * 8);
+        }
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const int d = g + 4 * h;
+            if (d >= D) continue;
+            if (SAMPLE) {
+                if (!hist) Xs[r * 8 + d] = from_z_call(sT, d, Zs[r * 8 + d]);
+            } else {
+                const double dflt = d == 5 ? 0.5 * (sT.d_min + sT.d_max)
+                                           : d == 6 ? 0.0 : (d == 1 || d == 4) ? 0.1 : 1.0;
+                Xs[r * 8 + d] = valid ? x_io[d * ld + i] : dflt;
+            }
+        }
+        wave_lds_sync();
         // ---- density of x: the same code in both modes
-        double jac = 0.0, lp = 0.0, lqa = 0.0;
+        // layer-2 fragments of the first two k-steps, in flight meanwhile
+        v8bf B2[2][8];
+        const auto load_w2 = [&](int k0) {
+#pragma unroll
+            for (int ks = 0; ks < 2; ks++)
+#pragma unroll
+                for (int t = 0; t < 8; t++)
+                    B2[ks][t] = *(const v8bf *)(W2b + (16 * t + r) * H + 32 * (k0 + ks) + 8 * g);
+        };
+        double lp = 0.0, lqa = 0.0;
         if (g == 0) {
-            float z[7];
-            jac = to_z(sT, x, z);
-            for (int d = 0; d < D; d++) Zs[r * 8 + d] = z[d];
-            lp = ile_rng::ln_prior(x[1], x[5], sT.d_min, sT.d_max, sT.t_ref_max);
-            if (mixed) lqa = lp + ln_hist_ratio(sP, mix.nb, x[0], x[1]);
+            lp = ln_prior_call(sT, Xs[r * 8 + 1], Xs[r * 8 + 5]);
+            if (mixed) lqa = lp + ln_hist_call(sP, mix.nb, Xs[r * 8], Xs[r * 8 + 1]);
         }
-        __syncthreads();
+        double xd[2];
+#pragma unroll
+        for (int h = 0; h < 2; h++) xd[h] = g + 4 * h < D ? Xs[r * 8 + g + 4 * h] : 0.0;
+        wave_lds_sync();
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const int d = g + 4 * h;
+            if (d >= D) continue;
+            const zterm t = to_z_call(sT, d, xd[h]);
+            Xs[r * 8 + d] = t.lj;
+            Zs[r * 8 + d] = t.z;
+        }
+        wave_lds_sync();
         {
             float z[7];
 #pragma unroll
             for (int e = 0; e < D; e++) z[e] = Zs[r * 8 + e];
+            load_w2(0);
             v8bf A1[4];
             layer1(sW1, 8, sb1, z, g, A1);
             v4f acc[8];
-            layer2(A1, sW2, WLD, r, g, acc);
+#pragma unroll
+            for (int t = 0; t < 8; t++) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < 2; ks++)
+#pragma unroll
+                for (int t = 0; t < 8; t++) acc[t] = mfma(A1[ks], B2[ks][t], acc[t]);
+            load_w2(2);
+#pragma unroll
+            for (int ks = 0; ks < 2; ks++)
+#pragma unroll
+                for (int t = 0; t < 8; t++) acc[t] = mfma(A1[2 + ks], B2[ks][t], acc[t]);
 #pragma unroll
             for (int t = 0; t < 8; t++) {
-                const float bb = sb2[16 * t + r];
+                const int k2 = 16 * t + r;
+                const float bb = sb2[k2];
 #pragma unroll
                 for (int v = 0; v < 4; v++)
-                    Hs[(4 * g + v) * WLD + 16 * t + r] = (__bf16)tanhf(acc[t][v] + bb);
+                    H2s[swz(4 * g + v, k2 >> 3) + (k2 & 7)] = (__bf16)tanhf(acc[t][v] + bb);
             }
-            __syncthreads();
+            wave_lds_sync();
             v8bf A2[4];
 #pragma unroll
-            for (int ks = 0; ks < 4; ks++) A2[ks] = *(const v8bf *)(Hs + r * WLD + 32 * ks + 8 * g);
+            for (int ks = 0; ks < 4; ks++) A2[ks] = frag(H2s, ks);
             float lqz[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
             for (int d = 0; d < D; d++) {
                 v4f t3[3];
-                layer3_dim(A2, sW3, WLD, d, r, g, t3);
+                if (d > 0)
+                    layer3(A2, d, t3);
+                else
+#pragma unroll
+                    for (int j = 0; j < 3; j++) t3[j] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int v = 0; v < 4; v++) {
                     float sig, rr, ell, la;
@@ -494,20 +634,26 @@ __global__ __launch_bounds__(256) void k_mdn_infer(
             if (r == 0)
                 for (int v = 0; v < 4; v++) sLq[w][4 * g + v] = lqz[v];
         }
-        __syncthreads();
+        wave_lds_sync();
+        if (SAMPLE && valid)
+#pragma unroll
+            for (int h = 0; h < 2; h++)
+                if (g + 4 * h < D) x_io[(g + 4 * h) * ld + i] = xd[h];
         if (g == 0 && valid) {
+            double jac = 0.0;
+#pragma unroll
+            for (int d = 0; d < D; d++) jac += Xs[r * 8 + d];
             const double lnn = jac == -INFINITY ? -INFINITY : (double)sLq[w][r] + jac;
-            double lq = mixed ? logaddexp(log1p(-mix.eps) + lnn, log(mix.eps) + lqa) : lnn;
+            double lq = mixed ? ln_mix_call(mix.eps, lnn, lqa) : lnn;
             if (SAMPLE) {
                 // a draw on the boundary of the support (probability 0) has
                 // p = 0: a finite ln q makes its weight exactly 0
                 if (!(lp > -INFINITY) || !(lq > -INFINITY)) lq = 0.0;
-                for (int d = 0; d < D; d++) x_io[d * ld + i] = x[d];
                 if (ln_p) ln_p[i] = lp;
             }
             ln_q[i] = lq;
         }
-        __syncthreads();
+        wave_lds_sync();
     }
 }
 
@@ -1172,9 +1318,9 @@ hipError_t ile_launch_mdn_logpdf(const ile_mdn_dev &M, const ile_mdn_mix &mix, c
 {
     if (n <= 0) return hipSuccess;
     if (mix.nb > MAXB) return hipErrorInvalidValue;
-    const int64_t tiles = (n + 63) / 64;
+    const int64_t tiles = (n + 15) / 16;
     grid = (int)std::min<int64_t>(tiles, std::max(grid, 1));
-    hipLaunchKernelGGL(k_mdn_infer<false>, dim3(grid), dim3(256), 0, st, M.theta, M.W2b, M.W3b,
+    hipLaunchKernelGGL(k_mdn_infer<false>, dim3(grid), dim3(IT), 0, st, M.theta, M.W2b, M.W3b,
                        M.tr, mix, (uint64_t)0, (int64_t)0, n, const_cast<double *>(x), ld,
                        (double *)nullptr, ln_q);
     return hipGetLastError();
@@ -1186,9 +1332,9 @@ hipError_t ile_launch_mdn_sample(const ile_mdn_dev &M, const ile_mdn_mix &mix, u
 {
     if (n <= 0) return hipSuccess;
     if (mix.nb > MAXB) return hipErrorInvalidValue;
-    const int64_t tiles = (n + 63) / 64;
+    const int64_t tiles = (n + 15) / 16;
     grid = (int)std::min<int64_t>(tiles, std::max(grid, 1));
-    hipLaunchKernelGGL(k_mdn_infer<true>, dim3(grid), dim3(256), 0, st, M.theta, M.W2b, M.W3b,
+    hipLaunchKernelGGL(k_mdn_infer<true>, dim3(grid), dim3(IT), 0, st, M.theta, M.W2b, M.W3b,
                        M.tr, mix, seed, first, n, x, ld, ln_p, ln_q);
     return hipGetLastError();
 }

@@ -312,3 +312,29 @@ def test_training_is_reproducible_and_learns(torch):
     print(f"loss {l0:.4f} -> {l2:.4f} (last minibatch {l1:.4f}); {ms:.1f} ms for 300 steps")
     assert np.array_equal(pa, pb)
     assert l2 < l0 - 0.5
+
+
+@pytest.mark.parametrize("eps", [0.0, 0.1])
+@pytest.mark.parametrize("n", [1, 15, 17, 129, 2049, 4111])
+def test_draws_do_not_depend_on_their_number(torch, n, eps):
+    """A draw belongs to its counter: n draws are the first n of 5000 bit for
+    bit (whole and partial tiles of 16, one and several per wave), and their
+    ln q is ile_prop_logpdf_dev's."""
+    inst = synth.make_instance(["D1"], 1, 4096, 4096.0, 101, 5)
+    with ile.Context(inst) as ctx:
+        ile.ile_hist_set(ctx.h, np.full(50, 0.02), np.full(50, 0.02))
+        with ile.Proposal(ctx, seed=3, sigma_scale=1.2) as p:
+            p.set_params(synth.mdn_params(41, gain=1.1))
+            p.set_transform(**_transform())
+            got = []
+            for m in (n, 5000):
+                x = torch.zeros((7, m), dtype=torch.float64, device="cuda")
+                lp, lq, lq2 = (torch.zeros(m, dtype=torch.float64, device="cuda") for _ in range(3))
+                torch.cuda.synchronize()
+                p.sample_dev(77, 0, m, x, m, lp, lq, eps=eps)
+                p.logpdf_dev(x, m, m, lq2, eps=eps)
+                p.sync()
+                assert torch.equal(lq, lq2)
+                got.append((x[:, :n].cpu(), lp[:n].cpu(), lq[:n].cpu()))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
