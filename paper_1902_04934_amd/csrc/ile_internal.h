@@ -357,7 +357,7 @@ hipError_t ile_launch_hv_bin(const double *series, int64_t m, int n_t, const dou
 #define ILE_MDN_OFF_B3 60544
 #define ILE_MDN_NPARAM 60880
 #define ILE_MDN_W3T_LD 384    // rows of the transposed W3 copy, zero past 336
-#define ILE_MDN_NPART 60928   // per-workgroup partial: grads, loss sum, weight sum
+#define ILE_MDN_NPART 36608   // per-workgroup partial: unmasked gradient tiles, loss sum, weight sum
 #define ILE_MDN_TILE 64       // samples per workgroup pass
 
 // MADE masks: hidden unit k has degree k mod 6; unit k sees inputs

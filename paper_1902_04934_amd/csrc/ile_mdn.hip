@@ -233,7 +233,6 @@ __device__ inline double ln_hist_ratio(const double *P, int nb, double ra, doubl
 
 // ---------------------------------------------------------- the layers
 // Layer 1 for sample r: units k = 32 ks + 8 g + i as BF16 A fragments.
-template <bool FAST = false>
 __device__ inline void layer1(const float *W1, int w1ld, const float *b1, const float z[7],
                               int g, v8bf A[4])
 {
@@ -245,7 +244,7 @@ __device__ inline void layer1(const float *W1, int w1ld, const float *b1, const 
             float a = b1[k];
 #pragma unroll
             for (int d = 0; d < D; d++) a = fmaf(W1[k * w1ld + d], z[d], a);
-            A[ks][i] = (__bf16)(FAST ? ftanh(a) : tanhf(a));
+            A[ks][i] = (__bf16)tanhf(a);
         }
     }
 }
@@ -661,7 +660,76 @@ __global__ __launch_bounds__(IT, 2) void k_mdn_infer(
 // Forward and backward of 64 samples (batch slots blockIdx.x*64 ..): the
 // workgroup's gradient of  L = -sum_s w_s ln q(z~_s)  (not yet divided by
 // sum w), its loss sum and weight sum go to part[blockIdx.x][.].
-__global__ __launch_bounds__(256) void k_mdn_grad(
+//
+// A batch of 16384 is 256 such workgroups, one per CU, so the time is the
+// longest chain of one wave; with a wave per 16 samples each walked all of it
+// alone and read all the weights (52.7 us a launch).  Sixteen waves share the
+// 64 samples instead, two tiles of 16 samples a wave, so that a weight
+// fragment serves both: wave w = 8 p + t takes output tile t of layer 2 and of
+// both backward products for tiles 2 p and 2 p + 1, and dimension t < 7 of the
+// mixture; the rows of the weight-gradient tiles are dealt to all sixteen.
+// Every sum keeps its order, so the gradient is the same bit for bit.  32.8 us
+// a launch: 9.6 to the end of layer 2, about 10 for the mixture (its
+// exponentials and logarithms), the rest the backward products and the rows.
+constexpr int GW = 16, GT = 64 * GW;
+
+// A partial row holds what the masks let through.  With the hidden units in
+// the order of their degree (mdn_unit), dimension d's rows of W3 use the first
+// mdn_count(d) of them and a row of W2 of degree e the first mdn_count(e + 1),
+// so of the 16 x 16 gradient tiles [output][unit] only those left of these
+// edges exist: 137 of 232, and the row is 146 KB instead of 244 (of both it is
+// the bytes written here and read by the update that count).  Then b1, b2, b3,
+// W1, the loss sum and the weight sum.
+__host__ __device__ constexpr int mdn_unit(int i)   // i-th unit by degree
+{
+    return i < 44 ? i / 22 + 6 * (i % 22) : 2 + (i - 44) / 21 + 6 * ((i - 44) % 21);
+}
+__host__ __device__ constexpr int mdn_count(int e)   // units of degree below e
+{
+    return e <= 2 ? 22 * e : 44 + 21 * (e - 2);
+}
+constexpr int N_TILE3 = 93, N_TILE = 137;   // tiles of W3, and with those of W2
+struct mdn_tiles {
+    unsigned char ot[N_TILE], kt[N_TILE];
+    int n3, n;
+};
+constexpr mdn_tiles make_tiles()
+{
+    mdn_tiles T{};
+    int n = 0;
+    for (int ot = 0; ot < O / 16; ot++)
+        for (int kt = 0; 16 * kt < mdn_count(ot / 3); kt++, n++) {
+            T.ot[n] = (unsigned char)ot;
+            T.kt[n] = (unsigned char)kt;
+        }
+    T.n3 = n;
+    for (int ot = 0; ot < H / 16; ot++)
+        for (int kt = 0; 16 * kt < mdn_count(mdn_unit(16 * ot + 15) % 6 + 1); kt++, n++) {
+            T.ot[n] = (unsigned char)ot;
+            T.kt[n] = (unsigned char)kt;
+        }
+    T.n = n;
+    return T;
+}
+static_assert(make_tiles().n3 == N_TILE3 && make_tiles().n == N_TILE, "tile counts");
+__device__ constexpr mdn_tiles kTiles = make_tiles();
+constexpr int P_B1 = 256 * N_TILE, P_B2 = P_B1 + H, P_B3 = P_B2 + H, P_W1 = P_B3 + O,
+              P_LOSS = P_W1 + H * D, P_WSUM = P_LOSS + 1;
+static_assert(P_WSUM < NPART, "partial row");
+// parameter index of entry p < P_LOSS of a partial row
+__device__ inline int mdn_param_of(int p)
+{
+    if (p < P_B1) {
+        const int tile = p >> 8, r = (p >> 4) & 15;
+        const int o = 16 * kTiles.ot[tile] + r, k = mdn_unit(16 * kTiles.kt[tile] + (p & 15));
+        return tile < N_TILE3 ? OFF_W3 + o * H + k : OFF_W2 + mdn_unit(o) * H + k;
+    }
+    return p < P_B2 ? OFF_B1 + p - P_B1
+         : p < P_B3 ? OFF_B2 + p - P_B2
+         : p < P_W1 ? OFF_B3 + p - P_B3 : OFF_W1 + p - P_W1;
+}
+constexpr int DLD = 72;    // LDS row of the last dimension's 48 outputs (of 64)
+__global__ __launch_bounds__(GT) void k_mdn_grad(
     const float *__restrict__ theta, const __bf16 *__restrict__ W2b,
     const __bf16 *__restrict__ W3b, const __bf16 *__restrict__ W2t,
     const __bf16 *__restrict__ W3t, const ile_mdn_tr *__restrict__ trp,
@@ -670,261 +738,255 @@ __global__ __launch_bounds__(256) void k_mdn_grad(
 {
     __shared__ float sZ[64 * 8];
     __shared__ float sWt[64];
+    __shared__ float sLq[D * 64];                                    // ln q_d of each sample
     __shared__ __attribute__((aligned(16))) __bf16 sH1T[H * SLD];    // h1 [unit][sample]
     __shared__ __attribute__((aligned(16))) __bf16 sH2T[H * SLD];    // h2 [unit][sample]
     __shared__ __attribute__((aligned(16))) __bf16 sDOT[O * SLD];    // dL/do [output][sample]
-    __shared__ __attribute__((aligned(16))) __bf16 sDA2T[H * SLD];   // dL/da2 [unit][sample]
-    __shared__ __attribute__((aligned(16))) __bf16 sDA1T[H * SLD];   // dL/da1 [unit][sample]
-    __shared__ __attribute__((aligned(16))) __bf16 sHs[4][16 * WLD]; // per wave: h2, then dL/da2 [s][unit]
-    __shared__ __attribute__((aligned(16))) __bf16 sDOc[4][16 * CLD];// per wave: 96 outputs of dL/do [s][o]
-    __shared__ float sLoss[4];
+    __shared__ __attribute__((aligned(16))) __bf16 sHs[4][16 * WLD]; // per tile: h2, then dL/da2 [s][unit]
+    // in turn: h1 [s][unit] of each tile; dL/do [s][o] of each tile and pair of
+    // dimensions; dL/da2 and dL/da1 [unit][sample]
+    constexpr int DOP = 16 * CLD, DOM = 3 * DOP + 16 * DLD;
+    static_assert(4 * DOM >= 2 * H * SLD && 4 * DOM >= 4 * 16 * WLD, "shared region");
+    __shared__ __attribute__((aligned(16))) __bf16 sU[4 * DOM];
     __shared__ float sPar[OFF_W2 + H + O];   // FP32 W1, b1, b2, b3
+    __bf16 *sDA2T = sU, *sDA1T = sU + H * SLD;
 
     const float *W1 = sPar, *b1 = sPar + OFF_B1, *b2 = sPar + OFF_W2,
                 *b3 = sPar + OFF_W2 + H;
     const float sfloor = (float)trp->sigma_floor;
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int s0 = 16 * w;
-    __bf16 *Hs = sHs[w], *DOc = sDOc[w];
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), t = w & 7, m0 = 2 * (w >> 3);
+    const int kr = 16 * t + r;   // the lane's unit as an output of tile t
 
     // layer-2 fragments first: their loads overlap the staging below
-    v8bf B2f[32];
+    v8bf B2f[4];
 #pragma unroll
-    for (int ks = 0; ks < 4; ks++)
-#pragma unroll
-        for (int t = 0; t < 8; t++)
-            B2f[8 * ks + t] = *(const v8bf *)(W2b + (16 * t + r) * H + 32 * ks + 8 * g);
-    if (g == 0) {
-        const int64_t b = (int64_t)blockIdx.x * 64 + s0 + r;
+    for (int ks = 0; ks < 4; ks++) B2f[ks] = *(const v8bf *)(W2b + kr * H + 32 * ks + 8 * g);
+    if (tid < 512) {
+        const int s = tid >> 3, d = tid & 7;
+        const int64_t b = (int64_t)blockIdx.x * 64 + s;
         const bool valid = b < batch;
         const int64_t row = valid ? (idx ? (int64_t)idx[b] : b) : 0;
-        for (int d = 0; d < 8; d++) sZ[(s0 + r) * 8 + d] = (valid && d < D) ? zt[d * ldz + row] : 0.f;
-        sWt[s0 + r] = valid ? (wts ? (float)wts[row] : 1.f) : 0.f;
+        sZ[s * 8 + d] = (valid && d < D) ? zt[d * ldz + row] : 0.f;
+        if (d == 7) sWt[s] = valid ? (wts ? (float)wts[row] : 1.f) : 0.f;
     }
-    for (int e = tid; e < OFF_W2 + H + O; e += 256)
+    for (int e = tid; e < OFF_W2 + H + O; e += GT)
         sPar[e] = e < OFF_W2 ? theta[OFF_W1 + e]
                 : e < OFF_W2 + H ? theta[OFF_B2 + e - OFF_W2] : theta[OFF_B3 + e - OFF_W2 - H];
     __syncthreads();
 
-    // ---- forward
-    v8bf A1[4];
+    // ---- layer 1: wave (m, q) takes units 32 q + 8 g .. of tile m
     {
+        const int m = w >> 2, q = w & 3;
         float z[7];
 #pragma unroll
-        for (int d = 0; d < D; d++) z[d] = sZ[(s0 + r) * 8 + d];
-        layer1<true>(W1, D, b1, z, g, A1);
+        for (int d = 0; d < D; d++) z[d] = sZ[(16 * m + r) * 8 + d];
+        v8bf A;
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+            const int k = 32 * q + 8 * g + i;
+            float a = b1[k];
+#pragma unroll
+            for (int d = 0; d < D; d++) a = fmaf(W1[k * D + d], z[d], a);
+            A[i] = (__bf16)ftanh(a);
+            sH1T[k * SLD + 16 * m + r] = A[i];
+        }
+        *(v8bf *)(sU + m * 16 * WLD + r * WLD + 32 * q + 8 * g) = A;
     }
-#pragma unroll
-    for (int ks = 0; ks < 4; ks++)
-#pragma unroll
-        for (int i = 0; i < 8; i++) sH1T[(32 * ks + 8 * g + i) * SLD + s0 + r] = A1[ks][i];
-    float h2v[8][4];
+    __syncthreads();
+    // ---- layer 2
+    float h2v[2][4];
     {
-        v4f acc[8];
-#pragma unroll
-        for (int t = 0; t < 8; t++) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
+        v4f acc[2];
+        acc[0] = acc[1] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < 4; ks++)
 #pragma unroll
-            for (int t = 0; t < 8; t++) acc[t] = mfma(A1[ks], B2f[8 * ks + t], acc[t]);
+            for (int h = 0; h < 2; h++) {
+                const v8bf A = *(const v8bf *)(sU + ((m0 + h) * 16 + r) * WLD + 32 * ks + 8 * g);
+                acc[h] = mfma(A, B2f[ks], acc[h]);
+            }
+        const float bb = b2[kr];
 #pragma unroll
-        for (int t = 0; t < 8; t++) {
-            const float bb = b2[16 * t + r];
+        for (int h = 0; h < 2; h++) {
             v4bf pk;
 #pragma unroll
             for (int v = 0; v < 4; v++) {
-                const float h = ftanh(acc[t][v] + bb);
-                h2v[t][v] = h;
-                pk[v] = (__bf16)h;
-                Hs[(4 * g + v) * WLD + 16 * t + r] = pk[v];
+                const float x = ftanh(acc[h][v] + bb);
+                h2v[h][v] = x;
+                pk[v] = (__bf16)x;
+                sHs[m0 + h][(4 * g + v) * WLD + kr] = pk[v];
             }
-            *(v4bf *)(sH2T + (16 * t + r) * SLD + s0 + 4 * g) = pk;
+            *(v4bf *)(sH2T + kr * SLD + 16 * (m0 + h) + 4 * g) = pk;
         }
     }
-    wave_lds_sync();   // Hs is the wave's own; sH2T is read after later barriers
-    v8bf A2[4];
-#pragma unroll
-    for (int ks = 0; ks < 4; ks++) A2[ks] = *(const v8bf *)(Hs + r * WLD + 32 * ks + 8 * g);
-
-    // ---- layer 3, mixture gradients and dL/dh2, two dimensions at a time.
-    // The W3 fragments of the next dimension and the W3^T fragments of the
-    // current pair are loaded ahead of the arithmetic that needs them.
-    v4f dh2[8];
-#pragma unroll
-    for (int t = 0; t < 8; t++) dh2[t] = v4f{0.f, 0.f, 0.f, 0.f};
-    float lacc = 0.f;
     v8bf Bn[12];
-    load_w3_dim(W3b, H, 0, r, g, Bn);
-#pragma unroll 1
-    for (int p = 0; p < 4; p++) {
-        v8bf Bt[24];
-#pragma unroll
-        for (int ks = 0; ks < 3; ks++)
-#pragma unroll
-            for (int t = 0; t < 8; t++)
-                Bt[8 * ks + t] = *(const v8bf *)(W3t + (16 * t + r) * W3T_LD + 96 * p + 32 * ks + 8 * g);
-#pragma unroll
-        for (int dd = 0; dd < 2; dd++) {
-            const int d = 2 * p + dd;
-            if (d < D) {
-                v8bf Bc[12];
-#pragma unroll
-                for (int j = 0; j < 12; j++) Bc[j] = Bn[j];
-                if (d + 1 < D) load_w3_dim(W3b, H, d + 1, r, g, Bn);
-                v4f t3[3];
-#pragma unroll
-                for (int j = 0; j < 3; j++) t3[j] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int ks = 0; ks < 4; ks++)
-#pragma unroll
-                    for (int j = 0; j < 3; j++) t3[j] = mfma(A2[ks], Bc[3 * ks + j], t3[j]);
-                v4bf ga, gm, gr;
-#pragma unroll
-                for (int v = 0; v < 4; v++) {
-                    const int s = 4 * g + v;
-                    const float al = t3[0][v] + b3[48 * d + r];
-                    const float mu = t3[1][v] + b3[48 * d + 16 + r];
-                    const float rho = t3[2][v] + b3[48 * d + 32 + r];
-                    const float ws = sWt[s0 + s];
-                    float rs, rr, ell, la;
-                    const float lq = mix_lnq_fast(al, mu, rho, sZ[(s0 + s) * 8 + d], sfloor, rs, rr, ell, la);
-                    const float gam = fexp(ell - lq), pi = fexp(al - la);
-                    if (r == 0) lacc -= ws * lq;
-                    ga[v] = (__bf16)(-ws * (gam - pi));
-                    gm[v] = (__bf16)(-ws * gam * rr * rs);
-                    gr[v] = (__bf16)(-ws * gam * (rr * rr - 1.f) * rs * fsigmoid(rho));
-                    DOc[s * CLD + 48 * dd + r] = ga[v];
-                    DOc[s * CLD + 48 * dd + 16 + r] = gm[v];
-                    DOc[s * CLD + 48 * dd + 32 + r] = gr[v];
-                }
-                *(v4bf *)(sDOT + (48 * d + r) * SLD + s0 + 4 * g) = ga;
-                *(v4bf *)(sDOT + (48 * d + 16 + r) * SLD + s0 + 4 * g) = gm;
-                *(v4bf *)(sDOT + (48 * d + 32 + r) * SLD + s0 + 4 * g) = gr;
-            } else {
-#pragma unroll
-                for (int v = 0; v < 4; v++)
-#pragma unroll
-                    for (int j = 0; j < 3; j++) DOc[(4 * g + v) * CLD + 48 * dd + 16 * j + r] = (__bf16)0.f;
-            }
-        }
-        wave_lds_sync();   // DOc is the wave's own
-#pragma unroll
-        for (int ks = 0; ks < 3; ks++) {
-            const v8bf a = *(const v8bf *)(DOc + r * CLD + 32 * ks + 8 * g);
-#pragma unroll
-            for (int t = 0; t < 8; t++) dh2[t] = mfma(a, Bt[8 * ks + t], dh2[t]);
-        }
-        wave_lds_sync();
-    }
+    if (t < D) load_w3_dim(W3b, H, t, r, g, Bn);
+    __syncthreads();
 
+    // ---- layer 3 and the mixture's gradients, dimension t
+    if (t < D) {
+        const int d = t, p = d >> 1, dd = d & 1;
+        const int cld = p < 3 ? CLD : DLD;
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const int m = m0 + h, s0 = 16 * m;
+            __bf16 *DOc = sU + m * DOM + p * DOP;
+            v4f t3[3];
+#pragma unroll
+            for (int j = 0; j < 3; j++) t3[j] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < 4; ks++) {
+                const v8bf A = *(const v8bf *)(sHs[m] + r * WLD + 32 * ks + 8 * g);
+#pragma unroll
+                for (int j = 0; j < 3; j++) t3[j] = mfma(A, Bn[3 * ks + j], t3[j]);
+            }
+            v4bf ga, gm, gr;
+#pragma unroll
+            for (int v = 0; v < 4; v++) {
+                const int s = 4 * g + v;
+                const float al = t3[0][v] + b3[48 * d + r];
+                const float mu = t3[1][v] + b3[48 * d + 16 + r];
+                const float rho = t3[2][v] + b3[48 * d + 32 + r];
+                const float ws = sWt[s0 + s];
+                float rs, rr, ell, la;
+                const float lq = mix_lnq_fast(al, mu, rho, sZ[(s0 + s) * 8 + d], sfloor, rs, rr, ell, la);
+                const float gam = fexp(ell - lq), pi = fexp(al - la);
+                if (r == 0) sLq[d * 64 + s0 + s] = lq;
+                ga[v] = (__bf16)(-ws * (gam - pi));
+                gm[v] = (__bf16)(-ws * gam * rr * rs);
+                gr[v] = (__bf16)(-ws * gam * (rr * rr - 1.f) * rs * fsigmoid(rho));
+                DOc[s * cld + 48 * dd + r] = ga[v];
+                DOc[s * cld + 48 * dd + 16 + r] = gm[v];
+                DOc[s * cld + 48 * dd + 32 + r] = gr[v];
+            }
+            *(v4bf *)(sDOT + (48 * d + r) * SLD + s0 + 4 * g) = ga;
+            *(v4bf *)(sDOT + (48 * d + 16 + r) * SLD + s0 + 4 * g) = gm;
+            *(v4bf *)(sDOT + (48 * d + 32 + r) * SLD + s0 + 4 * g) = gr;
+        }
+    } else {
+        // outputs 48 .. 63 of the last pair: the padding of its K
+#pragma unroll
+        for (int h = 0; h < 2; h++)
+#pragma unroll
+            for (int v = 0; v < 4; v++)
+                sU[(m0 + h) * DOM + 3 * DOP + (4 * g + v) * DLD + 48 + r] = (__bf16)0.f;
+    }
+    // the backward fragments, in flight across the barrier
+    v8bf Bt[11];
+#pragma unroll
+    for (int c = 0; c < 11; c++)
+        Bt[c] = *(const v8bf *)(W3t + kr * W3T_LD + 32 * c + 8 * g);
+    __syncthreads();
+
+    // ---- dL/dh2 = dL/do W3 (pair p is outputs 96 p ..; the last k-step of the
+    // last pair would be all zeros)
+    v4f dh[2];
+    dh[0] = dh[1] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < 11; c++) {
+        const int p = c / 3, ks = c % 3, cld = p < 3 ? CLD : DLD;
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const v8bf A = *(const v8bf *)(sU + (m0 + h) * DOM + p * DOP + r * cld + 32 * ks + 8 * g);
+            dh[h] = mfma(A, Bt[c], dh[h]);
+        }
+    }
+    v8bf B2[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ks++) B2[ks] = *(const v8bf *)(W2t + kr * H + 32 * ks + 8 * g);
+    __syncthreads();   // sU changes hands
     // ---- dL/da2 = dL/dh2 (1 - h2^2)
-    v8bf B2[32];
 #pragma unroll
-    for (int ks = 0; ks < 4; ks++)
-#pragma unroll
-        for (int t = 0; t < 8; t++)
-            B2[8 * ks + t] = *(const v8bf *)(W2t + (16 * t + r) * H + 32 * ks + 8 * g);
-#pragma unroll
-    for (int t = 0; t < 8; t++) {
+    for (int h = 0; h < 2; h++) {
         v4bf pk;
 #pragma unroll
         for (int v = 0; v < 4; v++) {
-            pk[v] = (__bf16)(dh2[t][v] * (1.f - h2v[t][v] * h2v[t][v]));
-            Hs[(4 * g + v) * WLD + 16 * t + r] = pk[v];
+            pk[v] = (__bf16)(dh[h][v] * (1.f - h2v[h][v] * h2v[h][v]));
+            sHs[m0 + h][(4 * g + v) * WLD + kr] = pk[v];
         }
-        *(v4bf *)(sDA2T + (16 * t + r) * SLD + s0 + 4 * g) = pk;
+        *(v4bf *)(sDA2T + kr * SLD + 16 * (m0 + h) + 4 * g) = pk;
     }
-    wave_lds_sync();   // Hs is the wave's own; sDA2T is read after later barriers
+    __syncthreads();
 
     // ---- dL/dh1 = W2^T dL/da2, dL/da1 = dL/dh1 (1 - h1^2), h1 recomputed in FP32
     {
-        v8bf Ad[4];
-#pragma unroll
-        for (int ks = 0; ks < 4; ks++) Ad[ks] = *(const v8bf *)(Hs + r * WLD + 32 * ks + 8 * g);
-        v4f dh1[8];
-#pragma unroll
-        for (int t = 0; t < 8; t++) dh1[t] = v4f{0.f, 0.f, 0.f, 0.f};
+        v4f dh1[2];
+        dh1[0] = dh1[1] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < 4; ks++)
 #pragma unroll
-            for (int t = 0; t < 8; t++) dh1[t] = mfma(Ad[ks], B2[8 * ks + t], dh1[t]);
+            for (int h = 0; h < 2; h++) {
+                const v8bf A = *(const v8bf *)(sHs[m0 + h] + r * WLD + 32 * ks + 8 * g);
+                dh1[h] = mfma(A, B2[ks], dh1[h]);
+            }
+        float wk[7];
 #pragma unroll
-        for (int t = 0; t < 8; t++) {
-            const int k = 16 * t + r;
-            float wk[7];
+        for (int d = 0; d < D; d++) wk[d] = W1[kr * D + d];
+        const float bk = b1[kr];
 #pragma unroll
-            for (int d = 0; d < D; d++) wk[d] = W1[k * D + d];
-            const float bk = b1[k];
+        for (int h = 0; h < 2; h++) {
             v4bf pk;
 #pragma unroll
             for (int v = 0; v < 4; v++) {
-                const int s = s0 + 4 * g + v;
+                const int s = 16 * (m0 + h) + 4 * g + v;
                 float a = bk;
 #pragma unroll
                 for (int d = 0; d < D; d++) a = fmaf(wk[d], sZ[s * 8 + d], a);
-                const float h = ftanh(a);
-                pk[v] = (__bf16)(dh1[t][v] * (1.f - h * h));
+                const float x = ftanh(a);
+                pk[v] = (__bf16)(dh1[h][v] * (1.f - x * x));
             }
-            *(v4bf *)(sDA1T + k * SLD + s0 + 4 * g) = pk;
+            *(v4bf *)(sDA1T + kr * SLD + 16 * (m0 + h) + 4 * g) = pk;
         }
     }
-    lacc += __shfl_xor(lacc, 16);
-    lacc += __shfl_xor(lacc, 32);
-    if (lane == 0) sLoss[w] = lacc;
     __syncthreads();
 
     // ---- weight gradients over the workgroup's 64 samples
     float *P = part + (size_t)blockIdx.x * NPART;
     // (products taken as (dL/dW)^T tiles, so that each lane holds four
-    // consecutive k of one output row: one 16-byte store per lane and tile)
-    for (int q = w; q < 21 * 8; q += 4) {
-        const int ot = q >> 3, kt = q & 7;
+    // consecutive units of one output row: a tile is one 1 KB store)
+    for (int e = w; e < N_TILE; e += GW) {
+        const bool third = e < N_TILE3;
+        const int o = 16 * kTiles.ot[e] + r, k = mdn_unit(16 * kTiles.kt[e] + r);
+        const __bf16 *G = (third ? sDOT + o * SLD : sDA2T + mdn_unit(o) * SLD) + 8 * g;
+        const __bf16 *X = (third ? sH2T : sH1T) + k * SLD + 8 * g;
         v4f a = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int ks = 0; ks < 2; ks++) {
-            const v8bf A = *(const v8bf *)(sDOT + (16 * ot + r) * SLD + 32 * ks + 8 * g);
-            const v8bf B = *(const v8bf *)(sH2T + (16 * kt + r) * SLD + 32 * ks + 8 * g);
-            a = mfma(B, A, a);
-        }
-        *(v4f *)(P + OFF_W3 + (16 * ot + r) * H + 16 * kt + 4 * g) = a;
+        for (int ks = 0; ks < 2; ks++)
+            a = mfma(*(const v8bf *)(X + 32 * ks), *(const v8bf *)(G + 32 * ks), a);
+        *(v4f *)(P + 256 * e + 16 * r + 4 * g) = a;
     }
-    for (int q = w; q < 8 * 8; q += 4) {
-        const int ot = q >> 3, kt = q & 7;
-        v4f a = v4f{0.f, 0.f, 0.f, 0.f};
+    // biases, W1, the loss and the weight sum: one sum a thread
+    for (int e = tid; e < O + 2 * H + H * D; e += GT) {
+        if (e < O + 2 * H) {
+            const __bf16 *row = e < O ? sDOT + e * SLD
+                              : e < O + H ? sDA2T + (e - O) * SLD : sDA1T + (e - O - H) * SLD;
+            float acc = 0.f;
+            for (int s = 0; s < 64; s++) acc += (float)row[s];
+            P[e < O ? P_B3 + e : e < O + H ? P_B2 + e - O : P_B1 + e - O - H] = acc;
+        } else if (e < O + 2 * H + H * D) {
+            const int f = e - O - 2 * H, k = f / D, d = f % D;
+            float acc = 0.f;
+            for (int s = 0; s < 64; s++) acc = fmaf((float)sDA1T[k * SLD + s], sZ[s * 8 + d], acc);
+            P[P_W1 + f] = acc;
+        }
+    }
+    if (w == GW - 1 && lane < 16) {
+        // lane 4 m + g: samples 16 m + 4 g .. of tile m, then the tiles in order
+        float l = 0.f;
 #pragma unroll
-        for (int ks = 0; ks < 2; ks++) {
-            const v8bf A = *(const v8bf *)(sDA2T + (16 * ot + r) * SLD + 32 * ks + 8 * g);
-            const v8bf B = *(const v8bf *)(sH1T + (16 * kt + r) * SLD + 32 * ks + 8 * g);
-            a = mfma(B, A, a);
+        for (int d = 0; d < D; d++)
+#pragma unroll
+            for (int v = 0; v < 4; v++) l -= sWt[4 * lane + v] * sLq[d * 64 + 4 * lane + v];
+        l += __shfl_xor(l, 1);
+        l += __shfl_xor(l, 2);
+        const float l1 = __shfl(l, 4), l2 = __shfl(l, 8), l3 = __shfl(l, 12);
+        if (lane == 0) {
+            P[P_LOSS] = l + l1 + l2 + l3;
+            float ws = 0.f;
+            for (int s = 0; s < 64; s++) ws += sWt[s];
+            P[P_WSUM] = ws;
         }
-        *(v4f *)(P + OFF_W2 + (16 * ot + r) * H + 16 * kt + 4 * g) = a;
-    }
-    for (int o = tid; o < O; o += 256) {
-        float acc = 0.f;
-        for (int s = 0; s < 64; s++) acc += (float)sDOT[o * SLD + s];
-        P[OFF_B3 + o] = acc;
-    }
-    for (int k = tid; k < H; k += 256) {
-        float a2 = 0.f, a1 = 0.f;
-        for (int s = 0; s < 64; s++) {
-            a2 += (float)sDA2T[k * SLD + s];
-            a1 += (float)sDA1T[k * SLD + s];
-        }
-        P[OFF_B2 + k] = a2;
-        P[OFF_B1 + k] = a1;
-    }
-    for (int e = tid; e < H * D; e += 256) {
-        const int k = e / D, d = e % D;
-        float acc = 0.f;
-        for (int s = 0; s < 64; s++) acc = fmaf((float)sDA1T[k * SLD + s], sZ[s * 8 + d], acc);
-        P[OFF_W1 + e] = acc;
-    }
-    if (tid == 0) {
-        P[NPARAM] = sLoss[0] + sLoss[1] + sLoss[2] + sLoss[3];
-        float ws = 0.f;
-        for (int s = 0; s < 64; s++) ws += sWt[s];
-        P[NPARAM + 1] = ws;
     }
 }
 
@@ -950,38 +1012,46 @@ __global__ __launch_bounds__(256) void k_mdn_cast(ile_mdn_dev M)
 
 // Sum the partial rows in a fixed order, mask, normalize by the weight sum;
 // then one Adam step (beta1 0.9, beta2 0.999, eps 1e-8) on the FP32 weights
-// and refresh the BF16 copies.  A workgroup serves 64 parameters with four
-// row slices each (rows s, s+4, s+8, ...), so the read of all rows runs at
-// four times the occupancy; the slices combine in slice order.
-constexpr int UPD_P = 64;   // parameters per workgroup
+// and refresh the BF16 copies.  A workgroup serves 64 entries of the rows with
+// four row slices each (rows s, s+4, s+8, ...), so the read of all rows runs at
+// four times the occupancy; the slices combine in slice order.  Bound by that
+// read, which runs at the rate of a large copy (37 MB of a batch of 16384 in
+// 8.5 us; 12.2 us when the rows held the masked entries too).  A masked
+// parameter's gradient
+// is zero: its weight and moments are zeros and stay so (grad, if wanted, holds
+// zeros there already).
+constexpr int UPD_P = 64;   // entries per workgroup
 __global__ __launch_bounds__(256) void k_mdn_update(ile_mdn_dev M, const float *__restrict__ part,
                                                     int np, float *grad, double *loss, int adam,
                                                     float bc1, float bc2, float lr)
 {
     __shared__ float red_g[4][UPD_P], red_w[4][UPD_P];
     const int jj = threadIdx.x & (UPD_P - 1), sl = threadIdx.x / UPD_P;
-    const int j = blockIdx.x * UPD_P + jj;
+    const int p = blockIdx.x * UPD_P + jj;
     float ws = 0.f, gs = 0.f;
-    if (j < NPARAM) {
+    if (p < P_LOSS) {
         // the loads are independent, so unrolling lets many be in flight
 #pragma unroll 8
         for (int t = sl; t < np; t += 4) {
-            ws += part[(size_t)t * NPART + NPARAM + 1];
-            gs += part[(size_t)t * NPART + j];
+            ws += part[(size_t)t * NPART + P_WSUM];
+            gs += part[(size_t)t * NPART + p];
         }
     }
     red_g[sl][jj] = gs;
     red_w[sl][jj] = ws;
     __syncthreads();
-    if (sl != 0 || j >= NPARAM) return;
+    if (sl != 0 || p >= P_LOSS) return;
     gs = ((red_g[0][jj] + red_g[1][jj]) + red_g[2][jj]) + red_g[3][jj];
     ws = ((red_w[0][jj] + red_w[1][jj]) + red_w[2][jj]) + red_w[3][jj];
-    const float gj = (ws > 0.f && ile_mdn_trainable(j)) ? gs / ws : 0.f;
-    if (j == 0 && loss) {
+    if (p == 0 && loss) {
         float ls = 0.f;
-        for (int t = 0; t < np; t++) ls += part[(size_t)t * NPART + NPARAM];
+#pragma unroll 16
+        for (int t = 0; t < np; t++) ls += part[(size_t)t * NPART + P_LOSS];
         *loss = ws > 0.f ? (double)ls / (double)ws : 0.0;
     }
+    const int j = mdn_param_of(p);
+    if (!ile_mdn_trainable(j)) return;
+    const float gj = ws > 0.f ? gs / ws : 0.f;
     if (grad) grad[j] = gj;
     if (!adam) return;
     const float m = 0.9f * M.m[j] + 0.1f * gj;
@@ -1048,14 +1118,32 @@ __global__ __launch_bounds__(256) void k_fit_max(const double *__restrict__ lnw,
     if (threadIdx.x == 0) P[0] = bm;
 }
 
-__global__ void k_fit_init(double *ws, double ess_frac)
+// The single-workgroup steps fetch the FB block partials with all their lanes
+// (one memory round trip instead of one a partial: 41 us for the moments) into
+// LDS, then one thread a sum adds them in block order.
+template <int NV>
+__device__ inline void fetch_parts(const double *ws, double (*sp)[FB + 1])
 {
+    for (int e = threadIdx.x; e < FB * NV; e += blockDim.x)
+        sp[e % NV][e / NV] = ws[16 + (e / NV) * 16 + e % NV];
+    __syncthreads();
+}
+__device__ inline double sum_parts(const double *sp)
+{
+    double v = 0.0;
+#pragma unroll 16
+    for (int b = 0; b < FB; b++) v += sp[b];
+    return v;
+}
+
+__global__ __launch_bounds__(256) void k_fit_init(double *ws, double ess_frac)
+{
+    __shared__ double sp[2][FB + 1];
+    fetch_parts<2>(ws, sp);
     if (threadIdx.x != 0) return;
-    double mx = -INFINITY, cnt = 0.0;
-    for (int b = 0; b < FB; b++) {
-        mx = fmax(mx, ws[16 + b * 16]);
-        cnt += ws[16 + b * 16 + 1];
-    }
+    double mx = -INFINITY;
+    const double cnt = sum_parts(sp[1]);
+    for (int b = 0; b < FB; b++) mx = fmax(mx, sp[0][b]);
     ws[S_MAX] = mx;
     ws[S_CNT] = cnt;
     ws[S_TARGET] = fmax(1.0, ess_frac * cnt);
@@ -1083,14 +1171,13 @@ __global__ __launch_bounds__(256) void k_fit_ess_part(const double *__restrict__
 }
 
 // it = 0 judges beta = 1; it = 1..30 halve [lo, hi]
-__global__ void k_fit_ess_step(double *ws, int it)
+__global__ __launch_bounds__(256) void k_fit_ess_step(double *ws, int it)
 {
-    if (threadIdx.x != 0 || ws[S_DONE] != 0.0) return;
-    double s1 = 0.0, s2 = 0.0;
-    for (int b = 0; b < FB; b++) {
-        s1 += ws[16 + b * 16];
-        s2 += ws[16 + b * 16 + 1];
-    }
+    __shared__ double sp[2][FB + 1];
+    if (ws[S_DONE] != 0.0) return;   // uniform: thread 0 writes it after the barrier
+    fetch_parts<2>(ws, sp);
+    if (threadIdx.x != 0) return;
+    const double s1 = sum_parts(sp[0]), s2 = sum_parts(sp[1]);
     const bool ok = s2 > 0.0 && s1 * s1 / s2 >= ws[S_TARGET];
     if (it == 0) {
         if (ok) {
@@ -1134,18 +1221,15 @@ __global__ __launch_bounds__(256) void k_fit_circ_part(const double *__restrict_
     block_sums256<6>(v, red, ws + 16 + blockIdx.x * 16);
 }
 
-__global__ void k_fit_circ_fin(double *ws, ile_mdn_tr *tr)
+__global__ __launch_bounds__(256) void k_fit_circ_fin(double *ws, ile_mdn_tr *tr)
 {
-    if (threadIdx.x != 0) return;
+    __shared__ double sp[6][FB + 1];
+    fetch_parts<6>(ws, sp);
+    const int j = threadIdx.x;
+    if (j >= 3) return;
     const double per[3] = {kTwoPi, kPi, kTwoPi};
-    for (int j = 0; j < 3; j++) {
-        double sc = 0.0, ss = 0.0;
-        for (int b = 0; b < FB; b++) {
-            sc += ws[16 + b * 16 + 2 * j];
-            ss += ws[16 + b * 16 + 2 * j + 1];
-        }
-        tr->origin[j] = atan2(ss, sc) * per[j] / kTwoPi;
-    }
+    const double sc = sum_parts(sp[2 * j]), ss = sum_parts(sp[2 * j + 1]);
+    tr->origin[j] = atan2(ss, sc) * per[j] / kTwoPi;
 }
 
 __global__ __launch_bounds__(256) void k_fit_mom_part(const double *__restrict__ x, int64_t ld,
@@ -1184,14 +1268,13 @@ __global__ void k_fit_stats_only(const double *ws, double *stats)
     stats[1] = ws[S_BETA];
 }
 
-__global__ void k_fit_mom_fin(double *ws, ile_mdn_tr *tr, double *stats)
+__global__ __launch_bounds__(256) void k_fit_mom_fin(double *ws, ile_mdn_tr *tr, double *stats)
 {
+    __shared__ double sp[15][FB + 1], v[15];
+    fetch_parts<15>(ws, sp);
+    if (threadIdx.x < 15) v[threadIdx.x] = sum_parts(sp[threadIdx.x]);
+    __syncthreads();
     if (threadIdx.x != 0) return;
-    double v[15];
-    for (int q = 0; q < 15; q++) {
-        v[q] = 0.0;
-        for (int b = 0; b < FB; b++) v[q] += ws[16 + b * 16 + q];
-    }
     for (int d = 0; d < D; d++) {
         const double m = v[0] > 0 ? v[1 + d] / v[0] : 0.0;
         const double var = v[0] > 0 ? v[8 + d] / v[0] - m * m : 1.0;
@@ -1241,31 +1324,45 @@ __global__ __launch_bounds__(256) void k_mdn_cdf_part(const double *__restrict__
 
 // exclusive scan of the CB * 256 chunk totals: each of 256 threads scans 64
 // consecutive totals, thread 0 scans the 256 thread sums, each thread adds
-// its offset (fixed order)
+// its offset (fixed order).  The totals pass through LDS, so that memory is
+// read and written in order and the chains run on LDS and registers (21 us as
+// a chain of strided loads and stores).
 __global__ __launch_bounds__(256) void k_mdn_cdf_scan(double *tot)
 {
-    __shared__ double ts[256];
     constexpr int PER = CB;   // CB * 256 totals over 256 threads
-    double *mine = tot + (size_t)threadIdx.x * PER;
-    double run = 0.0;
-    for (int i = 0; i < PER; i++) {
-        const double v = mine[i];
-        mine[i] = run;
-        run += v;
-    }
-    ts[threadIdx.x] = run;
+    __shared__ double st[256][PER + 1], ts[256];
+    const int tid = threadIdx.x;
+#pragma unroll 16
+    for (int e = tid; e < 256 * PER; e += 256) st[e / PER][e % PER] = tot[e];
     __syncthreads();
-    if (threadIdx.x == 0) {
+    double run = 0.0, ex[PER];
+#pragma unroll
+    for (int i = 0; i < PER; i++) {
+        ex[i] = run;
+        run += st[tid][i];
+    }
+    ts[tid] = run;
+    __syncthreads();
+    if (tid == 0) {
         double acc = 0.0;
-        for (int t = 0; t < 256; t++) {
-            const double v = ts[t];
-            ts[t] = acc;
-            acc += v;
+        for (int t0 = 0; t0 < 256; t0 += 32) {
+            double v[32];
+#pragma unroll
+            for (int i = 0; i < 32; i++) v[i] = ts[t0 + i];
+#pragma unroll
+            for (int i = 0; i < 32; i++) {
+                ts[t0 + i] = acc;
+                acc += v[i];
+            }
         }
     }
     __syncthreads();
-    const double off = ts[threadIdx.x];
-    for (int i = 0; i < PER; i++) mine[i] += off;
+    const double off = ts[tid];
+#pragma unroll
+    for (int i = 0; i < PER; i++) st[tid][i] = ex[i] + off;
+    __syncthreads();
+#pragma unroll 16
+    for (int e = tid; e < 256 * PER; e += 256) tot[e] = st[e / PER][e % PER];
 }
 
 __global__ __launch_bounds__(256) void k_mdn_cdf_write(const double *__restrict__ w, int64_t n,
@@ -1345,17 +1442,17 @@ hipError_t ile_launch_mdn_fit(const double *x, int64_t ld, const double *lnw, in
 {
     if (n <= 0) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_fit_max, dim3(FB), dim3(256), 0, st, lnw, n, ws);
-    hipLaunchKernelGGL(k_fit_init, dim3(1), dim3(64), 0, st, ws, ess_frac);
+    hipLaunchKernelGGL(k_fit_init, dim3(1), dim3(256), 0, st, ws, ess_frac);
     for (int it = 0; it <= 30; it++) {
         hipLaunchKernelGGL(k_fit_ess_part, dim3(FB), dim3(256), 0, st, lnw, n, ws);
-        hipLaunchKernelGGL(k_fit_ess_step, dim3(1), dim3(64), 0, st, ws, it);
+        hipLaunchKernelGGL(k_fit_ess_step, dim3(1), dim3(256), 0, st, ws, it);
     }
     if (fit_transform) {
         hipLaunchKernelGGL(k_fit_circ_part, dim3(FB), dim3(256), 0, st, x, ld, lnw, n, ws);
-        hipLaunchKernelGGL(k_fit_circ_fin, dim3(1), dim3(64), 0, st, ws, tr);
+        hipLaunchKernelGGL(k_fit_circ_fin, dim3(1), dim3(256), 0, st, ws, tr);
         hipLaunchKernelGGL(k_fit_mom_part, dim3(FB), dim3(256), 0, st, x, ld, lnw, n,
                            (const ile_mdn_tr *)tr, ws);
-        hipLaunchKernelGGL(k_fit_mom_fin, dim3(1), dim3(64), 0, st, ws, tr, stats);
+        hipLaunchKernelGGL(k_fit_mom_fin, dim3(1), dim3(256), 0, st, ws, tr, stats);
     } else {
         hipLaunchKernelGGL(k_fit_stats_only, dim3(1), dim3(64), 0, st, ws, stats);
     }
@@ -1408,7 +1505,7 @@ hipError_t ile_launch_mdn_grad(const ile_mdn_dev &M, const float *z, int64_t ldz
                                hipStream_t st)
 {
     if (batch <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_mdn_grad, dim3((batch + 63) / 64), dim3(256), 0, st, M.theta, M.W2b,
+    hipLaunchKernelGGL(k_mdn_grad, dim3((batch + 63) / 64), dim3(GT), 0, st, M.theta, M.W2b,
                        M.W3b, M.W2t, M.W3t, M.tr, z, ldz, idx, w, batch, part);
     return hipGetLastError();
 }
@@ -1419,7 +1516,11 @@ hipError_t ile_launch_mdn_update(const ile_mdn_dev &M, const float *part, int n_
 {
     const double s = (double)std::max<int64_t>(step, 1);
     const float bc1 = (float)(1.0 - pow(0.9, s)), bc2 = (float)(1.0 - pow(0.999, s));
-    hipLaunchKernelGGL(k_mdn_update, dim3((NPARAM + UPD_P - 1) / UPD_P), dim3(256), 0, st, M, part,
+    if (grad) {   // the masked entries
+        hipError_t e = ile_launch_fill_u32((uint32_t *)grad, 0u, NPARAM, st);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_mdn_update, dim3((P_LOSS + UPD_P - 1) / UPD_P), dim3(256), 0, st, M, part,
                        n_part, grad, loss, adam ? 1 : 0, bc1, bc2, (float)lr);
     return hipGetLastError();
 }
