@@ -164,8 +164,9 @@ ile_status ile_set_data_fd(ile_ctx *ctx, const double *h_f, const double *d_f,
 /* The same construction on device buffers, without installing: h_f_dev
  * [n_lm][n_q][2], d_f_dev [n_det][n_q][2], psd_dev [n_det][n_q] in; Q_dev
  * [n_det][n_lm][n_q][2], U_dev and V_dev [n_det][n_lm][n_lm][2] out (every
- * buffer the caller's).  Blocking; ile_last_kernel_ms then gives the inverse
- * FFT's device time.  Errors as ile_set_data_fd. */
+ * buffer the caller's).  Blocking; ile_last_kernel_ms then gives the device
+ * time of the inverse FFT's kernels (which form U and V too).  Errors as
+ * ile_set_data_fd. */
 ile_status ile_qvu_fd_dev(ile_ctx *ctx, const double *h_f_dev, const double *d_f_dev,
                           const double *psd_dev, int64_t n_q, double df, double f_min,
                           double f_max, double t0_s, double *Q_dev, double *U_dev,

@@ -782,32 +782,28 @@ ile_status ile_qvu_fd_dev(ile_ctx *c, const double *h_f, const double *d_f, cons
     if (!(df > 0) || !std::isfinite(df) || !std::isfinite(t0_s) || std::isnan(f_min) ||
         std::isnan(f_max) || !(f_max > f_min))
         return fail(c, ILE_E_ARG, "bad df, band or t0");
-    const int nd = c->cfg.n_det, nl = c->cfg.n_lm, rows = nd * nl;
+    const int nd = c->cfg.n_det, nl = c->cfg.n_lm;
     ile_status s;
-    if ((s = ensure(c, c->fd_tmp, (size_t)rows * n_q * 16))) return s;
-    if ((s = ensure(c, c->fd_flag, 16))) return s;
+    if ((s = ensure(c, c->fd_tmp, ile_fd_tmp_bytes(n_q, nd, nl)))) return s;
     hipStream_t st = c->stream;
-    int32_t *flag = (int32_t *)c->fd_flag.p;
-    // the inverse FFT ends in Q: start in the scratch buffer when the number
-    // of its kernels (one for n_q <= 1024, else two) is odd
-    const bool odd = ile_fft_passes(n_q) & 1;
-    double *a = odd ? (double *)c->fd_tmp.p : Q, *b = odd ? Q : (double *)c->fd_tmp.p, *res = nullptr;
-    HIP_TRY(c, hipMemsetAsync(flag, 0, sizeof(int32_t), st));
-    HIP_TRY(c, ile_launch_fd_prod(h_f, d_f, psd, n_q, nd, nl, df, f_min, f_max, t0_s, a, flag, st));
+    // the flag is zero between calls: cleared when made and after an error
+    if (!c->fd_flag.p) {
+        if ((s = ensure(c, c->fd_flag, 16))) return s;
+        HIP_TRY(c, hipMemsetAsync(c->fd_flag.p, 0, 16, st));
+    }
+    int32_t *flag = (int32_t *)c->fd_flag.p, *hflag = (int32_t *)c->hpin;
     hipEvent_t e0 = next_event(c), e1 = next_event(c);
     if (!e0 || !e1) return fail(c, ILE_E_DEVICE, "hipEventCreate failed");
-    HIP_TRY(c, hipEventRecord(e0, st));
-    HIP_TRY(c, ile_launch_ifft_rows(a, b, n_q, rows, &res, st));
-    HIP_TRY(c, hipEventRecord(e1, st));
-    if (res != Q) return fail(c, ILE_E_DEVICE, "internal: FFT result buffer");
-    HIP_TRY(c, ile_launch_uv_fd(h_f, psd, n_q, nd, nl, df, f_min, f_max, U, V, st));
+    HIP_TRY(c, ile_launch_qvu(h_f, d_f, psd, n_q, nd, nl, df, f_min, f_max, t0_s, Q, U, V,
+                              c->fd_tmp.p, flag, hflag, e0, e1, st));
     HIP_TRY(c, hipStreamSynchronize(st));
     float ms = 0.f;
     if (hipEventElapsedTime(&ms, e0, e1) == hipSuccess) c->last_ms = ms;
     c->n_ev_used = 0;
-    int32_t f = 0;
-    HIP_TRY(c, hipMemcpy(&f, flag, sizeof(f), hipMemcpyDeviceToHost));
-    if (f) return fail(c, ILE_E_NUMERIC, "non-finite input or non-positive spectrum in the band");
+    if (*hflag) {
+        HIP_TRY(c, hipMemsetAsync(flag, 0, sizeof(int32_t), st));
+        return fail(c, ILE_E_NUMERIC, "non-finite input or non-positive spectrum in the band");
+    }
     return ILE_OK;
 }
 

@@ -310,19 +310,17 @@ hipError_t ile_launch_rom_z(const ile_geom &gp, const double *smp, int64_t N, co
                             int n_b, int n_pow, double *Z, int32_t *err, hipStream_t st);
 
 // ------------------------------------ Q, U, V from the frequency domain
-// prod: X [n_det][n_lm][n] complex; err bit 0 for a non-finite input or a
-// non-positive spectrum in the band.  ifft_rows: inverse FFT of `rows`
-// complex rows of n (power of two) ping-ponging between a (input) and b;
-// *result is the buffer holding the output.
-hipError_t ile_launch_fd_prod(const double *h, const double *d, const double *psd, int64_t n,
-                              int n_det, int n_lm, double df, double f_min, double f_max,
-                              double t0, double *X, int32_t *err, hipStream_t st);
-int ile_fft_passes(int64_t n);
-hipError_t ile_launch_ifft_rows(double *a, double *b, int64_t n, int rows, double **result,
-                                hipStream_t st);
-hipError_t ile_launch_uv_fd(const double *h, const double *psd, int64_t n, int n_det, int n_lm,
-                            double df, double f_min, double f_max, double *U, double *V,
-                            hipStream_t st);
+// Q [n_det][n_lm][n] complex, U, V [n_det][n_lm][n_lm] complex from the mode
+// and data transforms and the spectra (n a power of two in [2, 2^20]); err bit
+// 0 for a non-finite input or a non-positive spectrum in the band, copied to
+// the host word err_host (mapped host memory, valid once the stream has been
+// waited for).  tmp: ile_fd_tmp_bytes; the kernels that transform lie between
+// the events.
+size_t ile_fd_tmp_bytes(int64_t n, int n_det, int n_lm);
+hipError_t ile_launch_qvu(const double *h, const double *d, const double *psd, int64_t n,
+                          int n_det, int n_lm, double df, double f_min, double f_max, double t0,
+                          double *Q, double *U, double *V, void *tmp, int32_t *err,
+                          int32_t *err_host, hipEvent_t e0, hipEvent_t e1, hipStream_t st);
 
 // ------------------------------------------------ extrinsic harvest
 // weights: w = exp(ln w - max ln w), ln w = lnL + ln p - ln q (NULL: 0),

@@ -170,3 +170,43 @@ def test_fd_largest_shapes(torch, orc):
     with _Handle(c) as ctx:
         Q, U, V, _ = _dev_build(torch, ctx, c, 10.0, 900.0, -0.25)
     print("4 x 32:", _check(orc, c, Q, U, V, 10.0, 900.0, -0.25))
+
+
+@pytest.mark.parametrize("n_q,n_lm,n_det", [(4, 1, 1), (8, 2, 4), (16, 3, 1), (64, 25, 2), (2048, 32, 1),
+                                            (4096, 24, 2), (65536, 1, 1), (131072, 2, 1),
+                                            (524288, 1, 1), (1048576, 1, 2)])
+def test_fd_edges(torch, orc, n_q, n_lm, n_det):
+    """Every mixture of transform passes (radix 8, then 4 or 2; the longest
+    rows, whose sequences stand alone in a workgroup), both block sizes of the
+    U, V sums and their odd mode counts, one to four detectors.  Same
+    tolerance.  Up to 4096 lags against the oracle's direct sums (32 sampled
+    lags of the longer rows); beyond, the direct sum's own phases, 2 pi f t with
+    f t of thousands of turns, are rounded at 1e-12 and more, so every lag is
+    compared with numpy's transform of the products (f t0 taken modulo one turn,
+    exact here) and U, V with plain matrix products."""
+    modes = [(l, m) for l in range(2, 7) for m in range(-l, l + 1)][:n_lm]
+    rng = np.random.default_rng(n_q + n_lm)
+    cn = lambda *s: rng.standard_normal(s + (2,)).view(np.complex128)[..., 0]
+    c = dict(dets=[(10.0 * k, 30.0 * k, 5.0) for k in range(n_det)], modes=modes, n_q=n_q,
+             srate_hz=float(n_q), df=1.0, h_f=cn(n_lm, n_q), d_f=cn(n_det, n_q),
+             psd=rng.uniform(0.5, 2.0, (n_det, n_q)))
+    f_max = 0.3 * n_q if n_q > 16 else 1e9
+    with _Handle(c) as ctx:
+        Q, U, V, _ = _dev_build(torch, ctx, c, -1.0, f_max, -0.25)
+        Q2, U2, V2, _ = _dev_build(torch, ctx, c, -1.0, f_max, -0.25)
+    assert np.array_equal(Q, Q2) and np.array_equal(U, U2) and np.array_equal(V, V2)
+    s = None if n_q <= 64 else rng.choice(n_q, 32, replace=False)
+    if n_q <= 4096:
+        _check(orc, c, Q, U, V, -1.0, f_max, -0.25, s)
+        return
+    i = np.arange(n_q)
+    f = np.where(i < n_q // 2, i, i - n_q).astype(float)
+    w = np.where(np.abs(f) < f_max, 2.0 / c["psd"], 0.0)
+    g = w * c["d_f"] * np.exp(2j * np.pi * np.mod(-0.25 * f, 1.0))
+    h = c["h_f"]
+    hm = h[:, (-i) % n_q]
+    Qn = np.fft.ifft(h.conj()[None] * g[:, None], axis=2) * n_q
+    Un = np.stack([(h.conj() * x) @ h.T for x in w])
+    Vn = np.stack([(hm * x) @ h.T for x in w])
+    for got, want in ((Q, Qn), (U, Un), (V, Vn)):
+        assert np.abs(got - want).max() <= 1e-12 * np.abs(want).max()
