@@ -662,19 +662,9 @@ ile_status ile_set_data(ile_ctx *c, const double *Q, int64_t n_q, double t0_s,
     // the Hermitian part of U and the symmetric part of V: the only parts
     // the quadratic term of Eq. (7) sees (Re(Y^H U Y) = Y^H U_h Y,
     // Y^T V Y = Y^T V_s Y)
-    // (upper triangles, row by row, U_h and V_s interleaved per entry)
     {
-        std::vector<double> t;
-        t.reserve((size_t)nd * nl * (nl + 1) * 2);
-        for (int k = 0; k < nd; k++)
-            for (int a = 0; a < nl; a++)
-                for (int b = a; b < nl; b++) {
-                    const size_t e = ((size_t)k * nl + a) * nl + b, f = ((size_t)k * nl + b) * nl + a;
-                    t.push_back(0.5 * (U[2 * e] + U[2 * f]));
-                    t.push_back(0.5 * (U[2 * e + 1] - U[2 * f + 1]));
-                    t.push_back(0.5 * (V[2 * e] + V[2 * f]));
-                    t.push_back(0.5 * (V[2 * e + 1] + V[2 * f + 1]));
-                }
+        std::vector<double> t(ile_pack_uv_doubles(nd, nl));
+        ile_pack_uv(nd, nl, U, V, t.data());
         if ((s = ensure(c, c->uvt, t.size() * sizeof(double)))) return s;
         HIP_TRY(c, hipMemcpy(c->uvt.p, t.data(), t.size() * sizeof(double), hipMemcpyHostToDevice));
     }

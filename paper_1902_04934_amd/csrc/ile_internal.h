@@ -184,6 +184,38 @@ __host__ __device__ inline int ksp_of(int n_lm) { return (2 * n_lm + 3) / 4; }
 // holds them K-contiguous per position: [n_det][n_q][32 * ksb_of(n_lm)] bf16.
 __host__ __device__ inline int ksb_of(int n_lm) { return (6 * n_lm + 31) / 32; }
 
+// Packed triangles of the quadratic term: detector by detector, four rows a0 ..
+// a0 + 3 at a time, first their diagonal entries, then column by column b =
+// a0 + 1 .. n_lm - 1 their entries (a, b), zeros where b <= a or a >= n_lm; an
+// entry is (Re U_h, Im U_h, Re V_s, Im V_s) of the Hermitian part of U and the
+// symmetric part of V.  Four groups of zeros follow the last (they are fetched,
+// not used).  Doubles needed, then the packing itself from U, V
+// [n_det][n_lm][n_lm] complex.
+inline size_t ile_pack_uv_doubles(int n_det, int n_lm)
+{
+    size_t groups = 0;
+    for (int a0 = 0; a0 < n_lm; a0 += 4) groups += n_lm - a0;
+    return 16 * (n_det * groups + 4);
+}
+inline void ile_pack_uv(int n_det, int n_lm, const double *U, const double *V, double *out)
+{
+    memset(out, 0, ile_pack_uv_doubles(n_det, n_lm) * sizeof(double));
+    for (int k = 0; k < n_det; k++)
+        for (int a0 = 0; a0 < n_lm; a0 += 4)
+            for (int c = a0; c < n_lm; c++, out += 16)   // c = a0: the diagonal
+                for (int i = 0; i < 4 && a0 + i < n_lm; i++) {
+                    const int a = a0 + i, b = c == a0 ? a : c;
+                    if (c != a0 && b <= a) continue;
+                    const size_t e = 2 * (((size_t)k * n_lm + a) * n_lm + b),
+                                 f = 2 * (((size_t)k * n_lm + b) * n_lm + a);
+                    double *o = out + 4 * i;
+                    o[0] = 0.5 * (U[e] + U[f]);
+                    o[1] = 0.5 * (U[e + 1] - U[f + 1]);
+                    o[2] = 0.5 * (V[e] + V[f]);
+                    o[3] = 0.5 * (V[e + 1] + V[f + 1]);
+                }
+}
+
 // Tuning of the contraction kernel.
 struct ile_tune {
     int tile_samples;   // samples per workgroup tile (16)
@@ -233,11 +265,9 @@ hipError_t ile_launch_terms(const ile_geom &g, const double *smp, int64_t N,
 // Positions per launch of the terms (a multiple of 16): the buffer for N
 // samples holds ile_terms_fields x min(N, ILE_TERMS_CHUNK) doubles.
 #define ILE_TERMS_CHUNK ((int64_t)1 << 21)
-// uvt: per detector the upper triangles of the Hermitian part of U and the
-// symmetric part of V, row by row, entry (a, b >= a) at 4 (a n_lm -
-// a (a - 1) / 2 + b - a) as (Re U_h, Im U_h, Re V_s, Im V_s); terms: a buffer
-// of ile_terms_fields x cap doubles, cap >= 16 a multiple of 16 (both used
-// when ile_contract_uses_terms, else may be null).
+// uvt: the packed triangles (ile_pack_uv); terms: a buffer of
+// ile_terms_fields x cap doubles, cap >= 16 a multiple of 16 (both used when
+// ile_contract_uses_terms, else may be null).
 // smp_s, sh_s: the samples and window starts already in tile order (the
 // terms pass then reads them in order), or null (it gathers them through
 // perm).

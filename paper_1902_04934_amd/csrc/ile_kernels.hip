@@ -942,9 +942,8 @@ __device__ __forceinline__ void tile_prologue(
 // (d_ref/D) F_k and the quadratic term
 //   q = (d_ref/D)^2 / 4 sum_k [ |F_k|^2 Y^H U_h,k Y + Re(F_k^2 Y^T V_s,k Y) ]
 // with U_h the Hermitian part of U_k and V_s the symmetric part of V_k, so
-// that only b >= a enters (the off-diagonal terms twice): per detector the
-// host packs the upper triangles row by row, entry (a, b >= a) at
-// 4 (a nl - a (a - 1) / 2 + b - a) as (Re U_h, Im U_h, Re V_s, Im V_s).
+// that only b >= a enters (the off-diagonal terms twice): the host packs the
+// upper triangles (ile_pack_uv).
 // Output: tile-major, field f of position t0 + r at
 // terms[16 F (r / 16) + 16 f + r % 16]; the last n_det fields are integer
 // pairs, the sample's window start less the smallest of its tile, and in the
@@ -1034,27 +1033,71 @@ __device__ __forceinline__ double2 terms_harmonic(const ile_geom &g, const Terms
 }
 
 // Row a of detector k's part of the quadratic term (the b > a sums w_U, w_V
-// over the row's entries given), with f2 = |F|^2 and F^2 = (F2r, F2i).
+// over the row's entries given), with f2 = |F|^2 and F^2 = (F2r, F2i).  The
+// roundings are written out, so that they do not depend on the code around.
 __device__ __forceinline__ double terms_row(double2 Ya, double4 d, double ur, double ui,
                                             double vr, double vi, double f2, double F2r,
                                             double F2i)
 {
     // Y_a (V_s,aa Y_a + 2 w_V): the complex sum of the V part
-    const double wr = d.z * Ya.x - d.w * Ya.y + 2.0 * vr;
-    const double wi = d.z * Ya.y + d.w * Ya.x + 2.0 * vi;
-    const double yvr = Ya.x * wr - Ya.y * wi, yvi = Ya.x * wi + Ya.y * wr;
-    const double uq = d.x * (Ya.x * Ya.x + Ya.y * Ya.y) + 2.0 * (Ya.x * ur + Ya.y * ui);
-    return f2 * uq + (F2r * yvr - F2i * yvi);
+    const double wr = fma(2.0, vr, fma(Ya.x, d.z, -(Ya.y * d.w)));
+    const double wi = fma(2.0, vi, fma(d.z, Ya.y, Ya.x * d.w));
+    const double yvr = fma(Ya.x, wr, -(Ya.y * wi)), yvi = fma(Ya.y, wr, Ya.x * wi);
+    const double yu = fma(ur, Ya.x, ui * Ya.y), y2 = fma(Ya.x, Ya.x, Ya.y * Ya.y);
+    const double uq = fma(d.x, y2, yu + yu);
+    return fma(f2, uq, fma(F2r, yvr, -(F2i * yvi)));
 }
 
-__device__ __forceinline__ void terms_mac(double2 Yb, double4 e, double &ur, double &ui,
-                                          double &vr, double &vi)
+// Element n of a 16-lane row's 16 values, in every lane of the row.
+template <int n> __device__ __forceinline__ double row_bcast(double x)
 {
-    ur = fma(e.x, Yb.x, fma(-e.y, Yb.y, ur));
-    ui = fma(e.x, Yb.y, fma(e.y, Yb.x, ui));
-    vr = fma(e.z, Yb.x, fma(-e.w, Yb.y, vr));
-    vi = fma(e.z, Yb.y, fma(e.w, Yb.x, vi));
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, 0x150 + n, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), 0x150 + n, 0xF, 0xF, false);
+    return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
 }
+
+template <int n> __device__ __forceinline__ double4 row_quad(double x)   // elements n .. n + 3
+{
+    return make_double4(row_bcast<n>(x), row_bcast<n + 1>(x), row_bcast<n + 2>(x), row_bcast<n + 3>(x));
+}
+
+// The products of a group of four entries e (lane l holds value l % 16 of the
+// group's 16, the same in every row of lanes), the entries of four rows in one
+// column, with the column's harmonic y: for each row
+//   u += (e_x + i e_y) y, v += (e_z + i e_w) y,
+// each sum taking its e_y (e_w) product first.  An entry's value reaches the
+// lanes as the multiply-add's broadcast operand (DPP row_newbcast), which
+// costs nothing: the waits before the first one are what a DPP operand needs
+// after a vector write of its register.
+struct tri_acc {
+    double ur, ui, vr, vi;
+};
+#define TRI_F(acc, sgn, n, y)                                                                \
+    "v_fmac_f64_dpp %" acc ", " sgn "%16, %" y " row_newbcast:" n " row_mask:0xf bank_mask:0xf\n\t"
+#define TRI_E(ur, ui, vr, vi, n1, n3, y0, y1, s)                                             \
+    TRI_F(ur, s, n1, y0) TRI_F(ui, "", n1, y1) TRI_F(vr, s, n3, y0) TRI_F(vi, "", n3, y1)
+__device__ __forceinline__ void tri_mac(double e, double2 y, tri_acc (&A)[4])
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    asm("s_nop 4\n\t"
+        TRI_E("0", "1", "2", "3", "1", "3", "18", "17", "-")
+        TRI_E("4", "5", "6", "7", "5", "7", "18", "17", "-")
+        TRI_E("8", "9", "10", "11", "9", "11", "18", "17", "-")
+        TRI_E("12", "13", "14", "15", "13", "15", "18", "17", "-")
+        TRI_E("0", "1", "2", "3", "0", "2", "17", "18", "")
+        TRI_E("4", "5", "6", "7", "4", "6", "17", "18", "")
+        TRI_E("8", "9", "10", "11", "8", "10", "17", "18", "")
+        TRI_E("12", "13", "14", "15", "12", "14", "17", "18", "")
+        : "+v"(A[0].ur), "+v"(A[0].ui), "+v"(A[0].vr), "+v"(A[0].vi), "+v"(A[1].ur),
+          "+v"(A[1].ui), "+v"(A[1].vr), "+v"(A[1].vi), "+v"(A[2].ur), "+v"(A[2].ui),
+          "+v"(A[2].vr), "+v"(A[2].vi), "+v"(A[3].ur), "+v"(A[3].ui), "+v"(A[3].vr),
+          "+v"(A[3].vi)
+        : "v"(e), "v"(y.x), "v"(y.y));
+#endif
+}
+#undef TRI_E
+#undef TRI_F
 
 // Smallest (or largest) of a 16-lane row, in every lane, by DPP row rotations.
 template <bool MIN> __device__ __forceinline__ int row_red(int x)
@@ -1089,26 +1132,24 @@ __device__ __forceinline__ double *terms_slot(const ile_geom &g, double *terms, 
     return terms + (r >> 4) * (16 * (int64_t)terms_fields(g.n_det, g.n_lm)) + (r & 15);
 }
 
-// Entry i of the triangles by vector loads at a uniform address (one cache
-// line serves the wave): unlike scalar loads, which complete out of order,
-// they can be waited for one step at a time.
-__device__ __forceinline__ double4 tri_ld(__amdgpu_buffer_rsrc_t r, int i)
-{
-    typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-    const u4 lo = __builtin_amdgcn_raw_buffer_load_b128(r, 0, i * 32, 0);
-    const u4 hi = __builtin_amdgcn_raw_buffer_load_b128(r, 0, i * 32 + 16, 0);
-    const double2 x = __builtin_bit_cast(double2, lo), y = __builtin_bit_cast(double2, hi);
-    return make_double4(x.x, x.y, y.x, y.y);
-}
-
 constexpr int kTermsT = 64;    // lanes per block
 
 // Any number of modes: a lane's harmonics are an LDS row of 64 lanes
-// (conflict free, and no lane reads another's: no barrier); the triangles
-// are read four entries per step, one step ahead (tri_ld).
+// (conflict free, and no lane reads another's: no barrier), the first one, no
+// row's later column, a register: 21 modes then leave eight waves a CU.  The
+// quadratic form takes four rows of the triangle at a time: a column's
+// harmonic is read once for four entries, whose sixteen sums are independent,
+// and a group of four entries is one 8-byte load a lane (each row of 16 lanes
+// holds the whole group), issued four columns ahead; memory is one run over all
+// rows and detectors.  What is left is those loads' latency: 1e6 samples, 21
+// modes, 3 detectors take 432 us, 147 of them the harmonics and the stores,
+// against 161 for the multiply-adds at the vector rate.  A row at a time took
+// 663 with an entry as two 16-byte loads of one address (2 KB returned to the
+// wave's registers for 32 bytes) and 587 with the broadcast operand; two
+// columns ahead 454, with the first harmonic in LDS as well 484.
 __global__ __launch_bounds__(kTermsT) void k_terms(
     ile_geom g, const double *__restrict__ smp, int64_t N, const int32_t *__restrict__ perm,
-    const int32_t *__restrict__ shifts, bool in_order, const double4 *__restrict__ uvt,
+    const int32_t *__restrict__ shifts, bool in_order, const double *__restrict__ uvt,
     int64_t t0, int64_t n, double *__restrict__ terms)
 {
     extern __shared__ __align__(16) unsigned char dyn_lds[];
@@ -1117,20 +1158,23 @@ __global__ __launch_bounds__(kTermsT) void k_terms(
     // the last tile's positions past n are written too, as invalid samples
     // (terms holds whole tiles), so that a tile's 16 lanes are all active
     if (r >= ((n + 15) & ~(int64_t)15)) return;
-    const int nd = g.n_det, nl = g.n_lm, ntri = nl * (nl + 1) / 2;
-    double2 *Yl = reinterpret_cast<double2 *>(dyn_lds);   // [nl][64]
-    const __amdgpu_buffer_rsrc_t rt = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<double4 *>(uvt), (short)0, nd * ntri * (int)sizeof(double4), 0x00020000);
+    const int nd = g.n_det, nl = g.n_lm;
+    double2 *Yl = reinterpret_cast<double2 *>(dyn_lds) + lane;   // [nl - 1][64], Yl[b] of mode b + 1
     double *tp = terms_slot(g, terms, r);
     TermsSample S;
-    double cp[kPw], sp[kPw], er[kPw], ei[kPw];
-    terms_intake(g, smp, N, perm, shifts, t0 + min(r, n - 1), in_order, r < n, S, cp, sp, er, ei);
-    for (int a = 0; a < nl; a++) {
-        const double2 y = terms_harmonic(g, S, a, cp, sp, er, ei);
-        Yl[a * kTermsT + lane] = y;
-        tp[(2 + 2 * nd + 2 * a) * 16] = y.x;
-        tp[(3 + 2 * nd + 2 * a) * 16] = y.y;
+    double2 y0 = make_double2(0.0, 0.0);
+    {
+        double cp[kPw], sp[kPw], er[kPw], ei[kPw];
+        terms_intake(g, smp, N, perm, shifts, t0 + min(r, n - 1), in_order, r < n, S, cp, sp, er, ei);
+        for (int a = 0; a < nl; a++) {
+            const double2 y = terms_harmonic(g, S, a, cp, sp, er, ei);
+            if (a == 0) y0 = y;
+            else Yl[(a - 1) * kTermsT] = y;
+            tp[(2 + 2 * nd + 2 * a) * 16] = y.x;
+            tp[(3 + 2 * nd + 2 * a) * 16] = y.y;
+        }
     }
+    const double *p = uvt + (lane & 15);
     double qs = 0.0;
     for (int k = 0; k < nd; k++) {
         double fp, fx;
@@ -1138,43 +1182,48 @@ __global__ __launch_bounds__(kTermsT) void k_terms(
         tp[(2 + 2 * k) * 16] = S.kap * fp;
         tp[(3 + 2 * k) * 16] = S.kap * fx;
         const double f2 = fp * fp + fx * fx, F2r = fp * fp - fx * fx, F2i = 2.0 * fp * fx;
-        int ro = k * ntri;   // row a's first entry (its diagonal)
-        for (int a = 0; a < nl; a++) {
-            double ur = 0, ui = 0, vr = 0, vi = 0;
-            int b = a + 1;
-            if (b + 3 < nl) {
-                // four entries per step, the next step's loads issued before
-                // this step's products (sums still in the order of b)
-                double2 Yb[4];
-                double4 e[4];
-#pragma unroll
-                for (int q = 0; q < 4; q++) {
-                    Yb[q] = Yl[(b + q) * kTermsT + lane];
-                    e[q] = tri_ld(rt, ro + b + q - a);
-                }
-                for (; b + 7 < nl; b += 4) {
-                    double2 Yn[4];
-                    double4 en[4];
-#pragma unroll
-                    for (int q = 0; q < 4; q++) {
-                        Yn[q] = Yl[(b + 4 + q) * kTermsT + lane];
-                        en[q] = tri_ld(rt, ro + b + 4 + q - a);
-                    }
-#pragma unroll
-                    for (int q = 0; q < 4; q++) terms_mac(Yb[q], e[q], ur, ui, vr, vi);
-#pragma unroll
-                    for (int q = 0; q < 4; q++) {
-                        Yb[q] = Yn[q];
-                        e[q] = en[q];
-                    }
-                }
-#pragma unroll
-                for (int q = 0; q < 4; q++) terms_mac(Yb[q], e[q], ur, ui, vr, vi);
-                b += 4;
+        for (int a0 = 0; a0 < nl; a0 += 4) {
+            // the block's diagonal, then columns a0 + 1 .. nl - 1 (zeros where
+            // the column is not past the row's diagonal)
+            const double dg = p[0];
+            double e0 = p[16], e1 = p[32], e2 = p[48], e3 = p[64];
+            tri_acc A[4] = {};
+            int b = a0;   // columns b + 1
+            for (; b + 4 < nl; b += 4) {
+                const double2 ya = Yl[b * kTermsT], yb = Yl[(b + 1) * kTermsT];
+                const double2 yc = Yl[(b + 2) * kTermsT], yd = Yl[(b + 3) * kTermsT];
+                p += 64;
+                const double n0 = p[16], n1 = p[32], n2 = p[48], n3 = p[64];
+                tri_mac(e0, ya, A);
+                tri_mac(e1, yb, A);
+                tri_mac(e2, yc, A);
+                tri_mac(e3, yd, A);
+                e0 = n0;
+                e1 = n1;
+                e2 = n2;
+                e3 = n3;
             }
-            for (; b < nl; b++) terms_mac(Yl[b * kTermsT + lane], uvt[ro + b - a], ur, ui, vr, vi);
-            qs += terms_row(Yl[a * kTermsT + lane], uvt[ro], ur, ui, vr, vi, f2, F2r, F2i);
-            ro += nl - a;
+            if (b + 1 < nl) {
+                tri_mac(e0, Yl[b * kTermsT], A);
+                p += 16;
+            }
+            if (b + 2 < nl) {
+                tri_mac(e1, Yl[(b + 1) * kTermsT], A);
+                p += 16;
+            }
+            if (b + 3 < nl) {
+                tri_mac(e2, Yl[(b + 2) * kTermsT], A);
+                p += 16;
+            }
+            p += 16;
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+                if (a0 + i < nl) {
+                    const double4 d = i == 0 ? row_quad<0>(dg) : i == 1 ? row_quad<4>(dg)
+                                    : i == 2 ? row_quad<8>(dg) : row_quad<12>(dg);
+                    const double2 ya = i == 0 && a0 == 0 ? y0 : Yl[(a0 + i - 1) * kTermsT];
+                    qs += terms_row(ya, d, A[i].ur, A[i].ui, A[i].vr, A[i].vi, f2, F2r, F2i);
+                }
         }
     }
     terms_store(g, S, qs, tp);
@@ -1182,7 +1231,7 @@ __global__ __launch_bounds__(kTermsT) void k_terms(
 
 static size_t terms_lds_bytes(const ile_geom &g)
 {
-    return (size_t)kTermsT * g.n_lm * sizeof(double2);
+    return (size_t)kTermsT * (g.n_lm - 1) * sizeof(double2);
 }
 
 // One tile: samples perm[base .. base + TS) of a point (those below N).
@@ -2281,7 +2330,7 @@ constexpr size_t kPhBudget32 = 50 * 1024;
 
 static hipError_t launch_terms(const ile_geom &g, const double *smp, int64_t N,
                                const int32_t *perm, const int32_t *shifts, bool in_order,
-                               const double4 *uvt, int64_t t0, int64_t n, double *terms,
+                               const double *uvt, int64_t t0, int64_t n, double *terms,
                                hipStream_t st)
 {
     hipLaunchKernelGGL(k_terms, dim3(nblk(n, kTermsT)), dim3(kTermsT), terms_lds_bytes(g), st,
@@ -2309,7 +2358,7 @@ static hipError_t allow_dyn_lds(const void *fn, size_t dyn, size_t (&allowed)[64
 template <typename TQ, int NT, bool DUMP>
 hipError_t launch_contract_ph(const ile_geom &g, const double *smp, int64_t N,
                               const int32_t *perm, const int32_t *shifts, const double *smp_s,
-                              const int32_t *sh_s, const void *Q, const double4 *uvt,
+                              const int32_t *sh_s, const void *Q, const double *uvt,
                               double *terms, int64_t cap, double *out, double *series, size_t dyn,
                               hipStream_t st)
 {
@@ -2490,8 +2539,8 @@ hipError_t ile_launch_terms(const ile_geom &g, const double *smp, int64_t N,
                             double *terms, hipStream_t st)
 {
     if (N <= 0) return hipSuccess;
-    if (terms_lds_bytes(g) > 64 * 1024) return hipErrorInvalidValue;
-    return launch_terms(g, smp, N, perm, shifts, false, (const double4 *)uvt, 0, N, terms, st);
+    if (g.n_lm > 64) return hipErrorInvalidValue;
+    return launch_terms(g, smp, N, perm, shifts, false, uvt, 0, N, terms, st);
 }
 
 bool ile_contract_uses_terms(ile_precision prec, const ile_tune &tu)
@@ -2514,7 +2563,7 @@ hipError_t ile_launch_contract(const ile_geom &g, ile_precision prec,
         ile_contract_prepare(gp, prec, tu);
         if (gp.wrow < 16) return hipErrorInvalidValue;
         if (!uvt || !terms || cap < 16 || cap % 16) return hipErrorInvalidValue;
-        if (terms_lds_bytes(g) > 64 * 1024) return hipErrorInvalidValue;
+        if (g.n_lm > 64) return hipErrorInvalidValue;
         const size_t e = prec == ILE_FP64 ? 8 : 4;
         // one 32-bit buffer range covers the whole series
         if ((size_t)g.n_det * 4 * ksp_of(g.n_lm) * g.n_q * e > 0x7fffffffu)
@@ -2522,10 +2571,10 @@ hipError_t ile_launch_contract(const ile_geom &g, ile_precision prec,
         const size_t dyn = ph_dyn_bytes(16, g.n_det, g.n_lm, gp.wrow, e);
 #define ILE_PH(TQ, NT)                                                                       \
     return series ? launch_contract_ph<TQ, NT, true>(gp, smp, N, perm, shifts, smp_s, sh_s, Q,  \
-                                                     (const double4 *)uvt, terms, cap, out,    \
+                                                     uvt, terms, cap, out,    \
                                                      series, dyn, st)                          \
                   : launch_contract_ph<TQ, NT, false>(gp, smp, N, perm, shifts, smp_s, sh_s,   \
-                                                      Q, (const double4 *)uvt, terms, cap,     \
+                                                      Q, uvt, terms, cap,     \
                                                       out, series, dyn, st)
         if (prec == ILE_FP64) {
             if (tu.threads == 256) ILE_PH(double, 256);

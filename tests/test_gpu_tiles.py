@@ -61,3 +61,20 @@ def test_tile_edges(n_det, n_lm, n_t, n, lds_kb, precision):
     assert np.all(np.isnan(got[bad]))
     keep = np.nonzero(~bad)[0]
     check_margT(got[keep], want[keep], s, octx, inst, idx=keep, **tol)
+
+
+@pytest.mark.parametrize("n_lm", [1, 2, 3, 4, 5, 6, 7, 8, 9, 32])
+@pytest.mark.parametrize("n_det", [1, 3])
+def test_quadratic_term_rows(n_det, n_lm):
+    """The quadratic term's rows in fours, its columns in fours: every remainder
+    of each; the tiles' tolerance."""
+    from oracle import oracle as O
+    inst = synth.make_instance(SITES[:n_det], min(n_lm, 21), 4096, 4096.0, 33, 900 + n_lm)
+    if n_lm > 21:   # the first modes once more
+        i = np.arange(n_lm) % 21
+        inst.modes = [inst.modes[j] for j in i]
+        inst.Q, inst.U, inst.V = inst.Q[:, i].copy(), inst.U[:, i][:, :, i].copy(), inst.V[:, i][:, :, i].copy()
+    s, _ = synth.prior_samples(150, n_lm)
+    octx = O.Ctx(inst)
+    with ile.Context(inst, precision="fp64") as ctx:
+        check_margT(ctx.eval(s), octx.eval(s), s, octx, inst, tol=1e-9)
