@@ -18,16 +18,15 @@
 
 // Workspace of ile_integrate_dev_noalloc: a fixed array that every GPU the
 // library runs on holds until the process ends.  Up to ILE_NOALLOC_MAX_N
-// samples: 8 (lnL) + 4 n_det (window starts) + 8 (keys, order) + 8 (2 +
-// 3 n_det + 2 n_lm) (the phased engine's per-sample terms) + 56 + 4 n_det
-// (samples and window starts in tile order) bytes each, plus
-// up to 2^21 + 1 bucket counts, their scan and the reduction partials.
+// samples: 8 (lnL) + 12 (keys, slots, order) + 8 (2 + 3 n_det + 2 n_lm) and 64
+// (the phased engine's per-sample terms and records) or 4 n_det (the other
+// engines' window starts) bytes each, plus up to 2^21 + 1 bucket counts, their scan and the reduction partials.
 // Host code never passes `scratch` itself to a kernel (in host code the name
 // is a stand-in, not a device address): it takes the per-device address that
 // hipGetSymbolAddress returned in ile_create.
 constexpr size_t kNoAllocBytes =
     (size_t)ILE_NOALLOC_MAX_N *
-        (8 + 4 * ILE_MAX_DET + 8 + 8 * (2 + 3 * ILE_MAX_DET + 2 * ILE_MAX_LM) + 56 + 4 * ILE_MAX_DET) +
+        (8 + 12 + 8 * (2 + 3 * ILE_MAX_DET + 2 * ILE_MAX_LM) + sizeof(ile_sample_rec)) +
     ((size_t)9 << 20);
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 
@@ -67,7 +66,7 @@ struct ile_ctx {
     DevBuf Q, U, V;
     DevBuf uvt;                     // upper triangles of U_h and V_s (see ile_launch_contract)
     DevBuf smp, out, lnp, lnq, shifts, keys, perm, hist, scan_tmp, errflag,
-        red_tmp, parts, res, series, terms, smp_s, sh_s;
+        red_tmp, parts, res, series, terms, slot, rec;
     DevBuf hP, hC, bins, hist_tmp;  // adaptive proposal state and scratch
     int hist_nb = 0;
     DevBuf trx, trw;                // training set of the learned sampler
@@ -263,8 +262,8 @@ ile_status ensure_work(ile_ctx *c, int64_t N)
 {
     ile_status s;
     const size_t n = (size_t)std::max<int64_t>(N, 1);
-    if ((s = ensure(c, c->shifts, n * c->g.n_det * sizeof(int32_t)))) return s;
     if ((s = ensure(c, c->keys, n * sizeof(uint32_t)))) return s;
+    if ((s = ensure(c, c->slot, n * sizeof(uint32_t)))) return s;
     if ((s = ensure(c, c->perm, n * sizeof(int32_t)))) return s;
     if ((s = ensure(c, c->hist, (size_t)c->n_buckets * sizeof(uint32_t)))) return s;
     if ((s = ensure(c, c->scan_tmp, (size_t)ile_scan_tmp_words(c->n_buckets) * 4 + 16))) return s;
@@ -275,8 +274,9 @@ ile_status ensure_work(ile_ctx *c, int64_t N)
         if ((s = ensure(c, c->terms,
                         (size_t)ile_terms_fields(c->g) * terms_cap(N) * sizeof(double))))
             return s;
-        if ((s = ensure(c, c->smp_s, n * 7 * sizeof(double)))) return s;
-        if ((s = ensure(c, c->sh_s, n * c->g.n_det * sizeof(int32_t)))) return s;
+        if ((s = ensure(c, c->rec, n * sizeof(ile_sample_rec)))) return s;
+    } else if ((s = ensure(c, c->shifts, n * c->g.n_det * sizeof(int32_t)))) {
+        return s;
     }
     return ILE_OK;
 }
@@ -291,27 +291,29 @@ hipEvent_t next_event(ile_ctx *c)
     return c->ev[c->n_ev_used++];
 }
 
-// Device scratch of one evaluation: window starts, ordering keys, the sample
+// Device scratch of one evaluation: ordering keys and bucket slots, the sample
 // order, the bucket counts and their scan, the reduction's partials.
 struct Work {
-    int32_t *shifts;
     uint32_t *keys;
+    uint32_t *slot;
     int32_t *perm;
     uint32_t *hist;
     uint32_t *scan_tmp;
     double *red_tmp;
     double *terms;   // per-sample terms of the phased engine, cap positions
     int64_t cap;
-    double *smp_s;   // the samples [7][N] and window starts [n_det][N] in tile
-    int32_t *sh_s;   // order, for the phased engine's terms pass (or null)
+    ile_sample_rec *rec;   // of the phased engine, else null
+    int32_t *shifts;       // of the other engines, else null
 };
 
 Work ctx_work(ile_ctx *c, int64_t N)
 {
-    return Work{(int32_t *)c->shifts.p, (uint32_t *)c->keys.p, (int32_t *)c->perm.p,
+    const bool terms = ile_contract_uses_terms(c->cfg.precision, c->tune);
+    return Work{(uint32_t *)c->keys.p, (uint32_t *)c->slot.p, (int32_t *)c->perm.p,
                 (uint32_t *)c->hist.p, (uint32_t *)c->scan_tmp.p, (double *)c->red_tmp.p,
-                (double *)c->terms.p, terms_cap(N), (double *)c->smp_s.p,
-                (int32_t *)c->sh_s.p};
+                (double *)c->terms.p, terms_cap(N),
+                terms ? (ile_sample_rec *)c->rec.p : nullptr,
+                terms ? nullptr : (int32_t *)c->shifts.p};
 }
 
 // The hot path on device data: window starts and ordering, then the fused
@@ -327,28 +329,19 @@ ile_status launch_eval(ile_ctx *c, const Work &w, const double *smp, int64_t N, 
                     "contraction needs %zu bytes of LDS per workgroup, device has %d",
                     lds_need, c->lds_max);
     hipStream_t st = c->stream;
-    HIP_TRY(c, ile_launch_fill_u32(w.hist, 0u, c->n_buckets, st));
-    HIP_TRY(c, ile_launch_prep(c->g, smp, N, w.shifts, w.keys, w.hist, c->n_buckets,
-                               (int32_t *)c->errflag.p, st));
-    // the phased engine's terms pass reads the samples in tile order: the
-    // sort moves them there (or, unsorted, they are there already)
-    const bool terms = ile_contract_uses_terms(c->cfg.precision, c->tune);
-    const double *smp_s = nullptr;
-    const int32_t *sh_s = nullptr;
-    if (c->sort) {
+    const bool rank = c->sort && N <= ile_rank_max(), count = c->sort && !rank;
+    if (count) HIP_TRY(c, ile_launch_fill_u32(w.hist, 0u, c->n_buckets, st));
+    HIP_TRY(c, ile_launch_prep(c->g, smp, N, w.rec, w.shifts, w.keys, w.slot,
+                               count ? w.hist : nullptr, c->n_buckets, (int32_t *)c->errflag.p,
+                               st));
+    if (count) {
         HIP_TRY(c, ile_launch_scan(w.hist, c->n_buckets, w.scan_tmp, st));
-        if (terms && w.smp_s && w.sh_s) {
-            HIP_TRY(c, ile_launch_scatter_copy(w.keys, N, w.hist, w.perm, smp, w.shifts,
-                                               c->g.n_det, w.smp_s, w.sh_s, st));
-            smp_s = w.smp_s;
-            sh_s = w.sh_s;
-        } else {
-            HIP_TRY(c, ile_launch_scatter(w.keys, N, w.hist, w.perm, st));
-        }
+        HIP_TRY(c, ile_launch_scatter(w.keys, w.slot, N, w.hist, w.scan_tmp, c->n_buckets, w.perm,
+                                      st));
+    } else if (rank) {
+        HIP_TRY(c, ile_launch_rank(w.keys, N, w.perm, st));
     } else {
         HIP_TRY(c, ile_launch_identity(w.perm, N, st));
-        smp_s = smp;
-        sh_s = w.shifts;
     }
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (timed) {
@@ -359,7 +352,7 @@ ile_status launch_eval(ile_ctx *c, const Work &w, const double *smp, int64_t N, 
     }
     HIP_TRY(c, ile_launch_contract(c->g, c->cfg.precision, c->tune, smp, N, w.perm, w.shifts,
                                    c->Q.p, (const double *)c->U.p, (const double *)c->V.p,
-                                   smp_s, sh_s, (const double *)c->uvt.p, w.terms, w.cap, out,
+                                   w.rec, (const double *)c->uvt.p, w.terms, w.cap, out,
                                    series, st));
     if (timed) HIP_TRY(c, hipEventRecord(e1, st));
     return ILE_OK;
@@ -992,16 +985,22 @@ ile_status ile_integrate_dev_noalloc(ile_ctx *c, const double *smp, const double
     const size_t n = (size_t)std::max<int64_t>(N, 1);
     double *out = (double *)take(n * sizeof(double));
     Work w;
-    w.shifts = (int32_t *)take(n * c->g.n_det * sizeof(int32_t));
     w.keys = (uint32_t *)take(n * sizeof(uint32_t));
+    w.slot = (uint32_t *)take(n * sizeof(uint32_t));
     w.perm = (int32_t *)take(n * sizeof(int32_t));
     w.hist = (uint32_t *)take((size_t)c->n_buckets * sizeof(uint32_t));
     w.scan_tmp = (uint32_t *)take((size_t)ile_scan_tmp_words(c->n_buckets) * 4 + 16);
     w.red_tmp = (double *)take(4 * (size_t)ile_reduce_blocks() * sizeof(double));
     w.cap = terms_cap(N);
-    w.terms = (double *)take((size_t)ile_terms_fields(c->g) * w.cap * sizeof(double));
-    w.smp_s = (double *)take(n * 7 * sizeof(double));
-    w.sh_s = (int32_t *)take(n * c->g.n_det * sizeof(int32_t));
+    w.terms = nullptr;
+    w.rec = nullptr;
+    w.shifts = nullptr;
+    if (ile_contract_uses_terms(c->cfg.precision, c->tune)) {
+        w.terms = (double *)take((size_t)ile_terms_fields(c->g) * w.cap * sizeof(double));
+        w.rec = (ile_sample_rec *)take(n * sizeof(ile_sample_rec));
+    } else {
+        w.shifts = (int32_t *)take(n * c->g.n_det * sizeof(int32_t));
+    }
     double *parts = (double *)take(8 * sizeof(double));
     if (off > kNoAllocBytes)
         return fail(c, ILE_E_UNSUPPORTED, "workspace needs %zu bytes, the fixed array has %zu",
@@ -1604,7 +1603,7 @@ void ile_destroy(ile_ctx *c)
                       &c->hP, &c->hC, &c->bins, &c->hist_tmp, &c->trx, &c->trw,
                       &c->hv_w, &c->hv_cdf, &c->hv_ws, &c->hv_part, &c->hv_flag, &c->hv_sel,
                       &c->fd_tmp, &c->fd_flag, &c->fd_in, &c->fd_out, &c->rom_A, &c->rom_Z,
-                      &c->uvt, &c->terms, &c->smp_s, &c->sh_s})
+                      &c->uvt, &c->terms, &c->slot, &c->rec})
         release(*b);
     for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
     if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);

@@ -61,73 +61,52 @@ __global__ __launch_bounds__(256) void k_prior_multi(const uint64_t *seed_dev,
     }
 }
 
-// window starts and ordering keys (same arithmetic as the single-point path)
-__global__ __launch_bounds__(256) void k_prep_multi(const ile_geom *geoms,
-                                                    const int64_t *offs, int n_points,
-                                                    int64_t n_total, const double *smp,
-                                                    int32_t *shifts, uint32_t *keys,
-                                                    uint32_t *hist, uint32_t B, int32_t *err)
+// window starts, ordering keys and bucket slots (same arithmetic as the
+// single-point path)
+__global__ __launch_bounds__(ILE_PREP_T) void k_prep_multi(
+    const ile_geom *__restrict__ geoms, const int64_t *__restrict__ offs, int n_points,
+    int64_t n_total, const double *__restrict__ smp, ile_sample_rec *__restrict__ rec,
+    int32_t *__restrict__ shifts, uint32_t *__restrict__ keys, uint32_t *__restrict__ slot,
+    uint32_t *hist, uint32_t B, int32_t *err)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_total) return;
-    const int p = point_of(offs, n_points, i);
+    const int64_t i = (int64_t)blockIdx.x * ILE_PREP_T + threadIdx.x;
+    const bool live = i < n_total;
+    const int64_t il = live ? i : n_total - 1;
+    const int p = point_of(offs, n_points, il);
     const ile_geom &g = geoms[p];
-    const int64_t o = offs[p], n = offs[p + 1] - o, t = i - o;
+    const int64_t o = offs[p], n = offs[p + 1] - o, t = il - o;
     const double *s = smp + 7 * o;
     double th[7];
 #pragma unroll
     for (int q = 0; q < 7; q++) th[q] = s[q * n + t];
-    bool ok = true;
-#pragma unroll
-    for (int q = 0; q < 7; q++) ok = ok && isfinite(th[q]);
-    ok = ok && th[5] > 0.0 && th[4] >= -1.0 && th[4] <= 1.0 && fabs(th[6]) <= g.t_ref_max;
     int sh[ILE_MAX_DET];
-    for (int k = 0; k < g.n_det; k++) {
-        sh[k] = 0;
-        if (ok) {
-            double tau;
-            {
-#pragma clang fp contract(off)
-                const double h = th[0] - g.gmst;
-                const double n0 = cos(th[1]) * cos(h), n1 = cos(th[1]) * sin(h), n2 = sin(th[1]);
-                const double nr = n0 * g.r[k][0] + n1 * g.r[k][1] + n2 * g.r[k][2];
-                tau = -nr / 299792458.0;
-            }
-            double x;
-            {
-#pragma clang fp contract(off)
-                x = (th[6] + tau - g.t0) / g.dt;
-            }
-            const double xs = floor(x + 0.5) - (double)g.half;
-            if (xs >= 0.0 && xs <= (double)g.s_max)
-                sh[k] = (int)xs;
-            else
-                ok = false;
-        }
+    const bool ok = window_starts(g, th, sh);
+    // invalid samples last within the point
+    const uint32_t key = (uint32_t)p * B + (ok ? cell_key(g, sh) : B - 1);
+    if (live) {
+        if (!ok) atomicOr(err, 1);
+        store_starts(g, th, sh, ok, rec ? rec + o : nullptr,
+                     rec ? nullptr : shifts + (int64_t)ILE_MAX_DET * o, t, n);
+        keys[i] = key;
     }
-    uint32_t key = B - 1;   // invalid samples last within the point
-    if (ok) {
-        key = cell_key(g, sh);
-    } else {
-        atomicOr(err, 1);
-    }
-    int32_t *shp = shifts + (int64_t)ILE_MAX_DET * o;
-    for (int k = 0; k < g.n_det; k++) shp[(int64_t)k * n + t] = ok ? sh[k] : -1;
-    key += (uint32_t)p * B;
-    keys[i] = key;
-    (void)wave_count_slot(hist, key);
+    const uint32_t r = block_count_slot(hist, key, live);
+    if (live) slot[i] = r;
 }
 
 // sorted position -> local sample index of the point
-__global__ __launch_bounds__(256) void k_scatter_multi(const uint32_t *keys, const int64_t *offs,
-                                                       int n_points, int64_t n_total,
-                                                       uint32_t *pos, int32_t *perm)
+__global__ __launch_bounds__(256) void k_scatter_multi(
+    const uint32_t *__restrict__ keys, const uint32_t *__restrict__ slot,
+    const int64_t *__restrict__ offs, int n_points, int64_t n_total,
+    const uint32_t *__restrict__ pos, const uint32_t *__restrict__ bsum, int nb,
+    int32_t *__restrict__ perm)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    extern __shared__ uint32_t pre[];
+    scan_prefix(bsum, nb, pre);
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n_total) return;
     const int p = point_of(offs, n_points, i);
-    const uint32_t at = wave_count_slot(pos, keys[i]);
-    perm[at] = (int32_t)(i - offs[p]);
+    const uint32_t k = keys[i];
+    perm[pos[k] + pre[k / ILE_SCAN_BLOCK] + slot[i]] = (int32_t)(i - offs[p]);
 }
 
 // per-point importance-sampling partials (prior proposal: w = L), one
@@ -228,21 +207,24 @@ hipError_t ile_launch_prior_multi(const uint64_t *seed_dev, const int64_t *offs,
 }
 
 hipError_t ile_launch_prep_multi(const ile_geom *geoms, const int64_t *offs, int n_points,
-                                 int64_t n_total, const double *smp, int32_t *shifts,
-                                 uint32_t *keys, uint32_t *hist, uint32_t B, int32_t *err,
-                                 hipStream_t st)
+                                 int64_t n_total, const double *smp, ile_sample_rec *rec,
+                                 int32_t *shifts, uint32_t *keys, uint32_t *slot,
+                                 uint32_t *hist, uint32_t B, int32_t *err, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_prep_multi, dim3(nblk(n_total, 256)), dim3(256), 0, st, geoms, offs,
-                       n_points, n_total, smp, shifts, keys, hist, B, err);
+    hipLaunchKernelGGL(k_prep_multi, dim3(nblk(n_total, ILE_PREP_T)), dim3(ILE_PREP_T), 0, st,
+                       geoms, offs, n_points, n_total, smp, rec, shifts, keys, slot, hist, B, err);
     return hipGetLastError();
 }
 
-hipError_t ile_launch_scatter_multi(const uint32_t *keys, const int64_t *offs, int n_points,
-                                    int64_t n_total, uint32_t *pos, int32_t *perm,
-                                    hipStream_t st)
+hipError_t ile_launch_scatter_multi(const uint32_t *keys, const uint32_t *slot,
+                                    const int64_t *offs, int n_points, int64_t n_total,
+                                    const uint32_t *pos, const uint32_t *bsum,
+                                    int64_t n_buckets, int32_t *perm, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_scatter_multi, dim3(nblk(n_total, 256)), dim3(256), 0, st, keys, offs,
-                       n_points, n_total, pos, perm);
+    const int nb = (int)ile_scan_tmp_words(n_buckets);
+    hipLaunchKernelGGL(k_scatter_multi, dim3(nblk(n_total, 256)), dim3(256),
+                       nb * sizeof(uint32_t), st, keys, slot, offs, n_points, n_total, pos, bsum,
+                       nb, perm);
     return hipGetLastError();
 }
 

@@ -48,7 +48,7 @@ struct ile_batch {
     ile_batch_tuning tune{256, 2, 0, 1};
     int cu_count = 0, lds_max = 0;
     std::string dev_name;
-    Buf geoms, pdev, items, offs, seed, counter, smp, out, shifts, keys, perm, hist, scan_tmp,
+    Buf geoms, pdev, items, offs, seed, counter, smp, out, shifts, keys, slot, rec, perm, hist, scan_tmp,
         errflag, res, lw, terms;
     // graph of one run and what it was built for
     hipGraph_t graph = nullptr;
@@ -176,8 +176,8 @@ ile_status build(ile_batch *b, int64_t n, double dmin, double dmax, bool ext)
     if ((s = bensure(b, b->counter, 16))) return s;
     if ((s = bensure(b, b->smp, (size_t)NT * 7 * sizeof(double)))) return s;
     if ((s = bensure(b, b->out, (size_t)NT * sizeof(double)))) return s;
-    if ((s = bensure(b, b->shifts, (size_t)NT * ILE_MAX_DET * sizeof(int32_t)))) return s;
     if ((s = bensure(b, b->keys, (size_t)NT * sizeof(uint32_t)))) return s;
+    if ((s = bensure(b, b->slot, (size_t)NT * sizeof(uint32_t)))) return s;
     if ((s = bensure(b, b->perm, (size_t)NT * sizeof(int32_t)))) return s;
     if ((s = bensure(b, b->hist, (size_t)nb * sizeof(uint32_t)))) return s;
     if ((s = bensure(b, b->scan_tmp, (size_t)ile_scan_tmp_words(nb) * 4 + 16))) return s;
@@ -191,9 +191,15 @@ ile_status build(ile_batch *b, int64_t n, double dmin, double dmax, bool ext)
     for (int p = 0; p < P; p++)
         toff[p + 1] = toff[p] + (size_t)ile_terms_fields(gs[p]) * (size_t)((n + 15) & ~15);
     const bool use_terms = ph && toff[P] * sizeof(double) <= kMaxTermsBytes;
-    if (use_terms && (s = bensure(b, b->terms, toff[P] * sizeof(double)))) return s;
+    if (use_terms) {
+        if ((s = bensure(b, b->terms, toff[P] * sizeof(double)))) return s;
+        if ((s = bensure(b, b->rec, (size_t)NT * sizeof(ile_sample_rec)))) return s;
+    } else if ((s = bensure(b, b->shifts, (size_t)NT * ILE_MAX_DET * sizeof(int32_t)))) {
+        return s;
+    }
     double *smp = (double *)b->smp.p, *out = (double *)b->out.p;
-    int32_t *sh = (int32_t *)b->shifts.p, *perm = (int32_t *)b->perm.p;
+    ile_sample_rec *rec = use_terms ? (ile_sample_rec *)b->rec.p : nullptr;
+    int32_t *sh = use_terms ? nullptr : (int32_t *)b->shifts.p, *perm = (int32_t *)b->perm.p;
     for (int p = 0; p < P; p++) {
         pd[p].Q = ile_ctx_Q(b->pts[p]);
         pd[p].U = (const double2 *)ile_ctx_U(b->pts[p]);
@@ -201,7 +207,7 @@ ile_status build(ile_batch *b, int64_t n, double dmin, double dmax, bool ext)
         pd[p].smp = smp + 7 * offs[p];
         pd[p].N = n;
         pd[p].perm = perm + offs[p];
-        pd[p].shifts = sh + (int64_t)ILE_MAX_DET * offs[p];
+        pd[p].shifts = sh ? sh + (int64_t)ILE_MAX_DET * offs[p] : nullptr;
         pd[p].out = out + offs[p];
         pd[p].terms = use_terms ? (const double *)b->terms.p + toff[p] : nullptr;
     }
@@ -244,15 +250,16 @@ ile_status build(ile_batch *b, int64_t n, double dmin, double dmax, bool ext)
         step(ile_launch_prior_multi((const uint64_t *)b->seed.p, (const int64_t *)b->offs.p, P,
                                     NT, dmin, dmax, tmax, smp, st));
     step(ile_launch_prep_multi((const ile_geom *)b->geoms.p, (const int64_t *)b->offs.p, P, NT,
-                               smp, sh, (uint32_t *)b->keys.p, (uint32_t *)b->hist.p, B,
-                               (int32_t *)b->errflag.p, st));
+                               smp, rec, sh, (uint32_t *)b->keys.p, (uint32_t *)b->slot.p,
+                               (uint32_t *)b->hist.p, B, (int32_t *)b->errflag.p, st));
     step(ile_launch_scan((uint32_t *)b->hist.p, nb, (uint32_t *)b->scan_tmp.p, st));
-    step(ile_launch_scatter_multi((const uint32_t *)b->keys.p, (const int64_t *)b->offs.p, P,
-                                  NT, (uint32_t *)b->hist.p, perm, st));
+    step(ile_launch_scatter_multi((const uint32_t *)b->keys.p, (const uint32_t *)b->slot.p,
+                                  (const int64_t *)b->offs.p, P, NT, (const uint32_t *)b->hist.p,
+                                  (const uint32_t *)b->scan_tmp.p, nb, perm, st));
     if (use_terms)
         for (int p = 0; p < P; p++)
-            step(ile_launch_terms(gs[p], pd[p].smp, n, pd[p].perm, pd[p].shifts,
-                                  ile_ctx_uvt(b->pts[p]), (double *)pd[p].terms, st));
+            step(ile_launch_terms(gs[p], rec + offs[p], n, pd[p].perm, ile_ctx_uvt(b->pts[p]),
+                                  (double *)pd[p].terms, st));
     step(ile_launch_contract_batched(b->cfg.precision, tu, (const ile_geom *)b->geoms.p,
                                      (const ile_point_dev *)b->pdev.p,
                                      (const int2 *)b->items.p, (int)items.size(),
@@ -573,7 +580,7 @@ void ile_batch_destroy(ile_batch *b)
     drop_graph(b);
     for (ile_ctx *c : b->pts) ile_destroy(c);
     for (Buf *x : {&b->geoms, &b->pdev, &b->items, &b->offs, &b->seed, &b->counter, &b->smp,
-                   &b->out, &b->shifts, &b->keys, &b->perm, &b->hist, &b->scan_tmp, &b->errflag,
+                   &b->out, &b->shifts, &b->keys, &b->slot, &b->rec, &b->perm, &b->hist, &b->scan_tmp, &b->errflag,
                    &b->res, &b->lw, &b->terms})
         if (x->p) (void)hipFree(x->p);
     if (b->e0) (void)hipEventDestroy(b->e0);

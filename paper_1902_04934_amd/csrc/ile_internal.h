@@ -71,35 +71,144 @@ struct ile_point_dev {
     const double *terms;
 };
 
-// Increment table[key] by one for every active lane, aggregated over the
-// lanes of the wave that share a key: one atomic per distinct key (the
-// ordering keys of concentrated draws fall into few buckets, where one
-// atomic per lane serializes).  Returns the lane's slot: the table value
-// before the wave's increment plus the lane's rank among the lanes with its
-// key.  The groups of equal keys are found first (register work only), then
-// the first lane of every group issues its atomic, all of them in one
-// instruction, so a wave waits for one atomic round trip however many
-// distinct keys it holds.  Every active lane of the wave must call it.
-__device__ inline uint32_t wave_count_slot(uint32_t *table, uint32_t key)
+// A sample as the per-sample terms read it: parameters 0 .. 5 (t_ref is in the
+// window starts) and the window starts (all -1 for an invalid sample, 0 past
+// n_det).  One 64-byte line, so gathering records through the sample order
+// reads no more memory than a copy in that order would.
+struct __attribute__((aligned(16))) ile_sample_rec {
+    double th[6];
+    int32_t s[ILE_MAX_DET];
+};
+static_assert(sizeof(ile_sample_rec) == 64, "one line");
+
+// Speed of light [m/s].
+constexpr double kIleC = 299792458.0;
+
+__device__ inline bool sample_ok(const ile_geom &g, const double th[7])
 {
-    uint64_t todo = __ballot(1);
-    const int lane = __lane_id();
-    int lead = lane;
-    uint32_t rank = 0, cnt = 0;
-    while (todo) {
-        const int leader = __ffsll((unsigned long long)todo) - 1;
-        const uint32_t k0 = __shfl(key, leader);
-        const uint64_t same = __ballot(key == k0);
-        if (key == k0) {
-            lead = leader;
-            rank = (uint32_t)__popcll(same & ((1ull << lane) - 1));
-            cnt = (uint32_t)__popcll(same);
+    bool fin = true;
+#pragma unroll
+    for (int p = 0; p < 7; p++) fin = fin && isfinite(th[p]);
+    return fin && th[5] > 0.0 && th[4] >= -1.0 && th[4] <= 1.0 &&
+           fabs(th[6]) <= g.t_ref_max;
+}
+
+// Window starts of a sample: s_k = floor((t_ref + tau_k - t0)/dt + 1/2) - half
+// with the arrival delay tau_k; false (s then undefined) if the sample or a
+// window is out of range.  Operation order as written, no contraction, so that
+// the window rounding agrees with an independent evaluation except within
+// 1e-9 of a tie.
+__device__ inline bool window_starts(const ile_geom &g, const double th[7],
+                                     int (&s)[ILE_MAX_DET])
+{
+#pragma clang fp contract(off)
+    bool ok = sample_ok(g, th);
+    const double h = th[0] - g.gmst;
+    const double cd = cos(th[1]);
+    const double n0 = cd * cos(h);
+    const double n1 = cd * sin(h);
+    const double n2 = sin(th[1]);
+#pragma unroll
+    for (int k = 0; k < ILE_MAX_DET; k++) {
+        s[k] = 0;
+        if (k < g.n_det) {
+            const double nr = n0 * g.r[k][0] + n1 * g.r[k][1] + n2 * g.r[k][2];
+            const double tau = -nr / kIleC;
+            const double x = (th[6] + tau - g.t0) / g.dt;
+            const double xs = floor(x + 0.5) - (double)g.half;
+            if (xs >= 0.0 && xs <= (double)g.s_max)
+                s[k] = (int)xs;
+            else
+                ok = false;
         }
-        todo &= ~same;
     }
-    uint32_t base = 0;
-    if (lead == lane) base = atomicAdd(&table[key], cnt);
-    return __shfl(base, lead) + rank;
+    return ok;
+}
+
+// A sample's record, or (rec null) its window starts.
+__device__ inline void store_starts(const ile_geom &g, const double th[7],
+                                    const int (&s)[ILE_MAX_DET], bool ok, ile_sample_rec *rec,
+                                    int32_t *shifts, int64_t i, int64_t N)
+{
+    if (rec) {
+        ile_sample_rec R;
+#pragma unroll
+        for (int p = 0; p < 6; p++) R.th[p] = th[p];
+#pragma unroll
+        for (int k = 0; k < ILE_MAX_DET; k++) R.s[k] = ok ? s[k] : -1;
+        rec[i] = R;
+    } else {
+#pragma unroll
+        for (int k = 0; k < ILE_MAX_DET; k++)
+            if (k < g.n_det) shifts[k * N + i] = ok ? s[k] : -1;
+    }
+}
+
+// Counting sort of the samples by key, three kernels: the keys are counted and
+// every sample takes its slot in its bucket (block_count_slot), the counts
+// are scanned within blocks of ILE_SCAN_BLOCK (ile_launch_scan), and a sample's
+// place is its bucket's offset, its scan block's (the prefix of the block
+// totals, which each workgroup of the scatter forms in LDS: cheaper than two
+// more kernels over the counts) and its slot.
+#define ILE_SCAN_BLOCK 4096
+#define ILE_PREP_T 1024
+
+// Counts key in table for every live thread of the workgroup (ILE_PREP_T
+// threads, all of which call it) and returns the thread's slot: the bucket's
+// count before the workgroup's, plus the thread's rank among the
+// workgroup's samples of that key.  Equal keys of a workgroup are merged in
+// an LDS hash table first, so that a table entry takes one atomic per
+// workgroup that holds its key: concentrated draws fall into a few buckets,
+// where the atomics of one address are serial.
+__device__ inline uint32_t block_count_slot(uint32_t *table, uint32_t key, bool live)
+{
+    constexpr int NS = 2 * ILE_PREP_T;
+    constexpr uint32_t kFree = 0xffffffffu;   // no key (fewer than 2^25 buckets)
+    __shared__ uint32_t hk[NS], hc[NS], hb[NS];
+    for (int i = threadIdx.x; i < NS; i += ILE_PREP_T) {
+        hk[i] = kFree;
+        hc[i] = 0;
+    }
+    __syncthreads();
+    uint32_t at = (key * 2654435761u) >> 16 & (NS - 1), r = 0;
+    if (live) {
+        for (;;) {   // at most ILE_PREP_T of the NS entries are ever taken
+            uint32_t have = hk[at];
+            if (have == kFree) have = atomicCAS(&hk[at], kFree, key);
+            if (have == kFree || have == key) break;
+            at = (at + 1) & (NS - 1);
+        }
+        r = atomicAdd(&hc[at], 1u);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < NS; i += ILE_PREP_T)
+        if (hc[i]) hb[i] = atomicAdd(&table[hk[i]], hc[i]);
+    __syncthreads();
+    return live ? hb[at] + r : 0u;
+}
+
+// Exclusive prefix of the nb scan-block totals into pre (LDS, nb words), by a
+// workgroup of 256 threads, all of which call it.
+__device__ inline void scan_prefix(const uint32_t *bsum, int nb, uint32_t *pre)
+{
+    __shared__ uint32_t ws[4];
+    const int t = threadIdx.x, lane = t & 63, per = (nb + 255) / 256;
+    uint32_t sum = 0;
+    for (int j = t * per; j < min((t + 1) * per, nb); j++) sum += bsum[j];
+    uint32_t inc = sum;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t u = __shfl_up(inc, off);
+        if (lane >= off) inc += u;
+    }
+    if (lane == 63) ws[t >> 6] = inc;
+    __syncthreads();
+    uint32_t run = inc - sum;
+    for (int w = 0; w < (t >> 6); w++) run += ws[w];
+    for (int j = t * per; j < min((t + 1) * per, nb); j++) {
+        pre[j] = run;
+        run += bsum[j];
+    }
+    __syncthreads();
 }
 
 // Ordering key of a sample: its cell (window starts of up to three
@@ -231,18 +340,26 @@ void ile_contract_prepare(ile_geom &g, ile_precision prec, const ile_tune &tu);
 
 // Launch wrappers (ile_kernels.hip).  All are asynchronous on `st`.
 hipError_t ile_launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t st);
-hipError_t ile_launch_prep(const ile_geom &g, const double *smp, int64_t N,
-                           int32_t *shifts, uint32_t *keys, uint32_t *hist,
+// Window starts and ordering keys of N samples: records into rec or (rec null)
+// window starts [n_det][N] into shifts; the bucket counts and every sample's
+// slot in its bucket into hist and slot (hist null: neither).  Invalid samples
+// take the last bucket and set bit 0 of *err.
+hipError_t ile_launch_prep(const ile_geom &g, const double *smp, int64_t N, ile_sample_rec *rec,
+                           int32_t *shifts, uint32_t *keys, uint32_t *slot, uint32_t *hist,
                            uint32_t n_buckets, int32_t *err, hipStream_t st);
+// Exclusive scan within blocks of ILE_SCAN_BLOCK of the n counts v, the block
+// totals into tmp.
 hipError_t ile_launch_scan(uint32_t *v, int64_t n, uint32_t *tmp, hipStream_t st);
 int64_t ile_scan_tmp_words(int64_t n);
-hipError_t ile_launch_scatter(const uint32_t *keys, int64_t N, uint32_t *offs,
+// perm: the samples in key order, from the scanned counts of n_buckets.
+hipError_t ile_launch_scatter(const uint32_t *keys, const uint32_t *slot, int64_t N,
+                              const uint32_t *offs, const uint32_t *bsum, int64_t n_buckets,
                               int32_t *perm, hipStream_t st);
-// The scatter plus copies of the samples [7][N] and window starts [nd][N]
-// in tile order into smp_s, sh_s.
-hipError_t ile_launch_scatter_copy(const uint32_t *keys, int64_t N, uint32_t *offs,
-                                   int32_t *perm, const double *smp, const int32_t *shifts,
-                                   int nd, double *smp_s, int32_t *sh_s, hipStream_t st);
+// The same order from the keys alone, by comparing all pairs: N at most
+// ile_rank_max(), where one kernel of N^2 comparisons takes less time than
+// the counts' clearing, scan and scatter.
+int64_t ile_rank_max();
+hipError_t ile_launch_rank(const uint32_t *keys, int64_t N, int32_t *perm, hipStream_t st);
 hipError_t ile_launch_identity(int32_t *perm, int64_t N, hipStream_t st);
 // Per-sample terms of Eq. (7) that the phased engine reads instead of
 // forming them in its tiles (kernel k_terms, run by ile_launch_contract
@@ -259,24 +376,23 @@ int ile_terms_fields(const ile_geom &g);
 bool ile_contract_uses_terms(ile_precision prec, const ile_tune &tu);
 // The terms of positions 0 .. N-1 of one point into terms (16 F round16(N)
 // doubles); uvt as for ile_launch_contract.
-hipError_t ile_launch_terms(const ile_geom &g, const double *smp, int64_t N,
-                            const int32_t *perm, const int32_t *shifts, const double *uvt,
-                            double *terms, hipStream_t st);
+hipError_t ile_launch_terms(const ile_geom &g, const ile_sample_rec *rec, int64_t N,
+                            const int32_t *perm, const double *uvt, double *terms,
+                            hipStream_t st);
 // Positions per launch of the terms (a multiple of 16): the buffer for N
 // samples holds ile_terms_fields x min(N, ILE_TERMS_CHUNK) doubles.
 #define ILE_TERMS_CHUNK ((int64_t)1 << 21)
 // uvt: the packed triangles (ile_pack_uv); terms: a buffer of
 // ile_terms_fields x cap doubles, cap >= 16 a multiple of 16 (both used when
 // ile_contract_uses_terms, else may be null).
-// smp_s, sh_s: the samples and window starts already in tile order (the
-// terms pass then reads them in order), or null (it gathers them through
-// perm).
+// rec: the samples' records when ile_contract_uses_terms (smp and shifts are
+// then not read), else null.
 hipError_t ile_launch_contract(const ile_geom &g, ile_precision prec,
                                const ile_tune &tu, const double *smp, int64_t N,
                                const int32_t *perm, const int32_t *shifts,
                                const void *Q, const double *U, const double *V,
-                               const double *smp_s, const int32_t *sh_s, const double *uvt,
-                               double *terms, int64_t cap, double *out, double *series,
+                               const ile_sample_rec *rec, const double *uvt, double *terms,
+                               int64_t cap, double *out, double *series,
                                hipStream_t st);
 size_t ile_contract_lds_bytes(const ile_geom &g, ile_precision prec,
                               const ile_tune &tu);
@@ -318,12 +434,13 @@ hipError_t ile_launch_prior_multi(const uint64_t *seed_dev, const int64_t *offs,
                                   int64_t n_total, double d_min, double d_max,
                                   double t_ref_max, double *smp, hipStream_t st);
 hipError_t ile_launch_prep_multi(const ile_geom *geoms, const int64_t *offs, int n_points,
-                                 int64_t n_total, const double *smp, int32_t *shifts,
-                                 uint32_t *keys, uint32_t *hist, uint32_t B, int32_t *err,
-                                 hipStream_t st);
-hipError_t ile_launch_scatter_multi(const uint32_t *keys, const int64_t *offs, int n_points,
-                                    int64_t n_total, uint32_t *pos, int32_t *perm,
-                                    hipStream_t st);
+                                 int64_t n_total, const double *smp, ile_sample_rec *rec,
+                                 int32_t *shifts, uint32_t *keys, uint32_t *slot,
+                                 uint32_t *hist, uint32_t B, int32_t *err, hipStream_t st);
+hipError_t ile_launch_scatter_multi(const uint32_t *keys, const uint32_t *slot,
+                                    const int64_t *offs, int n_points, int64_t n_total,
+                                    const uint32_t *pos, const uint32_t *bsum,
+                                    int64_t n_buckets, int32_t *perm, hipStream_t st);
 hipError_t ile_launch_reduce_points(const double *out, const double *lw, const int64_t *offs,
                                     int n_points, double *res, hipStream_t st);
 hipError_t ile_launch_batch_lw(const double *lp, const double *lq, int64_t n_total, double *lw,
