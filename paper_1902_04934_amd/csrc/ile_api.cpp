@@ -379,13 +379,10 @@ void begin_call(ile_ctx *c)
 // pinned host memory with the one wait (fetched_result reads the fields).
 ile_status finish_call(ile_ctx *c)
 {
-    int32_t *hflag = (int32_t *)c->hpin;
-    if (c->errflag.p)
-        HIP_TRY(c, hipMemcpyAsync(hflag, c->errflag.p, sizeof(int32_t), hipMemcpyDeviceToHost,
-                                  c->stream));
-    if (c->res.p)
-        HIP_TRY(c, hipMemcpyAsync((double *)c->hpin + 1, c->res.p, 6 * sizeof(double),
-                                  hipMemcpyDeviceToHost, c->stream));
+    const int32_t *hflag = (const int32_t *)c->hpin;
+    if (c->errflag.p || c->res.p)
+        HIP_TRY(c, ile_launch_fetch((const int32_t *)c->errflag.p, (const double *)c->res.p,
+                                    (double *)c->hpin, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     double tot = 0.0;
     int n = 0;
@@ -411,6 +408,15 @@ ile_status finish_call(ile_ctx *c)
 void fetched_result(const ile_ctx *c, double r[6])
 {
     std::memcpy(r, (const double *)c->hpin + 1, 6 * sizeof(double));
+}
+
+// The result fields of the work queued so far.
+ile_status wait_result(ile_ctx *c, double r[6])
+{
+    HIP_TRY(c, ile_launch_fetch(nullptr, (const double *)c->res.p, (double *)c->hpin, c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    fetched_result(c, r);
+    return ILE_OK;
 }
 
 ile_status check_ready(ile_ctx *c)
@@ -892,8 +898,8 @@ ile_status ile_rom_integrate_dev(ile_ctx *c, const double *smp, const double *lp
     if ((s = ensure_work(c, N))) return s;
     if (N > 0 && (s = rom_eval_impl(c, smp, N, (double *)c->out.p))) return s;
     HIP_TRY(c, ile_launch_reduce((const double *)c->out.p, lp, lq, N, (double *)c->red_tmp.p,
-                                 (double *)c->parts.p, c->stream));
-    HIP_TRY(c, ile_launch_finish((const double *)c->parts.p, 1, res, c->stream));
+                                 (double *)c->parts.p, (const double *)c->parts.p, 1, res,
+                                 c->stream));
     return ILE_OK;
 }
 
@@ -948,9 +954,9 @@ static ile_status integrate_dev_impl(ile_ctx *c, const double *smp, const double
     if ((s = ensure(c, c->out, (size_t)std::max<int64_t>(N, 1) * sizeof(double)))) return s;
     if ((s = ensure(c, c->parts, 8 * sizeof(double)))) return s;
     if ((s = run_eval(c, smp, N, (double *)c->out.p, nullptr))) return s;
-    HIP_TRY(c, ile_launch_reduce((const double *)c->out.p, lp, lq, N,
-                                 (double *)c->red_tmp.p, (double *)c->parts.p, c->stream));
-    HIP_TRY(c, ile_launch_finish((const double *)c->parts.p, 1, res, c->stream));
+    HIP_TRY(c, ile_launch_reduce((const double *)c->out.p, lp, lq, N, (double *)c->red_tmp.p,
+                                 (double *)c->parts.p, (const double *)c->parts.p, 1, res,
+                                 c->stream));
     return ILE_OK;
 }
 
@@ -1006,8 +1012,7 @@ ile_status ile_integrate_dev_noalloc(ile_ctx *c, const double *smp, const double
         return fail(c, ILE_E_UNSUPPORTED, "workspace needs %zu bytes, the fixed array has %zu",
                     off, kNoAllocBytes);
     if ((s = launch_eval(c, w, smp, N, out, nullptr, false))) return s;
-    HIP_TRY(c, ile_launch_reduce(out, lp, lq, N, w.red_tmp, parts, c->stream));
-    HIP_TRY(c, ile_launch_finish(parts, 1, res, c->stream));
+    HIP_TRY(c, ile_launch_reduce(out, lp, lq, N, w.red_tmp, parts, parts, 1, res, c->stream));
     return ILE_OK;
 }
 
@@ -1105,8 +1110,8 @@ ile_status ile_harvest_dev(ile_ctx *c, const double *smp, const double *lp, cons
     if (result) {
         if ((s = ensure(c, c->parts, 8 * sizeof(double)))) return s;
         HIP_TRY(c, ile_launch_reduce(lnL, lp, lq, N, (double *)c->red_tmp.p,
-                                     (double *)c->parts.p, st));
-        HIP_TRY(c, ile_launch_finish((const double *)c->parts.p, 1, result, st));
+                                     (double *)c->parts.p, (const double *)c->parts.p, 1, result,
+                                     st));
     }
     HIP_TRY(c, ile_launch_hv_weights(lnL, lp, lq, N, w, (double *)c->hv_part.p, flag, st));
     HIP_TRY(c, ile_launch_mdn_cdf(w, N, cdf, (double *)c->hv_ws.p, st));
@@ -1150,11 +1155,11 @@ ile_status ile_run_prior(ile_ctx *c, uint64_t seed, int64_t N, int64_t chunk,
         if ((s = run_eval(c, (const double *)c->smp.p, n, (double *)c->out.p, nullptr)))
             return s;
         HIP_TRY(c, ile_launch_reduce((const double *)c->out.p, nullptr, nullptr, n,
-                                     (double *)c->red_tmp.p,
-                                     (double *)c->parts.p + 5 * ci, c->stream));
+                                     (double *)c->red_tmp.p, (double *)c->parts.p + 5 * ci,
+                                     (const double *)c->parts.p, (int)(ci + 1),
+                                     ci + 1 == n_chunks ? (double *)c->res.p : nullptr,
+                                     c->stream));
     }
-    HIP_TRY(c, ile_launch_finish((const double *)c->parts.p, (int)n_chunks,
-                                 (double *)c->res.p, c->stream));
     if ((s = finish_call(c))) return s;
     double r[6];
     fetched_result(c, r);
@@ -1370,10 +1375,9 @@ static ile_status run_learned(ile_ctx *c, const ile_run_opts *o, ile_result *out
         first0 += chunk;
         if ((s2 = run_eval(c, smp, chunk, (double *)c->out.p, nullptr))) return s2;
         HIP_TRY(c, ile_launch_reduce((const double *)c->out.p, lp, lq, chunk,
-                                     (double *)c->red_tmp.p, rpart, c->stream));
-        HIP_TRY(c, ile_launch_finish(rpart, 1, (double *)c->res.p, c->stream));
-        HIP_TRY(c, hipStreamSynchronize(c->stream));
-        HIP_TRY(c, hipMemcpy(r, c->res.p, 6 * sizeof(double), hipMemcpyDeviceToHost));
+                                     (double *)c->red_tmp.p, rpart, rpart, 1, (double *)c->res.p,
+                                     c->stream));
+        if ((s2 = wait_result(c, r))) return s2;
         c->learned.n_refine_samples += chunk;
         c->learned.last_refine_eff = r[1] / (double)chunk;
         if (rec < 32) {
@@ -1432,17 +1436,15 @@ static ile_status run_learned(ile_ctx *c, const ile_run_opts *o, ile_result *out
         if ((s = run_eval(c, smp, n, (double *)c->out.p, nullptr))) return s;
         HIP_TRY(c, ile_launch_reduce((const double *)c->out.p, lp, lq, n,
                                      (double *)c->red_tmp.p, (double *)c->parts.p + 5 * ci,
-                                     c->stream));
+                                     (const double *)c->parts.p, (int)(ci + 1),
+                                     (double *)c->res.p, c->stream));
         if (!learned && (s = refit_impl(c, (const int32_t *)c->bins.p, n, (const double *)c->out.p,
                                         lp, lq, n, floor_w, temper)))
             return s;
-        HIP_TRY(c, ile_launch_finish((const double *)c->parts.p, (int)(ci + 1),
-                                     (double *)c->res.p, c->stream));
         done += n;
         ci++;
         if (learned) c->learned.n_learned_samples += n;
-        HIP_TRY(c, hipStreamSynchronize(c->stream));
-        HIP_TRY(c, hipMemcpy(r, c->res.p, sizeof(r), hipMemcpyDeviceToHost));
+        if ((s = wait_result(c, r))) return s;
         if (o->n_eff_target > 0 && r[1] >= o->n_eff_target) break;
     }
     if ((s = finish_call(c))) return s;
@@ -1507,19 +1509,17 @@ ile_status ile_run(ile_ctx *c, const ile_run_opts *o, ile_result *out, int64_t *
         if ((s = run_eval(c, smp, n, (double *)c->out.p, nullptr))) return s;
         HIP_TRY(c, ile_launch_reduce((const double *)c->out.p, lp, lq, n,
                                      (double *)c->red_tmp.p, (double *)c->parts.p + 5 * ci,
-                                     c->stream));
+                                     (const double *)c->parts.p, (int)(ci + 1),
+                                     (double *)c->res.p, c->stream));
         if (adapting &&
             (s = refit_impl(c, (const int32_t *)c->bins.p, n, (const double *)c->out.p, lp,
                             lq, n, floor_w, temper)))
             return s;
-        HIP_TRY(c, ile_launch_finish((const double *)c->parts.p, (int)(ci + 1),
-                                     (double *)c->res.p, c->stream));
         done += n;
         ci++;
         const bool check = o->n_eff_target > 0 || (adapting && o->adapt_chunks < 0);
         if (check || done >= o->max_samples) {
-            HIP_TRY(c, hipStreamSynchronize(c->stream));
-            HIP_TRY(c, hipMemcpy(r, c->res.p, sizeof(r), hipMemcpyDeviceToHost));
+            if ((s = wait_result(c, r))) return s;
             if (o->n_eff_target > 0 && r[1] >= o->n_eff_target) break;
             if (adapting && o->adapt_chunks < 0 && r[0] > std::max(10.0, 0.5 * r[4]))
                 adapting = false;

@@ -402,12 +402,16 @@ hipError_t ile_launch_prior(uint64_t seed, int64_t first, int64_t N,
 // Importance-sampling reduction of N values into a 5-double partial
 // {M, S1, S2, n, maxL} with S1 = sum e^{lnw-M}, S2 = sum e^{2(lnw-M)}.
 int ile_reduce_blocks();
+// res (if not null): the n_part partials at parts, of which partial is the
+// last, merged in order and finished into result[6].
 hipError_t ile_launch_reduce(const double *lnL, const double *ln_p,
                              const double *ln_q, int64_t N, double *tmp,
-                             double *partial, hipStream_t st);
-// Merge n_part partials (fixed order) and finish into result[6].
-hipError_t ile_launch_finish(const double *partials, int n_part, double *result,
+                             double *partial, const double *parts, int n_part, double *res,
                              hipStream_t st);
+// *flag to the first word of host and res[0 .. 5] to host[1 .. 6] (pinned
+// host memory; either may be null).
+hipError_t ile_launch_fetch(const int32_t *flag, const double *res, double *host,
+                            hipStream_t st);
 // Adaptive sampler (ile_sampler.hip): histogram state P[2][nb], C[2][nb+1].
 int ile_hist_max_bins();
 hipError_t ile_launch_hist_uniform(int nb, double *P, double *C, hipStream_t st);

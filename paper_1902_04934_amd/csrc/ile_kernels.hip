@@ -2070,163 +2070,61 @@ __device__ inline double lnw_at(const double *lnL, const double *lp,
     return lnL[i] + (lp ? lp[i] : 0.0) - (lq ? lq[i] : 0.0);
 }
 
-__global__ __launch_bounds__(kRedT) void k_red_max(const double *lnL,
-                                                   const double *lp,
-                                                   const double *lq, int64_t N,
-                                                   double *tmp)
+// Largest of a wave's values, in every lane.
+__device__ inline double wave_max(double x)
 {
-    __shared__ double sm[kRedT], sl[kRedT];
-    double M = -INFINITY, ML = -INFINITY;
-    for (int64_t i = (int64_t)blockIdx.x * kRedT + threadIdx.x; i < N;
-         i += (int64_t)kRedBlocks * kRedT) {
-        double w = lnw_at(lnL, lp, lq, i);
-        M = w > M ? w : M;
-        ML = lnL[i] > ML ? lnL[i] : ML;
-    }
-    sm[threadIdx.x] = M;
-    sl[threadIdx.x] = ML;
-    __syncthreads();
-    for (int s = kRedT / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s) {
-            sm[threadIdx.x] = fmax(sm[threadIdx.x], sm[threadIdx.x + s]);
-            sl[threadIdx.x] = fmax(sl[threadIdx.x], sl[threadIdx.x + s]);
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        tmp[blockIdx.x] = sm[0];
-        tmp[kRedBlocks + blockIdx.x] = sl[0];
-    }
+    for (int off = 32; off > 0; off >>= 1) x = fmax(x, __shfl_xor(x, off));
+    return x;
 }
 
-__device__ inline double global_max(const double *tmp)
+// A workgroup's NV sums of T values each (a thread's v[k] into sm[k][t]) by the
+// fixed tree (t, t + T/2), (t, t + T/4), ..., of which the first wave does all:
+// one barrier.  In lane 0 of that wave.
+template <int T, int NV>
+__device__ inline void tree_sum(double (&v)[NV], double (*sm)[T])
 {
-    double M = -INFINITY;
-    for (int b = 0; b < kRedBlocks; b++) M = fmax(M, tmp[b]);
-    return M;
-}
-
-__global__ __launch_bounds__(kRedT) void k_red_sum(const double *lnL,
-                                                   const double *lp,
-                                                   const double *lq, int64_t N,
-                                                   double *tmp)
-{
-    __shared__ double s1[kRedT], s2[kRedT];
-    __shared__ double sM;
-    if (threadIdx.x == 0) sM = global_max(tmp);
-    __syncthreads();
-    const double M = sM;
-    double a = 0.0, b = 0.0;
-    if (M != -INFINITY) {
-        for (int64_t i = (int64_t)blockIdx.x * kRedT + threadIdx.x; i < N;
-             i += (int64_t)kRedBlocks * kRedT) {
-            double e = exp(lnw_at(lnL, lp, lq, i) - M);
-            a += e;
-            b += e * e;
-        }
-    }
-    s1[threadIdx.x] = a;
-    s2[threadIdx.x] = b;
-    __syncthreads();
-    for (int s = kRedT / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s) {
-            s1[threadIdx.x] += s1[threadIdx.x + s];
-            s2[threadIdx.x] += s2[threadIdx.x + s];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        tmp[2 * kRedBlocks + blockIdx.x] = s1[0];
-        tmp[3 * kRedBlocks + blockIdx.x] = s2[0];
-    }
-}
-
-__global__ __launch_bounds__(kRedT) void k_red_final(const double *tmp,
-                                                     int64_t N, double *partial)
-{
-    __shared__ double s1[kRedT], s2[kRedT], sl[kRedT];
-    const int t = threadIdx.x;   // kRedT == kRedBlocks
-    s1[t] = tmp[2 * kRedBlocks + t];
-    s2[t] = tmp[3 * kRedBlocks + t];
-    sl[t] = tmp[kRedBlocks + t];
-    __syncthreads();
-    for (int s = kRedT / 2; s > 0; s >>= 1) {
-        if (t < s) {
-            s1[t] += s1[t + s];
-            s2[t] += s2[t + s];
-            sl[t] = fmax(sl[t], sl[t + s]);
-        }
-        __syncthreads();
-    }
-    if (t == 0) {
-        partial[0] = global_max(tmp);
-        partial[1] = s1[0];
-        partial[2] = s2[0];
-        partial[3] = (double)N;
-        partial[4] = sl[0];
-    }
-}
-
-// The same partial from one workgroup when N is small (at most
-// kRedSmallMax): the three kernels above cost more in launches and in their
-// mostly idle blocks than the work.  Same quantities, its own summation tree.
-constexpr int kRedSmallT = 1024;
-constexpr int64_t kRedSmallMax = 16384;
-
-__global__ __launch_bounds__(kRedSmallT) void k_red_small(const double *lnL, const double *lp,
-                                                           const double *lq, int64_t N,
-                                                           double *partial)
-{
-    __shared__ double sa[kRedSmallT], sb[kRedSmallT], sc[kRedSmallT];
     const int t = threadIdx.x;
-    double M = -INFINITY, ML = -INFINITY;
-    for (int64_t i = t; i < N; i += kRedSmallT) {
-        const double w = lnw_at(lnL, lp, lq, i);
-        M = w > M ? w : M;
-        ML = lnL[i] > ML ? lnL[i] : ML;
-    }
-    sa[t] = M;
-    sc[t] = ML;
+#pragma unroll
+    for (int k = 0; k < NV; k++) sm[k][t] = v[k];
     __syncthreads();
-    for (int h = kRedSmallT / 2; h > 0; h >>= 1) {
-        if (t < h) {
-            sa[t] = fmax(sa[t], sa[t + h]);
-            sc[t] = fmax(sc[t], sc[t + h]);
-        }
-        __syncthreads();
-    }
-    const double Mg = sa[0];
-    __syncthreads();
-    double a = 0.0, b = 0.0;
-    if (Mg != -INFINITY) {
-        for (int64_t i = t; i < N; i += kRedSmallT) {
-            const double e = exp(lnw_at(lnL, lp, lq, i) - Mg);
-            a += e;
-            b += e * e;
-        }
-    }
-    sa[t] = a;
-    sb[t] = b;
-    __syncthreads();
-    for (int h = kRedSmallT / 2; h > 0; h >>= 1) {
-        if (t < h) {
-            sa[t] += sa[t + h];
-            sb[t] += sb[t + h];
-        }
-        __syncthreads();
-    }
-    if (t == 0) {
-        partial[0] = Mg;
-        partial[1] = sa[0];
-        partial[2] = sb[0];
-        partial[3] = (double)N;
-        partial[4] = sc[0];
+    if (t >= 64) return;
+#pragma unroll
+    for (int k = 0; k < NV; k++) {
+        double x[T / 64];
+#pragma unroll
+        for (int j = 0; j < T / 64; j++) x[j] = sm[k][t + 64 * j];
+#pragma unroll
+        for (int h = T / 128; h > 0; h >>= 1)
+#pragma unroll
+            for (int j = 0; j < h; j++) x[j] += x[j + h];
+        for (int off = 32; off > 0; off >>= 1) x[0] += __shfl_down(x[0], off);
+        v[k] = x[0];
     }
 }
 
-__global__ void k_finish(const double *parts, int n_part, double *res)
+// The result of a partial (M, S1, S2, n, maxL).
+__device__ inline void finish_one(double M, double S1, double S2, double n, double ML,
+                                  double *res)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    if (M == -INFINITY || n == 0.0) {
+        res[0] = -INFINITY;
+        res[1] = 0.0;
+        res[2] = 0.0;
+        res[3] = NAN;
+    } else {
+        res[0] = M + log(S1) - log(n);
+        res[1] = S1;
+        res[2] = S1 * S1 / S2;
+        const double var = S2 / (S1 * S1) - 1.0 / n;
+        res[3] = var > 0.0 ? sqrt(var) : 0.0;
+    }
+    res[4] = ML;
+    res[5] = n;
+}
+
+// Partials merged in order, then their result: one thread.
+__device__ inline void finish_parts(const double *parts, int n_part, double *res)
+{
     double M = -INFINITY, ML = -INFINITY, n = 0.0;
     for (int i = 0; i < n_part; i++) {
         M = fmax(M, parts[5 * i]);
@@ -2237,24 +2135,193 @@ __global__ void k_finish(const double *parts, int n_part, double *res)
     if (M != -INFINITY)
         for (int i = 0; i < n_part; i++) {
             if (parts[5 * i] == -INFINITY) continue;
-            double e = exp(parts[5 * i] - M);
-            S1 += parts[5 * i + 1] * e;
-            S2 += parts[5 * i + 2] * e * e;
+            const double e = exp(parts[5 * i] - M);
+            S1 = fma(parts[5 * i + 1], e, S1);
+            S2 = fma(parts[5 * i + 2] * e, e, S2);
         }
-    if (M == -INFINITY || n == 0.0) {
-        res[0] = -INFINITY;
-        res[1] = 0.0;
-        res[2] = 0.0;
-        res[3] = NAN;
-    } else {
-        res[0] = M + log(S1) - log(n);
-        res[1] = S1;
-        res[2] = S1 * S1 / S2;
-        double var = S2 / (S1 * S1) - 1.0 / n;
-        res[3] = var > 0.0 ? sqrt(var) : 0.0;
+    finish_one(M, S1, S2, n, ML, res);
+}
+
+// The partial (M, S1, S2, N, maxL) at partial and, if res, the result of the
+// n_part partials at parts (partial the last of them): one thread.
+__device__ inline void put_partial(double M, double S1, double S2, int64_t N, double ML,
+                                   double *partial, const double *parts, int n_part, double *res)
+{
+    partial[0] = M;
+    partial[1] = S1;
+    partial[2] = S2;
+    partial[3] = (double)N;
+    partial[4] = ML;
+    if (res && n_part == 1) finish_one(M, S1, S2, (double)N, ML, res);
+    else if (res) finish_parts(parts, n_part, res);
+}
+
+// Three kernels for many samples, the last also the result: 13 us at 1e5, where
+// every workgroup took the largest of the 256 maxima in one thread and the
+// result another kernel: 21.
+__global__ __launch_bounds__(kRedT) void k_red_max(const double *__restrict__ lnL,
+                                                   const double *__restrict__ lp,
+                                                   const double *__restrict__ lq, int64_t N,
+                                                   double *__restrict__ tmp)
+{
+    __shared__ double sm[kRedT / 64], sl[kRedT / 64];
+    double M = -INFINITY, ML = -INFINITY;
+    for (int64_t i = (int64_t)blockIdx.x * kRedT + threadIdx.x; i < N;
+         i += (int64_t)kRedBlocks * kRedT) {
+        double w = lnw_at(lnL, lp, lq, i);
+        M = w > M ? w : M;
+        ML = lnL[i] > ML ? lnL[i] : ML;
     }
-    res[4] = ML;
-    res[5] = n;
+    M = wave_max(M);
+    ML = wave_max(ML);
+    if ((threadIdx.x & 63) == 0) {
+        sm[threadIdx.x >> 6] = M;
+        sl[threadIdx.x >> 6] = ML;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kRedT / 64; w++) {
+            M = fmax(M, sm[w]);
+            ML = fmax(ML, sl[w]);
+        }
+        tmp[blockIdx.x] = M;
+        tmp[kRedBlocks + blockIdx.x] = ML;
+    }
+}
+
+// Largest of the kRedBlocks = kRedT values v, in every thread.
+__device__ inline double global_max(const double *v)
+{
+    static_assert(kRedBlocks == kRedT, "a value a thread");
+    __shared__ double sm[kRedT / 64];
+    const double x = wave_max(v[threadIdx.x]);
+    __syncthreads();   // sm may still be read
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = x;
+    __syncthreads();
+    double M = sm[0];
+    for (int w = 1; w < kRedT / 64; w++) M = fmax(M, sm[w]);
+    return M;
+}
+
+__global__ __launch_bounds__(kRedT) void k_red_sum(const double *lnL,
+                                                   const double *lp,
+                                                   const double *lq, int64_t N,
+                                                   double *tmp)
+{
+    __shared__ double sm[2][kRedT];
+    const double M = global_max(tmp);
+    double s[2] = {0.0, 0.0};
+    if (M != -INFINITY) {
+        for (int64_t i = (int64_t)blockIdx.x * kRedT + threadIdx.x; i < N;
+             i += (int64_t)kRedBlocks * kRedT) {
+            const double e = exp(lnw_at(lnL, lp, lq, i) - M);
+            s[0] += e;
+            s[1] = fma(e, e, s[1]);
+        }
+    }
+    tree_sum<kRedT, 2>(s, sm);
+    if (threadIdx.x == 0) {
+        tmp[2 * kRedBlocks + blockIdx.x] = s[0];
+        tmp[3 * kRedBlocks + blockIdx.x] = s[1];
+    }
+}
+
+__global__ __launch_bounds__(kRedT) void k_red_final(const double *tmp, int64_t N,
+                                                     double *partial, const double *parts,
+                                                     int n_part, double *res)
+{
+    __shared__ double sm[2][kRedT];
+    const int t = threadIdx.x;
+    double s[2] = {tmp[2 * kRedBlocks + t], tmp[3 * kRedBlocks + t]};
+    const double M = global_max(tmp), ML = global_max(tmp + kRedBlocks);
+    tree_sum<kRedT, 2>(s, sm);
+    if (t == 0) put_partial(M, s[0], s[1], N, ML, partial, parts, n_part, res);
+}
+
+// The same partial from one workgroup when N is small (at most
+// kRedSmallMax): the three kernels above cost more in launches and in their
+// mostly idle blocks than the work.  Same quantities, its own summation tree.
+// A thread's PER values are loaded at once and kept, and the result follows
+// from the same kernel: 1e4 samples 12 us, most of it the one CU's loads, where
+// a loop over the values, twice, took 13 and the result another kernel of 4.
+constexpr int kRedSmallT = 1024;
+constexpr int64_t kRedSmallMax = 16384;
+
+template <int PER>
+__global__ __launch_bounds__(kRedSmallT) void k_red_small(const double *__restrict__ lnL,
+                                                          const double *__restrict__ lp,
+                                                          const double *__restrict__ lq, int N,
+                                                          double *partial, const double *parts,
+                                                          int n_part, double *res)
+{
+    __shared__ double sm[2][kRedSmallT];
+    const int t = threadIdx.x;
+    double M = -INFINITY, ML = -INFINITY, w[PER], l[PER];
+#pragma unroll
+    for (int j = 0; j < PER; j++) w[j] = l[j] = -INFINITY;
+    if (N > 0) {
+        // array by array: a thread's loads of each are in flight together (under
+        // a test of lp or lq of their own they would be waited for one by one)
+        const auto at = [&](int j) { return min(t + kRedSmallT * j, N - 1); };
+        double x[PER];
+#pragma unroll
+        for (int j = 0; j < PER; j++) l[j] = lnL[at(j)];
+#pragma unroll
+        for (int j = 0; j < PER; j++) x[j] = 0.0;
+        if (lp)
+#pragma unroll
+            for (int j = 0; j < PER; j++) x[j] = lp[at(j)];
+#pragma unroll
+        for (int j = 0; j < PER; j++) w[j] = l[j] + x[j];
+#pragma unroll
+        for (int j = 0; j < PER; j++) x[j] = 0.0;
+        if (lq)
+#pragma unroll
+            for (int j = 0; j < PER; j++) x[j] = lq[at(j)];
+#pragma unroll
+        for (int j = 0; j < PER; j++) w[j] -= x[j];
+    }
+#pragma unroll
+    for (int j = 0; j < PER; j++) {   // (a value met twice leaves the largest as it is)
+        M = w[j] > M ? w[j] : M;
+        ML = l[j] > ML ? l[j] : ML;
+    }
+    M = wave_max(M);
+    ML = wave_max(ML);
+    if ((t & 63) == 0) {
+        sm[0][t >> 6] = M;
+        sm[1][t >> 6] = ML;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kRedSmallT / 64; q++) {
+        M = fmax(M, sm[0][q]);
+        ML = fmax(ML, sm[1][q]);
+    }
+    __syncthreads();
+    double s[2] = {0.0, 0.0};
+    if (M != -INFINITY) {
+#pragma unroll
+        for (int j = 0; j < PER; j++)
+            if (t + kRedSmallT * j < N) {
+                const double e = exp(w[j] - M);
+                s[0] += e;
+                s[1] = fma(e, e, s[1]);
+            }
+    }
+    tree_sum<kRedSmallT, 2>(s, sm);
+    if (t == 0) put_partial(M, s[0], s[1], N, ML, partial, parts, n_part, res);
+}
+
+// The error flag and the result fields to pinned host memory (the flag's
+// word, then six doubles from its second): one launch before the wait of a
+// call, where two copies took their own.
+__global__ void k_fetch(const int32_t *__restrict__ flag, const double *__restrict__ res,
+                        double *__restrict__ host)
+{
+    const int t = threadIdx.x;
+    if (t == 0 && flag) *reinterpret_cast<int32_t *>(host) = *flag;
+    if (t >= 1 && t <= 6 && res) host[t] = res[t - 1];
 }
 
 inline unsigned nblk(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
@@ -2673,11 +2740,19 @@ int ile_reduce_blocks() { return kRedBlocks; }
 
 hipError_t ile_launch_reduce(const double *lnL, const double *ln_p,
                              const double *ln_q, int64_t N, double *tmp,
-                             double *partial, hipStream_t st)
+                             double *partial, const double *parts, int n_part, double *res,
+                             hipStream_t st)
 {
     if (N <= kRedSmallMax) {
-        hipLaunchKernelGGL(k_red_small, dim3(1), dim3(kRedSmallT), 0, st, lnL, ln_p, ln_q, N,
-                           partial);
+#define ILE_SMALL(PER)                                                                        \
+    hipLaunchKernelGGL((k_red_small<PER>), dim3(1), dim3(kRedSmallT), 0, st, lnL, ln_p, ln_q, \
+                       (int)N, partial, parts, n_part, res)
+        if (N <= 1 * kRedSmallT) ILE_SMALL(1);
+        else if (N <= 4 * kRedSmallT) ILE_SMALL(4);
+        else if (N <= 8 * kRedSmallT) ILE_SMALL(8);
+        else if (N <= 12 * kRedSmallT) ILE_SMALL(12);
+        else ILE_SMALL(16);
+#undef ILE_SMALL
         return hipGetLastError();
     }
     hipLaunchKernelGGL(k_red_max, dim3(kRedBlocks), dim3(kRedT), 0, st, lnL, ln_p,
@@ -2685,14 +2760,13 @@ hipError_t ile_launch_reduce(const double *lnL, const double *ln_p,
     hipLaunchKernelGGL(k_red_sum, dim3(kRedBlocks), dim3(kRedT), 0, st, lnL, ln_p,
                        ln_q, N, tmp);
     hipLaunchKernelGGL(k_red_final, dim3(1), dim3(kRedT), 0, st, (const double *)tmp,
-                       N, partial);
+                       N, partial, parts, n_part, res);
     return hipGetLastError();
 }
 
-hipError_t ile_launch_finish(const double *partials, int n_part, double *result,
-                             hipStream_t st)
+hipError_t ile_launch_fetch(const int32_t *flag, const double *res, double *host, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_finish, dim3(1), dim3(64), 0, st, partials, n_part, result);
+    hipLaunchKernelGGL(k_fetch, dim3(1), dim3(64), 0, st, flag, res, host);
     return hipGetLastError();
 }
 

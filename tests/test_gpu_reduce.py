@@ -1,0 +1,40 @@
+"""The reduction of a call's weights, whose paths change with the number of
+samples (values a thread of the one workgroup, then many workgroups): against
+numpy in FP64 at the edges of each.  The sums are of positive terms in another
+order, each exp within an ulp or two: relative 1e-12 holds with a wide margin,
+ln L and sigma absolutely."""
+import numpy as np
+import pytest
+
+from paper_1902_04934_amd import ile, synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 1023, 1024, 1025, 4096, 4097, 8192, 8193, 12288, 12289,
+                               16384, 16385, 70001])
+@pytest.mark.parametrize("densities", [True, False])
+def test_result_of_n_samples(n, densities):
+    import torch
+    inst = synth.make_instance(["D1", "D2"], 2, 4096, 4096.0, 33, 3)
+    s, _ = synth.prior_samples(n, n)
+    rng = np.random.default_rng(n)
+    lp, lq = (rng.normal(size=n), rng.normal(size=n)) if densities else (np.zeros(n), np.zeros(n))
+    with ile.Context(inst, precision="fp64") as ctx:
+        lnL = ctx.eval(s)
+        d = torch.from_numpy(s).cuda()
+        p, q = (torch.from_numpy(x).cuda() if densities else None for x in (lp, lq))
+        out = torch.zeros(6, dtype=torch.float64, device="cuda")
+        torch.cuda.synchronize()
+        ctx.integrate_dev(d, p, q, n, out)
+        ctx.sync()
+        got = out.cpu().numpy()
+    w = lnL + lp - lq
+    M = w.max()
+    e = np.exp(w - M)
+    S1, S2 = e.sum(), (e * e).sum()
+    var = S2 / (S1 * S1) - 1.0 / n
+    assert abs(got[0] - (M + np.log(S1) - np.log(n))) < 1e-12 * max(1.0, abs(M))
+    assert np.allclose(got[1:3], [S1, S1 * S1 / S2], rtol=1e-12, atol=0)
+    assert abs(got[3] ** 2 - max(var, 0.0)) < 1e-13
+    assert got[4] == lnL.max() and got[5] == n
