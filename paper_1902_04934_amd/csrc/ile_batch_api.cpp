@@ -48,8 +48,10 @@ struct ile_batch {
     ile_batch_tuning tune{256, 2, 0, 1};
     int cu_count = 0, lds_max = 0;
     std::string dev_name;
-    Buf geoms, pdev, items, offs, seed, counter, smp, out, shifts, keys, slot, rec, perm, hist, scan_tmp,
-        errflag, res, lw, terms;
+    Buf geoms, pdev, items, offs, seed, counter, smp, out, shifts, keys, slot, rec, perm, hist,
+        scan_tmp, errflag, red_tmp, lw, terms;
+    double *hres = nullptr;   // pinned: the error flag, then 6 results a point (of n_hres points)
+    size_t n_hres = 0;
     // graph of one run and what it was built for
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -182,7 +184,15 @@ ile_status build(ile_batch *b, int64_t n, double dmin, double dmax, bool ext)
     if ((s = bensure(b, b->hist, (size_t)nb * sizeof(uint32_t)))) return s;
     if ((s = bensure(b, b->scan_tmp, (size_t)ile_scan_tmp_words(nb) * 4 + 16))) return s;
     if ((s = bensure(b, b->errflag, 16))) return s;
-    if ((s = bensure(b, b->res, (size_t)P * 6 * sizeof(double)))) return s;
+    if ((s = bensure(b, b->red_tmp, ile_reduce_points_tmp(P) * sizeof(double)))) return s;
+    if (b->n_hres < (size_t)P) {
+        if (b->hres) (void)hipHostFree(b->hres);
+        b->hres = nullptr;
+        b->n_hres = 0;
+        BHIP(b, hipHostMalloc((void **)&b->hres, (6 * (size_t)P + 1) * sizeof(double),
+                              hipHostMallocDefault));
+        b->n_hres = P;
+    }
     if (ext && (s = bensure(b, b->lw, (size_t)NT * sizeof(double)))) return s;
     // the phased engine's per-sample terms, per point, when they fit in
     // kMaxTermsBytes (else the tiles form them)
@@ -209,7 +219,9 @@ ile_status build(ile_batch *b, int64_t n, double dmin, double dmax, bool ext)
         pd[p].perm = perm + offs[p];
         pd[p].shifts = sh ? sh + (int64_t)ILE_MAX_DET * offs[p] : nullptr;
         pd[p].out = out + offs[p];
-        pd[p].terms = use_terms ? (const double *)b->terms.p + toff[p] : nullptr;
+        pd[p].terms = use_terms ? (double *)b->terms.p + toff[p] : nullptr;
+        pd[p].rec = use_terms ? rec + offs[p] : nullptr;
+        pd[p].uvt = use_terms ? ile_ctx_uvt(b->pts[p]) : nullptr;
     }
     // queue: tiles of every point; order 0 = decreasing per-tile cost
     std::vector<int> order(P);
@@ -256,16 +268,19 @@ ile_status build(ile_batch *b, int64_t n, double dmin, double dmax, bool ext)
     step(ile_launch_scatter_multi((const uint32_t *)b->keys.p, (const uint32_t *)b->slot.p,
                                   (const int64_t *)b->offs.p, P, NT, (const uint32_t *)b->hist.p,
                                   (const uint32_t *)b->scan_tmp.p, nb, perm, st));
-    if (use_terms)
-        for (int p = 0; p < P; p++)
-            step(ile_launch_terms(gs[p], rec + offs[p], n, pd[p].perm, ile_ctx_uvt(b->pts[p]),
-                                  (double *)pd[p].terms, st));
+    if (use_terms) {
+        int max_lm = 1;
+        for (int p = 0; p < P; p++) max_lm = std::max(max_lm, gs[p].n_lm);
+        step(ile_launch_terms_multi((const ile_geom *)b->geoms.p, (const ile_point_dev *)b->pdev.p,
+                                    P, max_lm, n, st));
+    }
     step(ile_launch_contract_batched(b->cfg.precision, tu, (const ile_geom *)b->geoms.p,
                                      (const ile_point_dev *)b->pdev.p,
                                      (const int2 *)b->items.p, (int)items.size(),
                                      (unsigned *)b->counter.p, grid, dyn, use_terms, st));
     step(ile_launch_reduce_points(out, ext ? (const double *)b->lw.p : nullptr,
-                                  (const int64_t *)b->offs.p, P, (double *)b->res.p, st));
+                                  (const int64_t *)b->offs.p, P, (double *)b->red_tmp.p,
+                                  (const int32_t *)b->errflag.p, b->hres, st));
     hipGraph_t g = nullptr;
     hipError_t ec = hipStreamEndCapture(st, &g);
     if (e != hipSuccess || ec != hipSuccess) {
@@ -304,7 +319,8 @@ ile_status run_graph(ile_batch *b, uint64_t seed, int64_t n, double dmin, double
 {
     ile_status s;
     if ((s = ensure_graph(b, n, dmin, dmax, ext))) return s;
-    BHIP(b, hipMemcpyAsync(b->seed.p, &seed, sizeof(seed), hipMemcpyHostToDevice, b->stream));
+    if (!ext)   // only the prior draws take a seed
+        BHIP(b, hipMemcpyAsync(b->seed.p, &seed, sizeof(seed), hipMemcpyHostToDevice, b->stream));
     BHIP(b, hipEventRecord(b->e0, b->stream));
     BHIP(b, hipGraphLaunch(b->exec, b->stream));
     BHIP(b, hipEventRecord(b->e1, b->stream));
@@ -312,8 +328,7 @@ ile_status run_graph(ile_batch *b, uint64_t seed, int64_t n, double dmin, double
     float ms = 0.f;
     BHIP(b, hipEventElapsedTime(&ms, b->e0, b->e1));
     b->last_ms = ms;
-    int32_t flag = 0;
-    BHIP(b, hipMemcpy(&flag, b->errflag.p, sizeof(flag), hipMemcpyDeviceToHost));
+    const int32_t flag = *reinterpret_cast<const int32_t *>(b->hres);
     if (flag) {
         BHIP(b, hipMemset(b->errflag.p, 0, 16));
         if (flag & 2) return bfail(b, ILE_E_RANGE, "invalid ln_p/ln_q of a draw");
@@ -326,8 +341,7 @@ ile_status run_graph(ile_batch *b, uint64_t seed, int64_t n, double dmin, double
 ile_status copy_results(ile_batch *b, ile_result *results)
 {
     const size_t P = b->pts.size();
-    std::vector<double> r(6 * P);
-    BHIP(b, hipMemcpy(r.data(), b->res.p, r.size() * sizeof(double), hipMemcpyDeviceToHost));
+    const double *r = b->hres + 1;   // written by the run's last kernel
     for (size_t p = 0; p < P; p++) {
         results[p].ln_L_marg = r[6 * p];
         results[p].n_eff = r[6 * p + 1];
@@ -581,8 +595,9 @@ void ile_batch_destroy(ile_batch *b)
     for (ile_ctx *c : b->pts) ile_destroy(c);
     for (Buf *x : {&b->geoms, &b->pdev, &b->items, &b->offs, &b->seed, &b->counter, &b->smp,
                    &b->out, &b->shifts, &b->keys, &b->slot, &b->rec, &b->perm, &b->hist, &b->scan_tmp, &b->errflag,
-                   &b->res, &b->lw, &b->terms})
+                   &b->red_tmp, &b->lw, &b->terms})
         if (x->p) (void)hipFree(x->p);
+    if (b->hres) (void)hipHostFree(b->hres);
     if (b->e0) (void)hipEventDestroy(b->e0);
     if (b->e1) (void)hipEventDestroy(b->e1);
     if (b->own_stream && b->stream) (void)hipStreamDestroy(b->stream);

@@ -66,9 +66,13 @@ struct ile_point_dev {
     const int32_t *perm;      // sorted order (local indices)
     const int32_t *shifts;    // window starts [n_det][N]
     double *out;              // lnLmargT [N]
-    // phased engine: the point's per-sample terms (ile_launch_terms, tile
-    // order from position 0), or null to form them in the tiles
-    const double *terms;
+    // phased engine: the point's per-sample terms (ile_launch_terms_multi, tile
+    // order from position 0) and what they are formed from, the samples'
+    // records and the packed triangles (ile_pack_uv); or all null, and the
+    // tiles form them
+    double *terms;
+    const struct ile_sample_rec *rec;
+    const double *uvt;
 };
 
 // A sample as the per-sample terms read it: parameters 0 .. 5 (t_ref is in the
@@ -209,6 +213,58 @@ __device__ inline void scan_prefix(const uint32_t *bsum, int nb, uint32_t *pre)
         run += bsum[j];
     }
     __syncthreads();
+}
+
+// Largest of a wave's values, in every lane.
+__device__ inline double wave_max(double x)
+{
+    for (int off = 32; off > 0; off >>= 1) x = fmax(x, __shfl_xor(x, off));
+    return x;
+}
+
+// A workgroup's NV sums of T values each (a thread's v[k] into sm[k][t]) by the
+// fixed tree (t, t + T/2), (t, t + T/4), ..., of which the first wave does all:
+// one barrier.  In lane 0 of that wave.
+template <int T, int NV>
+__device__ inline void tree_sum(double (&v)[NV], double (*sm)[T])
+{
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int k = 0; k < NV; k++) sm[k][t] = v[k];
+    __syncthreads();
+    if (t >= 64) return;
+#pragma unroll
+    for (int k = 0; k < NV; k++) {
+        double x[T / 64];
+#pragma unroll
+        for (int j = 0; j < T / 64; j++) x[j] = sm[k][t + 64 * j];
+#pragma unroll
+        for (int h = T / 128; h > 0; h >>= 1)
+#pragma unroll
+            for (int j = 0; j < h; j++) x[j] += x[j + h];
+        for (int off = 32; off > 0; off >>= 1) x[0] += __shfl_down(x[0], off);
+        v[k] = x[0];
+    }
+}
+
+// The result of a partial (M, S1, S2, n, maxL).
+__device__ inline void finish_one(double M, double S1, double S2, double n, double ML,
+                                  double *res)
+{
+    if (M == -INFINITY || n == 0.0) {
+        res[0] = -INFINITY;
+        res[1] = 0.0;
+        res[2] = 0.0;
+        res[3] = NAN;
+    } else {
+        res[0] = M + log(S1) - log(n);
+        res[1] = S1;
+        res[2] = S1 * S1 / S2;
+        const double var = S2 / (S1 * S1) - 1.0 / n;
+        res[3] = var > 0.0 ? sqrt(var) : 0.0;
+    }
+    res[4] = ML;
+    res[5] = n;
 }
 
 // Ordering key of a sample: its cell (window starts of up to three
@@ -374,11 +430,10 @@ hipError_t ile_launch_identity(int32_t *perm, int64_t N, hipStream_t st);
 // windows are zero for an invalid sample.  Whole tiles are written.
 int ile_terms_fields(const ile_geom &g);
 bool ile_contract_uses_terms(ile_precision prec, const ile_tune &tu);
-// The terms of positions 0 .. N-1 of one point into terms (16 F round16(N)
-// doubles); uvt as for ile_launch_contract.
-hipError_t ile_launch_terms(const ile_geom &g, const ile_sample_rec *rec, int64_t N,
-                            const int32_t *perm, const double *uvt, double *terms,
-                            hipStream_t st);
+// The terms of positions 0 .. n-1 of every point, one launch (max_lm: the
+// points' largest number of modes).
+hipError_t ile_launch_terms_multi(const ile_geom *geoms, const ile_point_dev *pts, int n_points,
+                                  int max_lm, int64_t n, hipStream_t st);
 // Positions per launch of the terms (a multiple of 16): the buffer for N
 // samples holds ile_terms_fields x min(N, ILE_TERMS_CHUNK) doubles.
 #define ILE_TERMS_CHUNK ((int64_t)1 << 21)
@@ -445,8 +500,12 @@ hipError_t ile_launch_scatter_multi(const uint32_t *keys, const uint32_t *slot,
                                     const int64_t *offs, int n_points, int64_t n_total,
                                     const uint32_t *pos, const uint32_t *bsum,
                                     int64_t n_buckets, int32_t *perm, hipStream_t st);
+// tmp: ile_reduce_points_tmp(n_points) doubles.  host (pinned): the error flag
+// in its first word, then the 6 n_points results from its second double.
+size_t ile_reduce_points_tmp(int n_points);
 hipError_t ile_launch_reduce_points(const double *out, const double *lw, const int64_t *offs,
-                                    int n_points, double *res, hipStream_t st);
+                                    int n_points, double *tmp, const int32_t *err, double *host,
+                                    hipStream_t st);
 hipError_t ile_launch_batch_lw(const double *lp, const double *lq, int64_t n_total, double *lw,
                                int32_t *err, hipStream_t st);
 hipError_t ile_launch_to_bf16_split(const double *Q, int64_t n, void *dst,

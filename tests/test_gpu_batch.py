@@ -146,3 +146,35 @@ def test_batch_items_beyond_one_dispatch(torch):
             b1.add_point(base)
             one = b1.run_dev(n, X[p:p + 1].contiguous())[0]
         assert one["ln_L_marg"] == allp[p]["ln_L_marg"] and one["n_eff"] == allp[p]["n_eff"]
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 255, 257, 16383, 16385, 33000])
+@pytest.mark.parametrize("own_draws", [False, True])
+def test_batch_results_of_n_samples(torch, n, own_draws):
+    """A point's result from its own ln L, in FP64 by numpy, at the edges of the
+    reduction's lanes and workgroups; points of 2 to 9 modes in one launch of
+    the terms.  Sums of positive terms in another order: relative 1e-12."""
+    pts = [synth.make_instance(["D1", "D2", "D3"][:1 + p % 3], nl, 4096, 4096.0, 33, 50 + p)
+           for p, nl in enumerate([2, 9, 5, 1])]
+    lw = np.zeros((len(pts), n))
+    with ile.Batch("fp64") as b:
+        for inst in pts:
+            b.add_point(inst)
+        if own_draws:
+            s = np.stack([synth.prior_samples(n, 70 + p)[0] for p in range(len(pts))])
+            rng = np.random.default_rng(n)
+            lp, lq = rng.normal(size=lw.shape), rng.normal(size=lw.shape)
+            lw = lp - lq
+            res = b.run_dev(n, *(torch.from_numpy(np.ascontiguousarray(x)).cuda()
+                                 for x in (s, lp, lq)))
+        else:
+            res = b.run(9, n)
+        lnl = np.asarray(b.lnL(n)).reshape(len(pts), n)
+    for p, r in enumerate(res):
+        w = lnl[p] + lw[p]
+        M = w.max()
+        e = np.exp(w - M)
+        S1, S2 = e.sum(), (e * e).sum()
+        assert abs(r["ln_L_marg"] - (M + np.log(S1) - np.log(n))) < 1e-12 * max(1.0, abs(M))
+        assert np.allclose([r["n_eff"], r["n_eff_kish"]], [S1, S1 * S1 / S2], rtol=1e-12, atol=0)
+        assert r["max_ln_L"] == lnl[p].max() and r["n_samples"] == n
