@@ -34,6 +34,8 @@ namespace {
 
 constexpr double kPi = 3.14159265358979323846;
 constexpr double kC = 299792458.0;
+// Largest device buffer through which a context's series go to their layout.
+constexpr size_t kStageBytes = (size_t)64 << 20;
 
 struct DevBuf {
     void *p = nullptr;
@@ -66,7 +68,7 @@ struct ile_ctx {
     DevBuf Q, U, V;
     DevBuf uvt;                     // upper triangles of U_h and V_s (see ile_launch_contract)
     DevBuf smp, out, lnp, lnq, shifts, keys, perm, hist, scan_tmp, errflag,
-        red_tmp, parts, res, series, terms, slot, rec;
+        red_tmp, parts, res, series, terms, slot, rec, stage;
     DevBuf hP, hC, bins, hist_tmp;  // adaptive proposal state and scratch
     int hist_nb = 0;
     DevBuf trx, trw;                // training set of the learned sampler
@@ -248,6 +250,17 @@ ile_status check_samples(ile_ctx *c, const double *s, int64_t N)
                         "sample %lld out of range (need finite values, D > 0, "
                         "|cos iota| <= 1, |t_ref| <= %g)",
                         (long long)i, c->cfg.t_ref_max_s);
+    return ILE_OK;
+}
+
+// A device flag that is zero between calls: cleared when made and after an
+// error.
+ile_status ensure_flag(ile_ctx *c)
+{
+    if (c->fd_flag.p) return ILE_OK;
+    ile_status s = ensure(c, c->fd_flag, 16);
+    if (s) return s;
+    HIP_TRY(c, hipMemsetAsync(c->fd_flag.p, 0, 16, c->stream));
     return ILE_OK;
 }
 
@@ -548,8 +561,28 @@ ile_status ile_set_data(ile_ctx *c, const double *Q, int64_t n_q, double t0_s,
         return fail(c, ILE_E_ARG, "n_q = %lld invalid", (long long)n_q);
     if (!std::isfinite(t0_s)) return fail(c, ILE_E_ARG, "t0 not finite");
     const size_t nQ = (size_t)nd * nl * n_q, nUV = (size_t)nd * nl * nl;
-    for (size_t i = 0; i < 2 * nQ; i++)
-        if (!std::isfinite(Q[i])) return fail(c, ILE_E_NUMERIC, "Q[%zu] not finite", i / 2);
+    ile_status s;
+    // Q that the staging buffer holds whole is checked on the device, in place
+    // before the planar copy takes over from the data there; the host looks
+    // for the entry only when there is one
+    const bool planar = c->cfg.precision != ILE_BF16, whole = planar && 16 * nQ <= kStageBytes;
+    bool finite = false;
+    HIP_TRY(c, hipSetDevice(c->cfg.device));
+    if (whole) {
+        if ((s = ensure(c, c->stage, 16 * nQ))) return s;
+        if ((s = ensure_flag(c))) return s;
+        HIP_TRY(c, hipMemcpyAsync(c->stage.p, Q, 16 * nQ, hipMemcpyHostToDevice, c->stream));
+        HIP_TRY(c, ile_launch_finite((const double *)c->stage.p, (int64_t)nQ,
+                                     (int32_t *)c->fd_flag.p, c->stream));
+        HIP_TRY(c, ile_launch_fetch((const int32_t *)c->fd_flag.p, nullptr, (double *)c->hpin,
+                                    c->stream));
+        HIP_TRY(c, hipStreamSynchronize(c->stream));
+        finite = !*(const int32_t *)c->hpin;
+        if (!finite) HIP_TRY(c, hipMemsetAsync(c->fd_flag.p, 0, 16, c->stream));
+    }
+    if (!finite)
+        for (size_t i = 0; i < 2 * nQ; i++)
+            if (!std::isfinite(Q[i])) return fail(c, ILE_E_NUMERIC, "Q[%zu] not finite", i / 2);
     for (size_t i = 0; i < 2 * nUV; i++)
         if (!std::isfinite(U[i]) || !std::isfinite(V[i]))
             return fail(c, ILE_E_NUMERIC, "U or V entry %zu not finite", i / 2);
@@ -604,8 +637,6 @@ ile_status ile_set_data(ile_ctx *c, const double *Q, int64_t n_q, double t0_s,
     for (int d = 0; d < 3; d++) g.key_lo[d] = (int)slo;
     c->n_buckets = (1u << (bits * g.key_dims)) + 1u;
 
-    ile_status s;
-    HIP_TRY(c, hipSetDevice(c->cfg.device));
     // device layout: planar rows per detector, row 2a = Re Q_a, 2a+1 = Im Q_a,
     // padded with zero rows to 4 * ksp_of(n_lm) (the matrix-core K steps)
     const size_t rp = (size_t)4 * ksp_of(nl);
@@ -616,19 +647,27 @@ ile_status ile_set_data(ile_ctx *c, const double *Q, int64_t n_q, double t0_s,
     if ((s = ensure(c, c->Q, q_bytes))) return s;
     if ((s = ensure(c, c->U, nUV * 16))) return s;
     if ((s = ensure(c, c->V, nUV * 16))) return s;
-    if (c->cfg.precision == ILE_FP64) {
-        std::vector<double> h(nQd, 0.0);
-        for (int k = 0; k < nd; k++)
-            for (int a = 0; a < nl; a++)
-                for (int64_t i = 0; i < n_q; i++) {
-                    const double *q = Q + 2 * (((size_t)k * nl + a) * n_q + i);
-                    h[((size_t)k * rp + 2 * a) * n_q + i] = q[0];
-                    h[((size_t)k * rp + 2 * a + 1) * n_q + i] = q[1];
-                }
-        HIP_TRY(c, hipMemcpy(c->Q.p, h.data(), nQd * 8, hipMemcpyHostToDevice));
-    } else if (c->cfg.precision == ILE_BF16) {
+    hipStream_t st = c->stream;
+    std::vector<uint16_t> h;
+    if (planar) {
+        // rows through the staging buffer: all at once, or whole rows, or
+        // parts of one (each part's copy follows the kernel that read the last)
+        const int64_t vals = (int64_t)(kStageBytes / 16), ni = std::min<int64_t>(n_q, vals);
+        const int nr = (int)std::min<int64_t>((int64_t)nd * nl, std::max<int64_t>(vals / ni, 1));
+        if ((s = ensure(c, c->stage, (size_t)16 * nr * ni))) return s;
+        for (int r = 0; r < nd * nl; r += nr)
+            for (int64_t i = 0; i < n_q; i += ni) {
+                const int m = std::min(nr, nd * nl - r);
+                const int64_t w = std::min<int64_t>(ni, n_q - i);
+                if (!whole)
+                    HIP_TRY(c, hipMemcpyAsync(c->stage.p, Q + 2 * ((size_t)r * n_q + i),
+                                              (size_t)16 * m * w, hipMemcpyHostToDevice, st));
+                HIP_TRY(c, ile_launch_planar((const double *)c->stage.p, r, m, i, w, nl, n_q,
+                                             c->cfg.precision == ILE_FP64, c->Q.p, st));
+            }
+    } else {
         // K-contiguous per position: [Q_hi rows; Q_lo rows; Q_hi rows; zeros]
-        std::vector<uint16_t> h((size_t)nd * n_q * kb, 0);
+        h.assign((size_t)nd * n_q * kb, 0);
         const size_t R = 2 * (size_t)nl;
         for (int k = 0; k < nd; k++)
             for (int a = 0; a < nl; a++)
@@ -644,31 +683,21 @@ ile_status ile_set_data(ile_ctx *c, const double *Q, int64_t n_q, double t0_s,
                         row[2 * R + r] = hi;
                     }
                 }
-        HIP_TRY(c, hipMemcpy(c->Q.p, h.data(), h.size() * 2, hipMemcpyHostToDevice));
-    } else {
-        std::vector<float> h(nQd, 0.0f);
-        for (int k = 0; k < nd; k++)
-            for (int a = 0; a < nl; a++)
-                for (int64_t i = 0; i < n_q; i++) {
-                    const double *q = Q + 2 * (((size_t)k * nl + a) * n_q + i);
-                    h[((size_t)k * rp + 2 * a) * n_q + i] = (float)q[0];
-                    h[((size_t)k * rp + 2 * a + 1) * n_q + i] = (float)q[1];
-                }
-        HIP_TRY(c, hipMemcpy(c->Q.p, h.data(), nQd * 4, hipMemcpyHostToDevice));
+        HIP_TRY(c, hipMemcpyAsync(c->Q.p, h.data(), h.size() * 2, hipMemcpyHostToDevice, st));
     }
-    HIP_TRY(c, hipMemcpy(c->U.p, U, nUV * 16, hipMemcpyHostToDevice));
-    HIP_TRY(c, hipMemcpy(c->V.p, V, nUV * 16, hipMemcpyHostToDevice));
+    HIP_TRY(c, hipMemcpyAsync(c->U.p, U, nUV * 16, hipMemcpyHostToDevice, st));
+    HIP_TRY(c, hipMemcpyAsync(c->V.p, V, nUV * 16, hipMemcpyHostToDevice, st));
     // the Hermitian part of U and the symmetric part of V: the only parts
     // the quadratic term of Eq. (7) sees (Re(Y^H U Y) = Y^H U_h Y,
     // Y^T V Y = Y^T V_s Y)
-    {
-        std::vector<double> t(ile_pack_uv_doubles(nd, nl));
-        ile_pack_uv(nd, nl, U, V, t.data());
-        if ((s = ensure(c, c->uvt, t.size() * sizeof(double)))) return s;
-        HIP_TRY(c, hipMemcpy(c->uvt.p, t.data(), t.size() * sizeof(double), hipMemcpyHostToDevice));
-    }
+    std::vector<double> t(ile_pack_uv_doubles(nd, nl));
+    ile_pack_uv(nd, nl, U, V, t.data());
+    if ((s = ensure(c, c->uvt, t.size() * sizeof(double)))) return s;
+    HIP_TRY(c, hipMemcpyAsync(c->uvt.p, t.data(), t.size() * sizeof(double),
+                              hipMemcpyHostToDevice, st));
     if ((s = ensure(c, c->errflag, 16))) return s;
-    HIP_TRY(c, hipMemset(c->errflag.p, 0, 16));
+    HIP_TRY(c, ile_launch_fill_u32((uint32_t *)c->errflag.p, 0u, 4, st));
+    HIP_TRY(c, hipStreamSynchronize(st));   // every stream may read the data from here on
     c->have_data = true;
     return ILE_OK;
 }
@@ -775,11 +804,7 @@ ile_status ile_qvu_fd_dev(ile_ctx *c, const double *h_f, const double *d_f, cons
     ile_status s;
     if ((s = ensure(c, c->fd_tmp, ile_fd_tmp_bytes(n_q, nd, nl)))) return s;
     hipStream_t st = c->stream;
-    // the flag is zero between calls: cleared when made and after an error
-    if (!c->fd_flag.p) {
-        if ((s = ensure(c, c->fd_flag, 16))) return s;
-        HIP_TRY(c, hipMemsetAsync(c->fd_flag.p, 0, 16, st));
-    }
+    if ((s = ensure_flag(c))) return s;
     int32_t *flag = (int32_t *)c->fd_flag.p, *hflag = (int32_t *)c->hpin;
     hipEvent_t e0 = next_event(c), e1 = next_event(c);
     if (!e0 || !e1) return fail(c, ILE_E_DEVICE, "hipEventCreate failed");
@@ -1603,7 +1628,7 @@ void ile_destroy(ile_ctx *c)
                       &c->hP, &c->hC, &c->bins, &c->hist_tmp, &c->trx, &c->trw,
                       &c->hv_w, &c->hv_cdf, &c->hv_ws, &c->hv_part, &c->hv_flag, &c->hv_sel,
                       &c->fd_tmp, &c->fd_flag, &c->fd_in, &c->fd_out, &c->rom_A, &c->rom_Z,
-                      &c->uvt, &c->terms, &c->slot, &c->rec})
+                      &c->uvt, &c->terms, &c->slot, &c->rec, &c->stage})
         release(*b);
     for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
     if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);

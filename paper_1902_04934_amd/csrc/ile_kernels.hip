@@ -204,6 +204,34 @@ __global__ __launch_bounds__(256) void k_inject_gram(int n_lm, int n, const doub
     }
 }
 
+// ------------------------------------------------------------ data layout
+__global__ __launch_bounds__(256) void k_finite(const double2 *__restrict__ z, int64_t n,
+                                                int32_t *flag)
+{
+    bool bad = false;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+        bad |= !(isfinite(z[i].x) && isfinite(z[i].y));
+    if (bad) atomicOr(flag, 1);
+}
+
+// A pass at the copy rate in place of the host's (3 x 21 x 16384 values: 1 ms of
+// checks and stores there, with the page faults of a second copy).
+template <typename T>
+__global__ __launch_bounds__(256) void k_planar(const double2 *__restrict__ raw, int r0,
+                                                int64_t i0, int64_t ni, int n_lm, int rp,
+                                                int64_t n_q, T *__restrict__ dst)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= ni) return;
+    const int r = r0 + blockIdx.y, k = r / n_lm, a = r % n_lm;
+    const double2 z = raw[(int64_t)blockIdx.y * ni + i];
+    T *d = dst + ((int64_t)k * rp + 2 * a) * n_q + i0 + i;
+    d[0] = (T)z.x;
+    d[n_q] = (T)z.y;
+    if (a == n_lm - 1)
+        for (int q = 2; 2 * a + q < rp; q++) d[q * n_q] = (T)0;
+}
+
 // ------------------------------------------------------------------ prep
 __global__ void k_fill_u32(uint32_t *p, uint32_t v, int64_t n)
 {
@@ -2418,6 +2446,29 @@ hipError_t launch_batched_ph(const ile_geom *geoms, const ile_point_dev *pts, co
 }  // namespace
 
 // ------------------------------------------------------------ launchers
+hipError_t ile_launch_finite(const double *z, int64_t n, int32_t *flag, hipStream_t st)
+{
+    if (n <= 0) return hipSuccess;
+    const unsigned grid = (unsigned)std::min<int64_t>((n + 255) / 256, 4096);
+    hipLaunchKernelGGL(k_finite, dim3(grid), dim3(256), 0, st, (const double2 *)z, n, flag);
+    return hipGetLastError();
+}
+
+hipError_t ile_launch_planar(const double *raw, int r0, int nr, int64_t i0, int64_t ni, int n_lm,
+                             int64_t n_q, bool fp64, void *dst, hipStream_t st)
+{
+    if (nr <= 0 || ni <= 0) return hipSuccess;
+    const dim3 grid(nblk(ni, 256), nr);
+    const int rp = 4 * ksp_of(n_lm);
+    if (fp64)
+        hipLaunchKernelGGL((k_planar<double>), grid, dim3(256), 0, st, (const double2 *)raw, r0,
+                           i0, ni, n_lm, rp, n_q, (double *)dst);
+    else
+        hipLaunchKernelGGL((k_planar<float>), grid, dim3(256), 0, st, (const double2 *)raw, r0,
+                           i0, ni, n_lm, rp, n_q, (float *)dst);
+    return hipGetLastError();
+}
+
 hipError_t ile_launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
