@@ -82,6 +82,7 @@ struct ile_ctx {
     std::vector<hipEvent_t> ev;   // pairs around contraction launches
     int n_ev_used = 0;
     double last_ms = 0.0;
+    int flag_word = 0;      // of errflag, which evaluations set: 1 in ile_integrate
     void *hpin = nullptr;   // pinned host words: the error flag, then the 6 result fields
 };
 
@@ -345,8 +346,8 @@ ile_status launch_eval(ile_ctx *c, const Work &w, const double *smp, int64_t N, 
     const bool rank = c->sort && N <= ile_rank_max(), count = c->sort && !rank;
     if (count) HIP_TRY(c, ile_launch_fill_u32(w.hist, 0u, c->n_buckets, st));
     HIP_TRY(c, ile_launch_prep(c->g, smp, N, w.rec, w.shifts, w.keys, w.slot,
-                               count ? w.hist : nullptr, c->n_buckets, (int32_t *)c->errflag.p,
-                               st));
+                               count ? w.hist : nullptr, c->n_buckets,
+                               (int32_t *)c->errflag.p + c->flag_word, st));
     if (count) {
         HIP_TRY(c, ile_launch_scan(w.hist, c->n_buckets, w.scan_tmp, st));
         HIP_TRY(c, ile_launch_scatter(w.keys, w.slot, N, w.hist, w.scan_tmp, c->n_buckets, w.perm,
@@ -409,7 +410,7 @@ ile_status finish_call(ile_ctx *c)
     if (n) c->last_ms = tot / n;
     if (c->errflag.p) {
         if (*hflag) {
-            HIP_TRY(c, hipMemset(c->errflag.p, 0, sizeof(int32_t)));
+            HIP_TRY(c, hipMemset(c->errflag.p, 0, 2 * sizeof(int32_t)));
             return fail(c, ILE_E_RANGE,
                         "a device-side sample was out of range (its output is NaN)");
         }
@@ -1051,18 +1052,23 @@ static void copy_result(const double *r, ile_result *out)
     out->n_samples = (int64_t)r[5];
 }
 
-ile_status ile_integrate(ile_ctx *c, const double *samples, const double *ln_p,
-                         const double *ln_q, int64_t N, ile_result *out)
+static ile_status check_draws(ile_ctx *c, const double *samples, const double *ln_p,
+                              const double *ln_q, int64_t N)
 {
-    ile_status s = check_ready(c);
+    ile_status s = check_samples(c, samples, N);
     if (s) return s;
-    if (N < 0 || !out || (N > 0 && (!samples || !ln_p || !ln_q)))
-        return fail(c, ILE_E_ARG, "bad N or pointer");
-    if ((s = check_samples(c, samples, N))) return s;
     for (int64_t i = 0; i < N; i++)
         if (std::isnan(ln_p[i]) || std::isnan(ln_q[i]) || ln_q[i] == -INFINITY ||
             ln_p[i] == INFINITY)
             return fail(c, ILE_E_RANGE, "ln_p/ln_q of sample %lld invalid", (long long)i);
+    return ILE_OK;
+}
+
+// Uploads and launches of ile_integrate, its result left in c->res.
+static ile_status integrate_queue(ile_ctx *c, const double *samples, const double *ln_p,
+                                  const double *ln_q, int64_t N)
+{
+    ile_status s;
     const size_t n = (size_t)std::max<int64_t>(N, 1);
     if ((s = ensure(c, c->smp, n * 7 * sizeof(double)))) return s;
     if ((s = ensure(c, c->lnp, n * sizeof(double)))) return s;
@@ -1076,10 +1082,33 @@ ile_status ile_integrate(ile_ctx *c, const double *samples, const double *ln_p,
         HIP_TRY(c, hipMemcpyAsync(c->lnq.p, ln_q, (size_t)N * sizeof(double),
                                   hipMemcpyHostToDevice, c->stream));
     }
-    if ((s = integrate_dev_impl(c, (const double *)c->smp.p, (const double *)c->lnp.p,
-                                (const double *)c->lnq.p, N, (double *)c->res.p)))
-        return s;
-    if ((s = finish_call(c))) return s;
+    return integrate_dev_impl(c, (const double *)c->smp.p, (const double *)c->lnp.p,
+                              (const double *)c->lnq.p, N, (double *)c->res.p);
+}
+
+ile_status ile_integrate(ile_ctx *c, const double *samples, const double *ln_p,
+                         const double *ln_q, int64_t N, ile_result *out)
+{
+    ile_status s = check_ready(c);
+    if (s) return s;
+    if (N < 0 || !out || (N > 0 && (!samples || !ln_p || !ln_q)))
+        return fail(c, ILE_E_ARG, "bad N or pointer");
+    // The arrays are checked while the device works on them (it takes any
+    // values: an invalid sample's is NaN): 20 us of a call of 1e4 samples
+    // otherwise spent before its first launch.  What they hold decides before
+    // anything the device reports, and leaves nothing behind: the device's
+    // flag of this call is a word of its own.
+    c->flag_word = 1;
+    s = integrate_queue(c, samples, ln_p, ln_q, N);
+    c->flag_word = 0;
+    const ile_status bad = check_draws(c, samples, ln_p, ln_q, N);
+    if (bad) {
+        (void)hipStreamSynchronize(c->stream);
+        if (c->errflag.p) (void)hipMemset((int32_t *)c->errflag.p + 1, 0, sizeof(int32_t));
+        c->n_ev_used = 0;
+        return bad;
+    }
+    if (s || (s = finish_call(c))) return s;
     double r[6];
     fetched_result(c, r);
     copy_result(r, out);

@@ -471,7 +471,7 @@ hipError_t ile_launch_reduce(const double *lnL, const double *ln_p,
                              const double *ln_q, int64_t N, double *tmp,
                              double *partial, const double *parts, int n_part, double *res,
                              hipStream_t st);
-// *flag to the first word of host and res[0 .. 5] to host[1 .. 6] (pinned
+// flag[0] | flag[1] to the first word of host and res[0 .. 5] to host[1 .. 6] (pinned
 // host memory; either may be null).
 hipError_t ile_launch_fetch(const int32_t *flag, const double *res, double *host,
                             hipStream_t st);

@@ -2314,7 +2314,7 @@ __global__ void k_fetch(const int32_t *__restrict__ flag, const double *__restri
                         double *__restrict__ host)
 {
     const int t = threadIdx.x;
-    if (t == 0 && flag) *reinterpret_cast<int32_t *>(host) = *flag;
+    if (t == 0 && flag) *reinterpret_cast<int32_t *>(host) = flag[0] | flag[1];
     if (t >= 1 && t <= 6 && res) host[t] = res[t - 1];
 }
 

@@ -38,3 +38,34 @@ def test_result_of_n_samples(n, densities):
     assert np.allclose(got[1:3], [S1, S1 * S1 / S2], rtol=1e-12, atol=0)
     assert abs(got[3] ** 2 - max(var, 0.0)) < 1e-13
     assert got[4] == lnL.max() and got[5] == n
+
+
+def test_refused_host_arrays_leave_nothing_behind():
+    """ile_integrate checks its arrays beside the device's work: a refusal names
+    the entry, the next call's values are those of a fresh context, and an
+    error that an earlier device call left is still reported after it."""
+    import torch
+    inst = synth.make_instance(["D1", "D2"], 2, 4096, 4096.0, 33, 3)
+    n = 500
+    s, lp = synth.prior_samples(n, 5)
+    with ile.Context(inst, precision="fp64") as ctx:
+        want = ctx.integrate(s, lp, lp)
+        bad = s.copy()
+        bad[5, 77] = -1.0
+        with pytest.raises(ile.IleError, match="sample 77 out of range"):
+            ctx.integrate(bad, lp, lp)
+        q = lp.copy()
+        q[11] = np.nan
+        with pytest.raises(ile.IleError, match="ln_p/ln_q of sample 11 invalid"):
+            ctx.integrate(s, lp, q)
+        assert ctx.integrate(s, lp, lp) == want
+        d = torch.from_numpy(bad).cuda()
+        out = torch.zeros(n, dtype=torch.float64, device="cuda")
+        torch.cuda.synchronize()
+        ctx.eval_dev(d, n, out)
+        with pytest.raises(ile.IleError, match="sample 77 out of range"):
+            ctx.integrate(bad, lp, lp)
+        with pytest.raises(ile.IleError, match="device-side sample"):
+            ctx.sync()
+        ctx.sync()
+        assert ctx.integrate(s, lp, lp) == want
