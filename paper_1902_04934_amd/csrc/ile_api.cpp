@@ -880,8 +880,10 @@ ile_status ile_rom_set(ile_ctx *c, const ile_mode *modes, int32_t n_lm, int32_t 
     for (size_t i = 0; i < na; i++)
         if (!std::isfinite(A[i])) return fail(c, ILE_E_NUMERIC, "A[%zu] not finite", i / 2);
     ile_status s;
-    if ((s = ensure(c, c->rom_A, na * sizeof(double)))) return s;
-    HIP_TRY(c, hipMemcpy(c->rom_A.p, A, na * sizeof(double), hipMemcpyHostToDevice));
+    std::vector<double> t(ile_pack_rom_doubles(n_lm, c->cfg.n_lm, n_pow));
+    ile_pack_rom(n_lm, c->cfg.n_lm, n_pow, A, t.data());
+    if ((s = ensure(c, c->rom_A, t.size() * sizeof(double)))) return s;
+    HIP_TRY(c, hipMemcpy(c->rom_A.p, t.data(), t.size() * sizeof(double), hipMemcpyHostToDevice));
     c->rom_g = gp;
     c->rom_pow = n_pow;
     return ILE_OK;

@@ -342,6 +342,48 @@ __device__ inline double2 sylm_dev(const ile_geom &g, int a, double cos_iota,
     return make_double2(sum * cm, sum * sm);
 }
 
+// The tables that harmonics are read from, register arrays read at indices that
+// are the same in every lane: powers of cos(iota/2), sin(iota/2) by repeated
+// products from 1, and e^{i m phi} = (e^{i phi})^m, |m| <= ILE_LMAX.
+constexpr int kPw = 2 * ILE_LMAX + 1;
+__device__ __forceinline__ void ylm_tables(double cos_iota, double phi, double (&cp)[kPw],
+                                           double (&sp)[kPw], double (&er)[kPw],
+                                           double (&ei)[kPw])
+{
+    const double c = sqrt(0.5 * (1.0 + cos_iota)), sn = sqrt(0.5 * (1.0 - cos_iota));
+    cp[0] = sp[0] = 1.0;
+#pragma unroll
+    for (int q = 1; q < kPw; q++) {
+        cp[q] = cp[q - 1] * c;
+        sp[q] = sp[q - 1] * sn;
+    }
+    double s1, c1;
+    sincos(phi, &s1, &c1);
+    er[ILE_LMAX] = 1.0;
+    ei[ILE_LMAX] = 0.0;
+#pragma unroll
+    for (int m = 1; m <= ILE_LMAX; m++) {
+        const double pr = er[ILE_LMAX + m - 1], pi = ei[ILE_LMAX + m - 1];
+        er[ILE_LMAX + m] = fma(pr, c1, -(pi * s1));
+        ei[ILE_LMAX + m] = fma(pr, s1, pi * c1);
+        er[ILE_LMAX - m] = er[ILE_LMAX + m];
+        ei[ILE_LMAX - m] = -ei[ILE_LMAX + m];
+    }
+}
+
+// -2Y_lm of mode a from the tables: its Wigner-d terms, then e^{i m phi}.
+__device__ __forceinline__ double2 ylm_entry(const ile_geom &g, int a, const double (&cp)[kPw],
+                                             const double (&sp)[kPw], const double (&er)[kPw],
+                                             const double (&ei)[kPw])
+{
+    const int u0 = g.mode_first[a], nt = g.mode_nterm[a];
+    double sum = 0.0;
+    for (int u = u0; u < u0 + nt; u++)
+        sum += g.term_a[u] * cp[g.term_pw[u] & 255] * sp[g.term_pw[u] >> 8];
+    const int mi = ILE_LMAX + g.mode_m[a];
+    return make_double2(sum * er[mi], sum * ei[mi]);
+}
+
 __host__ __device__ inline int ksp_of(int n_lm) { return (2 * n_lm + 3) / 4; }
 
 // K steps (32 rows each) of the BF16 hi/lo contraction: the rows are
@@ -522,8 +564,12 @@ hipError_t ile_launch_to_bf16_split(const double *Q, int64_t n, void *dst,
 // ------------------------------------ surrogate (linear-basis) form
 // z_b = sum_lm c_lm,b(lambda) -2Y_lm(iota, phi) per joint sample (rows 0..6
 // extrinsic, row 7 lambda of smp [8][N]); gp holds the physical modes' Y
-// tables; A [n_lm][n_b][n_pow] complex; err bit 0 for lambda outside [-1, 1]
-// (z = NaN).
+// tables; err bit 0 for lambda outside [-1, 1] (z = NaN).  A: the packed
+// coefficients, mode by mode and power by power of lambda the n_b complex
+// values, padded with zeros to groups of eight (ile_pack_rom_doubles; a group
+// more follows the last).
+size_t ile_pack_rom_doubles(int n_lm, int n_b, int n_pow);
+void ile_pack_rom(int n_lm, int n_b, int n_pow, const double *A, double *out);
 hipError_t ile_launch_rom_z(const ile_geom &gp, const double *smp, int64_t N, const double *A,
                             int n_b, int n_pow, double *Z, int32_t *err, hipStream_t st);
 

@@ -97,7 +97,6 @@ __device__ inline void antenna_dev(const ile_geom &g, int k, double ra,
 // Per-sample tables of the tile prologue: the sines and cosines of the
 // antenna patterns, powers 0 .. 2 ILE_LMAX of cos(iota/2) and sin(iota/2),
 // and e^{i m phi} for |m| <= ILE_LMAX.
-constexpr int kPw = 2 * ILE_LMAX + 1;
 constexpr int kProTab = 6 + 2 * kPw + 2 * kPw;   // doubles per sample
 
 __host__ __device__ inline size_t prologue_scratch_bytes(int ts, int nd, int nl)
@@ -993,27 +992,7 @@ __device__ __forceinline__ void terms_intake(const ile_geom &g,
     sincos(th[1], &S.tr[2], &S.tr[3]);
     sincos(th[2], &S.tr[4], &S.tr[5]);
     S.kap = ok ? g.d_ref / th[5] : 0.0;
-    // powers of cos(iota/2), sin(iota/2) by repeated products from 1, and
-    // e^{i m phi} = (e^{i phi})^m, |m| <= ILE_LMAX
-    const double c = sqrt(0.5 * (1.0 + th[4])), sn = sqrt(0.5 * (1.0 - th[4]));
-    cp[0] = sp[0] = 1.0;
-#pragma unroll
-    for (int q = 1; q < kPw; q++) {
-        cp[q] = cp[q - 1] * c;
-        sp[q] = sp[q - 1] * sn;
-    }
-    double s1, c1;
-    sincos(th[3], &s1, &c1);
-    er[ILE_LMAX] = 1.0;
-    ei[ILE_LMAX] = 0.0;
-#pragma unroll
-    for (int m = 1; m <= ILE_LMAX; m++) {
-        const double pr = er[ILE_LMAX + m - 1], pi = ei[ILE_LMAX + m - 1];
-        er[ILE_LMAX + m] = pr * c1 - pi * s1;
-        ei[ILE_LMAX + m] = pr * s1 + pi * c1;
-        er[ILE_LMAX - m] = er[ILE_LMAX + m];
-        ei[ILE_LMAX - m] = -ei[ILE_LMAX + m];
-    }
+    ylm_tables(th[4], th[3], cp, sp, er, ei);
 }
 
 // -2Y_lm of mode a: the mode's Wigner-d terms, then e^{i m phi}; or the
@@ -1025,12 +1004,7 @@ __device__ __forceinline__ double2 terms_harmonic(const ile_geom &g, const Terms
                                                   const double (&ei)[kPw])
 {
     if (g.ext_y) return S.ok ? g.ext_y[(int64_t)S.idx * g.n_lm + a] : make_double2(0.0, 0.0);
-    const int u0 = g.mode_first[a], nt = g.mode_nterm[a];
-    double sum = 0.0;
-    for (int u = u0; u < u0 + nt; u++)
-        sum += g.term_a[u] * cp[g.term_pw[u] & 255] * sp[g.term_pw[u] >> 8];
-    const int mi = ILE_LMAX + g.mode_m[a];
-    return make_double2(sum * er[mi], sum * ei[mi]);
+    return ylm_entry(g, a, cp, sp, er, ei);
 }
 
 // Row a of detector k's part of the quadratic term (the b > a sums w_U, w_V

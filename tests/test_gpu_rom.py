@@ -148,3 +148,34 @@ def test_rom_table_beyond_lds(torch, orc):
     err = np.abs(got - want).max()
     print(f"rom, table in global memory: max err {err:.3e}")
     assert err <= 1e-9
+
+
+@pytest.mark.parametrize("n_b,n_lm,n_pow", [(1, 1, 1), (7, 3, 2), (8, 5, 3), (9, 2, 8), (16, 1, 4),
+                                            (17, 4, 1), (21, 21, 4), (24, 6, 2), (25, 2, 3),
+                                            (32, 3, 2)])
+def test_rom_sizes(torch, orc, n_b, n_lm, n_pow):
+    """Every number of groups of eight basis elements, full and with a
+    remainder, one to eight powers of lambda, a last wave with empty lanes and
+    lambda at its ends; the plain path's FP64 tolerance."""
+    n = 70
+    basis = synth.make_instance(["D1", "D2"], min(n_b, 21), 1024, 1024.0, 21, 300 + n_b)
+    if n_b > 21:   # the first elements once more
+        i = np.arange(n_b) % 21
+        basis.modes = [basis.modes[j] for j in i]
+        basis.Q = basis.Q[:, i].copy()
+        basis.U, basis.V = (x[:, i][:, :, i].copy() for x in (basis.U, basis.V))
+    rng = np.random.default_rng(n_b)
+    A = (rng.normal(size=(n_lm, n_b, n_pow)) + 1j * rng.normal(size=(n_lm, n_b, n_pow))) / (
+        n_b * n_lm * n_pow)
+    lam = rng.uniform(-1, 1, n)
+    lam[:3] = -1.0, 0.0, 1.0
+    s8 = np.vstack([synth.prior_samples(n, n_b)[0], lam[None]])
+    modes = synth.MODE_ORDER[:n_lm]
+    want = orc.rom_eval(basis, modes, A, s8)
+    with ile.Context(basis) as ctx:
+        ile.ile_rom_set(ctx.h, modes, A)
+        got = _run(torch, ctx, s8)
+        s8[7, 69] = 1.5
+        with pytest.raises(ile.IleError):
+            _run(torch, ctx, s8)
+    assert np.abs(got - want).max() <= 1e-9
