@@ -438,10 +438,6 @@ void ile_contract_prepare(ile_geom &g, ile_precision prec, const ile_tune &tu);
 
 // Launch wrappers (ile_kernels.hip).  All are asynchronous on `st`.
 hipError_t ile_launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t st);
-// Window starts and ordering keys of N samples: records into rec or (rec null)
-// window starts [n_det][N] into shifts; the bucket counts and every sample's
-// slot in its bucket into hist and slot (hist null: neither).  Invalid samples
-// take the last bucket and set bit 0 of *err.
 // n complex values all finite? else bit 0 of *flag.
 hipError_t ile_launch_finite(const double *z, int64_t n, int32_t *flag, hipStream_t st);
 // Source rows r0 .. r0 + nr - 1 (row k n_lm + a: detector k, mode a) of Q,
@@ -450,6 +446,10 @@ hipError_t ile_launch_finite(const double *z, int64_t n, int32_t *flag, hipStrea
 // Re, Im of mode a; a detector's zero rows are written with its last mode.
 hipError_t ile_launch_planar(const double *raw, int r0, int nr, int64_t i0, int64_t ni, int n_lm,
                              int64_t n_q, bool fp64, void *dst, hipStream_t st);
+// Window starts and ordering keys of N samples: records into rec or (rec null)
+// window starts [n_det][N] into shifts; the bucket counts and every sample's
+// slot in its bucket into hist and slot (hist null: neither).  Invalid samples
+// take the last bucket and set bit 0 of *err.
 hipError_t ile_launch_prep(const ile_geom &g, const double *smp, int64_t N, ile_sample_rec *rec,
                            int32_t *shifts, uint32_t *keys, uint32_t *slot, uint32_t *hist,
                            uint32_t n_buckets, int32_t *err, hipStream_t st);

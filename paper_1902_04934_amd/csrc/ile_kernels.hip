@@ -8,8 +8,10 @@
 //
 // Pipeline for a block of N samples:
 //   k_prep        window starts s_k per (sample, detector), validity,
-//                 ordering key (Hilbert index of the window starts)
-//   k_scan*       counting sort of the samples by key (cells of nearby windows)
+//                 ordering key (Hilbert index of the window starts), the
+//                 sample's record and its slot among the samples of its key
+//   k_scan_local, k_scatter   the samples' order by key (cells of nearby
+//                 windows) from the counts; k_rank: by pairs, for small N
 //   k_terms       per sample in tile order: harmonics, antenna factors and the
 //                 quadratic term of Eq. (7) (FP64 and FP32 phased engine)
 //   k_contract_ph per tile of 16 samples: the coefficients in LDS; per time
@@ -20,11 +22,13 @@
 //                 the bins; deterministic tree at the end
 //   k_contract    the same with the per-sample work in the tile, producer and
 //                 consumer waves (BF16; selectable for FP64/FP32) or VALU
-//   k_red*        FP64 importance-sampling partials {M, S1, S2, n, maxL}.
+//   k_red*        FP64 importance-sampling partials {M, S1, S2, n, maxL} and
+//                 their result.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 

@@ -1017,9 +1017,8 @@ __global__ __launch_bounds__(256) void k_mdn_cast(ile_mdn_dev M)
 // four times the occupancy; the slices combine in slice order.  Bound by that
 // read, which runs at the rate of a large copy (37 MB of a batch of 16384 in
 // 8.5 us; 12.2 us when the rows held the masked entries too).  A masked
-// parameter's gradient
-// is zero: its weight and moments are zeros and stay so (grad, if wanted, holds
-// zeros there already).
+// parameter's gradient is zero: its weight and moments are zeros and stay so
+// (grad, if wanted, holds zeros there already).
 constexpr int UPD_P = 64;   // entries per workgroup
 __global__ __launch_bounds__(256) void k_mdn_update(ile_mdn_dev M, const float *__restrict__ part,
                                                     int np, float *grad, double *loss, int adam,
