@@ -699,6 +699,9 @@ ile_status ile_set_data(ile_ctx *c, const double *Q, int64_t n_q, double t0_s,
     if ((s = ensure(c, c->errflag, 16))) return s;
     HIP_TRY(c, ile_launch_fill_u32((uint32_t *)c->errflag.p, 0u, 4, st));
     HIP_TRY(c, hipStreamSynchronize(st));   // every stream may read the data from here on
+    // a context whose data is set once (a batch's points) holds no staging
+    // buffer; one that goes from point to point keeps it from its second on
+    if (!c->have_data) release(c->stage);
     c->have_data = true;
     return ILE_OK;
 }

@@ -41,3 +41,27 @@ def test_not_finite_refused(at, precision):
             assert np.array_equal(ctx.eval(s), want)
         ile.ile_set_data(ctx.h, inst.Q, inst.t0_s, inst.U, inst.V, inst.dets)
         assert np.array_equal(ctx.eval(s), want)
+
+
+def test_staging_is_given_back():
+    """A context holds no staging buffer after its first data, and the same one
+    through any number of further ones (device memory as the runtime counts
+    it, within the 2 MiB pages it hands out)."""
+    import torch
+    inst = synth.make_instance(["D1", "D2", "D3"], 21, 16384, 16384.0, 65, 8)   # 16.5 MB of series
+    raw = 16 * inst.Q.size
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+    with ile.Context(inst, precision="fp32"):   # code objects and pools of the first use
+        pass
+    f0 = free()
+    with ile.Context(inst, precision="fp32") as ctx:
+        planar = 3 * 44 * 16384 * 4
+        f1 = free()
+        assert f0 - f1 < planar + (12 << 20)
+        for _ in range(3):
+            ile.ile_set_data(ctx.h, inst.Q, inst.t0_s, inst.U, inst.V, inst.dets)
+        assert f1 - free() < raw + (4 << 20)
+    assert f0 - free() < (4 << 20)
