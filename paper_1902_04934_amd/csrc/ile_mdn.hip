@@ -205,13 +205,28 @@ __device__ inline double to_z_dim(const ile_mdn_tr &T, int d, double x, float &z
     return -log(T.scale[d]) - lu - l1u + ldu;
 }
 
-// all dimensions; returns the sum of their ln |dz~/dx| in order
+// The dimensions' ln |dz~/dx| summed in order, -inf where any of them is: a
+// declination past the poles has a NaN (the logarithm of a negative cosine),
+// which must not hide that x is outside another dimension's range.
+__device__ inline double sum_lj(const double *lj)
+{
+    double s = 0.0;
+    bool out = false;
+#pragma unroll
+    for (int d = 0; d < D; d++) {
+        out |= lj[d] == -INFINITY;
+        s += lj[d];
+    }
+    return out ? -INFINITY : s;
+}
+
+// all dimensions
 __device__ inline double to_z(const ile_mdn_tr &T, const double x[7], float z[7])
 {
-    double lj = 0.0;
+    double lj[D];
 #pragma unroll
-    for (int d = 0; d < D; d++) lj += to_z_dim(T, d, x[d], z[d]);
-    return lj;
+    for (int d = 0; d < D; d++) lj[d] = to_z_dim(T, d, x[d], z[d]);
+    return sum_lj(lj);
 }
 
 __device__ inline double logaddexp(double a, double b)
@@ -639,9 +654,7 @@ __global__ __launch_bounds__(IT, 2) void k_mdn_infer(
             for (int h = 0; h < 2; h++)
                 if (g + 4 * h < D) x_io[(g + 4 * h) * ld + i] = xd[h];
         if (g == 0 && valid) {
-            double jac = 0.0;
-#pragma unroll
-            for (int d = 0; d < D; d++) jac += Xs[r * 8 + d];
+            const double jac = sum_lj(Xs + r * 8);
             const double lnn = jac == -INFINITY ? -INFINITY : (double)sLq[w][r] + jac;
             double lq = mixed ? ln_mix_call(mix.eps, lnn, lqa) : lnn;
             if (SAMPLE) {
