@@ -368,8 +368,9 @@ __device__ __attribute__((noinline)) void hist_call(const double *P, const doubl
 // units of degree below d.  Pass d therefore evaluates the 21 or 22 units of
 // degree d - 1 of each layer and no other: their hidden values join those of
 // the earlier passes in LDS, and the products run over all 128 units as ever
-// (in the same order; the units not yet known have weights of zero, and hold
-// zeros or the wave's previous values, which are finite).  All seven passes
+// (in the same order; the units not yet known have weights of zero and hold
+// zeros, set for every tile: weights that BF16 rounds to infinities can make a
+// NaN, and 0 times the last tile's would reach this one).  All seven passes
 // together are one forward evaluation where they were six, which is what the
 // kernel's time was: its tanh and exponentials, a chain a lane waits for at
 // one wave per SIMD.  W2 comes from global memory, fetched ahead of the
@@ -417,15 +418,6 @@ __global__ __launch_bounds__(IT, 2) void k_mdn_infer(
     }
     if (tid == 0) sT = *trp;
     __bf16 *H1s = sH1[SAMPLE ? w : 0], *H2s = sH2[w];
-    if (SAMPLE) {
-        v8bf zero;
-#pragma unroll
-        for (int i = 0; i < 8; i++) zero[i] = (__bf16)0.f;
-        for (int c = lane; c < 16 * 16; c += 64) {
-            *(v8bf *)(H1s + 8 * c) = zero;
-            *(v8bf *)(H2s + 8 * c) = zero;
-        }
-    }
     __syncthreads();
     const float sfloor = (float)sT.sigma_floor, kappa = (float)sT.sigma_scale;
     float *Zs = sZ[w], *Rs = sR[w];
@@ -455,6 +447,15 @@ __global__ __launch_bounds__(IT, 2) void k_mdn_infer(
         const int64_t i = tile * 16 + r;   // sample of the lanes of column r
         const bool valid = i < n;
         if (SAMPLE) {
+            // no unit of this tile is known yet
+            v8bf none;
+#pragma unroll
+            for (int q = 0; q < 8; q++) none[q] = (__bf16)0.f;
+#pragma unroll
+            for (int c = lane; c < 16 * 16; c += 64) {
+                *(v8bf *)(H1s + 8 * c) = none;
+                *(v8bf *)(H2s + 8 * c) = none;
+            }
             // 16 uniforms per sample: group g computes Philox blocks 2g, 2g+1
 #pragma unroll
             for (int bb = 0; bb < 2; bb++) {
