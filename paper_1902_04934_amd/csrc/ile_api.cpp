@@ -1650,6 +1650,7 @@ ile_status ile_get_stream(const ile_ctx *c, void **stream_out)
 ile_status ile_sync(ile_ctx *c)
 {
     if (!c) return ILE_E_ARG;
+    HIP_TRY(c, hipSetDevice(c->cfg.device));   // finish_call launches a kernel
     ile_status s = finish_call(c);
     c->n_ev_used = 0;
     return s;
