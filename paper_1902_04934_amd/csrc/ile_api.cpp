@@ -453,11 +453,23 @@ ile_status finish_call(ile_ctx *c)
     if (n) c->last_ms = tot / n;
     if (c->errflag.p) {
         if (*hflag) {
-            HIP_TRY(c, hipMemset(c->errflag.p, 0, 2 * sizeof(int32_t)));
+            HIP_TRY(c, ile_launch_fill_u32((uint32_t *)c->errflag.p, 0u, 2, c->stream));
             return fail(c, ILE_E_RANGE,
                         "a device-side sample was out of range (its output is NaN)");
         }
     }
+    return ILE_OK;
+}
+
+// Ends an ile_integrate that returns no result: what it queued is waited for
+// (it may still read the caller's arrays) and its word of the flag cleared, in
+// the order of the context's stream.
+ile_status abandon_call(ile_ctx *c)
+{
+    c->n_ev_used = 0;
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    if (c->errflag.p)
+        HIP_TRY(c, ile_launch_fill_u32((uint32_t *)c->errflag.p + 1, 0u, 1, c->stream));
     return ILE_OK;
 }
 
@@ -1155,13 +1167,14 @@ ile_status ile_integrate(ile_ctx *c, const double *samples, const double *ln_p,
     s = integrate_queue(c, samples, ln_p, ln_q, N);
     c->flag_word = 0;
     const ile_status bad = check_draws(c, samples, ln_p, ln_q, N);
-    if (bad) {
-        (void)hipStreamSynchronize(c->stream);
-        if (c->errflag.p) (void)hipMemset((int32_t *)c->errflag.p + 1, 0, sizeof(int32_t));
-        c->n_ev_used = 0;
-        return bad;
+    if (bad || s) {
+        const std::string why = c->err;
+        const ile_status end = abandon_call(c);
+        if (end && !s) return end;   // the device failed in what an invalid array queued
+        c->err = why;
+        return bad ? bad : s;
     }
-    if (s || (s = finish_call(c))) return s;
+    if ((s = finish_call(c))) return s;
     double r[6];
     fetched_result(c, r);
     copy_result(r, out);
