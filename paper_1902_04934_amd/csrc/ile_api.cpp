@@ -255,6 +255,17 @@ ile_status check_samples(ile_ctx *c, const double *s, int64_t N)
     return ILE_OK;
 }
 
+// Waits for a stream when its scope ends early: copies queued there read arrays
+// of the caller, or that end with the scope.
+struct WaitUnlessDone {
+    hipStream_t st;
+    bool done = false;
+    ~WaitUnlessDone()
+    {
+        if (!done) (void)hipStreamSynchronize(st);
+    }
+};
+
 // A device flag that is zero between calls: cleared when made and after an
 // error.
 ile_status ensure_flag(ile_ctx *c)
@@ -644,12 +655,14 @@ ile_status ile_set_data(ile_ctx *c, const double *Q, int64_t n_q, double t0_s,
     } else if (whole) {
         if ((s = ensure(c, c->stage, 16 * nQ))) return s;
         if ((s = ensure_flag(c))) return s;
+        WaitUnlessDone wait{c->stream};
         HIP_TRY(c, hipMemcpyAsync(c->stage.p, Q, 16 * nQ, hipMemcpyHostToDevice, c->stream));
         HIP_TRY(c, ile_launch_finite((const double *)c->stage.p, (int64_t)nQ,
                                      (int32_t *)c->fd_flag.p, c->stream));
         HIP_TRY(c, ile_launch_fetch((const int32_t *)c->fd_flag.p, nullptr, (double *)c->hpin,
                                     c->stream));
         HIP_TRY(c, hipStreamSynchronize(c->stream));
+        wait.done = true;
         finite = !*(const int32_t *)c->hpin;
         if (!finite) HIP_TRY(c, hipMemsetAsync(c->fd_flag.p, 0, 16, c->stream));
     }
@@ -715,6 +728,8 @@ ile_status ile_set_data(ile_ctx *c, const double *Q, int64_t n_q, double t0_s,
     if ((s = ensure(c, c->V, nUV * 16))) return s;
     hipStream_t st = c->stream;
     std::vector<uint16_t> h;
+    std::vector<double> t(ile_pack_uv_doubles(nd, nl));
+    WaitUnlessDone wait{st};
     if (planar && !first) {
         // (each part's copy follows the kernel that read the last)
         const QParts P = q_parts(nd * nl, n_q, kStageBytes);
@@ -754,7 +769,6 @@ ile_status ile_set_data(ile_ctx *c, const double *Q, int64_t n_q, double t0_s,
     // the Hermitian part of U and the symmetric part of V: the only parts
     // the quadratic term of Eq. (7) sees (Re(Y^H U Y) = Y^H U_h Y,
     // Y^T V Y = Y^T V_s Y)
-    std::vector<double> t(ile_pack_uv_doubles(nd, nl));
     ile_pack_uv(nd, nl, U, V, t.data());
     if ((s = ensure(c, c->uvt, t.size() * sizeof(double)))) return s;
     HIP_TRY(c, hipMemcpyAsync(c->uvt.p, t.data(), t.size() * sizeof(double),
@@ -762,6 +776,7 @@ ile_status ile_set_data(ile_ctx *c, const double *Q, int64_t n_q, double t0_s,
     if ((s = ensure(c, c->errflag, 16))) return s;
     HIP_TRY(c, ile_launch_fill_u32((uint32_t *)c->errflag.p, 0u, 4, st));
     HIP_TRY(c, hipStreamSynchronize(st));   // every stream may read the data from here on
+    wait.done = true;
     c->have_data = true;
     return ILE_OK;
 }

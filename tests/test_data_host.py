@@ -33,3 +33,36 @@ def test_first_data_gives_nothing_back(tmp_path, n_q, precision):
         assert alloc("hipFree") == [] and alloc("hipMalloc") == []
         c.close()
     """)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "bf16"])
+@pytest.mark.parametrize("call", ["hipMemcpyAsync", "hipLaunchKernel", "hipMalloc"])
+def test_failed_data_is_waited_for(tmp_path, call, precision):
+    """Whichever call of ile_set_data fails, first data or further, a copy that
+    was queued before it (they read the caller's arrays and the call's own) has
+    been waited for when it returns."""
+    stand_in.run(tmp_path, f"""
+        inst = synth.make_instance(["D1", "D2"], 5, 4096, 4096.0, 65, 3)
+        def data(c):
+            ile.ile_set_data(c.h, inst.Q, inst.t0_s, inst.U, inst.V, inst.dets)
+        for further in (0, 1):
+            ended = 0
+            for nth in range(1, 20):
+                c = ile.Context(inst, precision={precision!r}) if further else None
+                clear()
+                if c is None:
+                    h = ile.ile_create(inst.dets, inst.modes, inst.srate_hz, inst.n_t, precision={precision!r})
+                    c = type("H", (), {{"h": h, "close": lambda self: ile.ile_destroy(self.h)}})()
+                    clear()
+                fail({call!r}, nth)
+                try:
+                    data(c)
+                    ended += 1
+                except ile.IleError as e:
+                    n = [x[0] for x in calls()]
+                    queued = [i for i, x in enumerate(n) if x == "hipMemcpyAsync"]
+                    assert not queued or "hipStreamSynchronize" in n[queued[-1]:], (further, nth, n)
+                clear()
+                c.close()
+            assert 0 < ended
+    """)
