@@ -687,7 +687,7 @@ ile_status ile_set_data(ile_ctx *c, const double *Q, int64_t n_q, double t0_s,
                     return fail(c, ILE_E_NUMERIC, "U[%d] not Hermitian at (%d,%d)", k, a, b);
             }
     }
-    ile_geom &g = c->g;
+    ile_geom g = c->g;   // the context's own changes with its data, below
     for (int k = 0; k < nd; k++) {
         const ile_detector &d = dets[k];
         if (!std::isfinite(d.lat_deg) || !std::isfinite(d.lon_deg) ||
@@ -721,8 +721,12 @@ ile_status ile_set_data(ile_ctx *c, const double *Q, int64_t n_q, double t0_s,
     g.key_shift = shift;
     g.key_bits = bits;
     for (int d = 0; d < 3; d++) g.key_lo[d] = (int)slo;
-    c->n_buckets = (1u << (bits * g.key_dims)) + 1u;
 
+    // nothing is refused any more: from here the old data goes, and a failure
+    // leaves the context without any
+    c->have_data = false;
+    c->g = g;
+    c->n_buckets = (1u << (bits * g.key_dims)) + 1u;
     if ((s = ensure(c, c->Q, q_bytes))) return s;
     if ((s = ensure(c, c->U, nUV * 16))) return s;
     if ((s = ensure(c, c->V, nUV * 16))) return s;

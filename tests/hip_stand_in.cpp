@@ -97,6 +97,9 @@ hipError_t hipLaunchKernel(const void *f, dim3 g, dim3, void **args, size_t, hip
         more += *(void **)args[7] ? " result" : " none";
     else if (n.find("k_red_final") != std::string::npos)
         more += *(void **)args[5] ? " result" : " none";
+    // the window starts' first argument: the geometry, n_q and s_max its words 4, 5
+    else if (n.find("k_prep") != std::string::npos)
+        more += " " + num(((const int *)args[0])[4]) + " " + num(((const int *)args[0])[5]);
     g_last = call("hipLaunchKernel", dev_of(st), more);
     if (g_last == hipSuccess && dev_of(st) != g_dev) g_last = hipErrorInvalidHandle;
     return g_last;

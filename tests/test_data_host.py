@@ -66,3 +66,51 @@ def test_failed_data_is_waited_for(tmp_path, call, precision):
                 c.close()
             assert 0 < ended
     """)
+
+
+def test_refused_data_leaves_the_geometry(tmp_path):
+    """Data refused for its length or a detector leaves the evaluations with the
+    series that the context holds; data that fails part way leaves none."""
+    stand_in.run(tmp_path, """
+        inst = synth.make_instance(["D1", "D2"], 5, 4096, 4096.0, 65, 3)
+        s, _ = synth.prior_samples(100, 4)
+        c = ile.Context(inst)
+        def prep():
+            clear()
+            c.eval(s)
+            return [x[3][2:] for x in calls() if x[0] == "hipLaunchKernel" and "k_prep" in x[3][0]]
+        def refused(Q, t0, dets):
+            try:
+                ile.ile_set_data(c.h, Q, t0, inst.U, inst.V, dets)
+            except ile.IleError as e:
+                return str(e)
+        want = prep()
+        assert want == [["4096", str(4096 - 65)]], want
+        long = np.concatenate([inst.Q] * 2, axis=2)
+        assert "too short" in refused(long, 0.0, inst.dets)
+        assert prep() == want
+        bad = [inst.dets[0], (95.0, 0.0, 0.0)]
+        assert "detector 1" in refused(long, inst.t0_s, bad)
+        assert prep() == want
+        for nth in range(1, 6):
+            c2 = ile.Context(inst)
+            clear()
+            fail("hipMalloc", nth)
+            try:
+                ile.ile_set_data(c2.h, long, inst.t0_s, inst.U, inst.V, inst.dets)
+                break
+            except ile.IleError:
+                pass
+            # the old data, as only the staging was missing, or none
+            c, held = c2, True
+            try:
+                assert prep() == want
+            except ile.IleError as e:
+                assert "set_data" in str(e), e
+                held = False
+            assert held == (nth == 1)
+            clear()
+            ile.ile_set_data(c2.h, long, inst.t0_s, inst.U, inst.V, inst.dets)
+            c2.eval(s)
+        assert nth == 3
+    """)

@@ -28,3 +28,29 @@ def test_first_and_further_data_agree(n_det, n_lm, n_q, precision):
         ile.ile_set_data(ctx.h, inst.Q[:, ::-1] * 1.5, inst.t0_s, inst.U, inst.V, inst.dets)
         assert np.array_equal(ctx.eval(s), other)
     assert np.all(np.isfinite(first)) and not np.array_equal(first, other)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_refused_data_keeps_the_old(precision):
+    """Series too short, an invalid detector behind a valid one, a value that is
+    not finite in a context's first series."""
+    inst = synth.make_instance(["D1", "D2"], 3, 4096, 4096.0, 65, 8)
+    other = synth.make_instance(["D3", "D1"], 3, 4096, 4096.0, 65, 9)
+    s, _ = synth.prior_samples(300, 9)
+    h = ile.ile_create(inst.dets, inst.modes, inst.srate_hz, inst.n_t, d_ref_mpc=inst.d_ref_mpc,
+                       gmst_rad=inst.gmst_rad, precision=precision)
+    Q = inst.Q.copy()
+    Q[1, 2, 77] = np.nan
+    with pytest.raises(ile.IleError, match=r"Q\[%d\] not finite" % (5 * 4096 + 77)):
+        ile.ile_set_data(h, Q, inst.t0_s, inst.U, inst.V, inst.dets)
+    with pytest.raises(ile.IleError, match="set_data has not"):
+        ile.ile_eval(h, s)
+    ile.ile_set_data(h, inst.Q, inst.t0_s, inst.U, inst.V, inst.dets)
+    want = ile.ile_eval(h, s)
+    with pytest.raises(ile.IleError, match="too short"):
+        ile.ile_set_data(h, other.Q, 0.0, other.U, other.V, other.dets)
+    assert np.array_equal(ile.ile_eval(h, s), want)
+    with pytest.raises(ile.IleError, match="detector 1"):
+        ile.ile_set_data(h, other.Q, other.t0_s, other.U, other.V, [other.dets[0], (95.0, 0.0, 0.0)])
+    assert np.array_equal(ile.ile_eval(h, s), want)
+    ile.ile_destroy(h)
