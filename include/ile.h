@@ -620,6 +620,11 @@ ile_status ile_batch_lnL(ile_batch *b, double *out, int64_t n_total);
 int32_t ile_batch_n_points(const ile_batch *b);
 ile_status ile_batch_set_tuning(ile_batch *b, const ile_batch_tuning *t);
 ile_status ile_batch_get_tuning(const ile_batch *b, ile_batch_tuning *t);
+/* Largest device buffer, in bytes, that a run keeps for the per-sample terms
+ * of Eq. (7) (phased engine; 8 (2 + 3 n_det + 2 n_lm) bytes a draw).  A run
+ * that needs more forms them in its tiles, the same to rounding but more
+ * slowly.  Default 32 GiB; 0: never such a buffer. */
+ile_status ile_batch_set_terms_limit(ile_batch *b, int64_t bytes);
 /* Time every candidate tuning on a run of n_per_point samples per point and
  * keep the fastest; cache_path (may be NULL) is read first and updated. */
 ile_status ile_batch_autotune(ile_batch *b, int64_t n_per_point, const char *cache_path);

@@ -33,8 +33,8 @@ struct Buf {
 };
 
 constexpr int kKeyBits = 15;   // ordering key bits per point (buckets 2^15 + 1)
-// Largest per-sample terms buffer of one batched run (the phased engine);
-// a run that needs more forms the terms in its tiles.
+// Largest per-sample terms buffer of one batched run (the phased engine) unless
+// the caller sets another; a run that needs more forms the terms in its tiles.
 constexpr size_t kMaxTermsBytes = (size_t)32 << 30;
 
 }  // namespace
@@ -46,6 +46,7 @@ struct ile_batch {
     std::string err;
     std::vector<ile_ctx *> pts;
     ile_batch_tuning tune{256, 2, 0, 1};
+    size_t terms_limit = kMaxTermsBytes;
     int cu_count = 0, lds_max = 0;
     std::string dev_name;
     Buf geoms, pdev, items, offs, seed, counter, smp, out, shifts, keys, slot, rec, perm, hist,
@@ -195,12 +196,12 @@ ile_status build(ile_batch *b, int64_t n, double dmin, double dmax, bool ext)
     }
     if (ext && (s = bensure(b, b->lw, (size_t)NT * sizeof(double)))) return s;
     // the phased engine's per-sample terms, per point, when they fit in
-    // kMaxTermsBytes (else the tiles form them)
+    // terms_limit (else the tiles form them)
     std::vector<size_t> toff(P + 1, 0);
     const bool ph = ile_contract_uses_terms(b->cfg.precision, tu);
     for (int p = 0; p < P; p++)
         toff[p + 1] = toff[p] + (size_t)ile_terms_fields(gs[p]) * (size_t)((n + 15) & ~15);
-    const bool use_terms = ph && toff[P] * sizeof(double) <= kMaxTermsBytes;
+    const bool use_terms = ph && toff[P] * sizeof(double) <= b->terms_limit;
     if (use_terms) {
         if ((s = bensure(b, b->terms, toff[P] * sizeof(double)))) return s;
         if ((s = bensure(b, b->rec, (size_t)NT * sizeof(ile_sample_rec)))) return s;
@@ -526,6 +527,23 @@ ile_status ile_batch_get_tuning(const ile_batch *b, ile_batch_tuning *t)
 {
     if (!b || !t) return ILE_E_ARG;
     *t = b->tune;
+    return ILE_OK;
+}
+
+ile_status ile_batch_set_terms_limit(ile_batch *b, int64_t bytes)
+{
+    if (!b) return ILE_E_ARG;
+    b->err.clear();
+    if (bytes < 0) return bfail(b, ILE_E_ARG, "bad limit");
+    if (b->terms_limit == (size_t)bytes) return ILE_OK;
+    BHIP(b, hipSetDevice(b->cfg.device));
+    BHIP(b, hipStreamSynchronize(b->stream));
+    drop_graph(b);
+    b->terms_limit = (size_t)bytes;
+    if (b->terms.bytes > b->terms_limit) {
+        (void)hipFree(b->terms.p);
+        b->terms = Buf{};
+    }
     return ILE_OK;
 }
 

@@ -176,6 +176,7 @@ def lib():
         L.ile_batch_n_points.argtypes = [_vp]
         L.ile_batch_set_tuning.argtypes = [_vp, C.POINTER(BatchTuning)]
         L.ile_batch_get_tuning.argtypes = [_vp, C.POINTER(BatchTuning)]
+        L.ile_batch_set_terms_limit.argtypes = [_vp, C.c_int64]
         L.ile_batch_autotune.argtypes = [_vp, C.c_int64, C.c_char_p]
         L.ile_batch_last_ms.argtypes = [_vp]
         L.ile_batch_last_ms.restype = C.c_double
@@ -634,6 +635,9 @@ class Batch:
         t = BatchTuning()
         _bcheck(lib().ile_batch_get_tuning(self.h, C.byref(t)), self.h)
         return dict(threads=t.threads, wgs_per_cu=t.wgs_per_cu, order=t.order, engine=t.engine)
+
+    def set_terms_limit(self, n_bytes):
+        _bcheck(lib().ile_batch_set_terms_limit(self.h, int(n_bytes)), self.h)
 
     def autotune(self, n_per_point, cache_path=None):
         _bcheck(lib().ile_batch_autotune(self.h, int(n_per_point),
