@@ -2319,18 +2319,19 @@ hipError_t launch_contract_t(const ile_geom &g, const double *smp, int64_t N,
     return hipGetLastError();
 }
 
-// Bins per chunk of the phased engine (also the LDS row stride of its bin
-// rows): the largest that keeps the workgroup's dynamic LDS within `budget`
-// bytes, an odd multiple of 128 bytes so that rows of neighbouring samples
-// start in alternate halves of the 256-byte bank period.  0 if none fits.
+// LDS row stride of the phased engine's bin rows, one more than the bins of a
+// chunk: the largest that keeps the coefficients and the rows within `budget`
+// bytes, an odd multiple of 128 bytes (the unit) so that rows of neighbouring
+// samples start in alternate halves of the 256-byte bank period.  One unit
+// where the budget leaves less than that (the device's limit then decides),
+// 0 where the coefficients leave nothing.
 int ph_wrow(int nd, int nl, size_t e, size_t budget)
 {
     const size_t fixed = coef_bytes<ENG_MFMA>(16, nd, nl, e) + 16;   // + the slot past X
     if (budget <= fixed) return 0;
     const int unit = (int)(128 / e);
     const int w = (int)((budget - fixed) / ((size_t)16 * e));
-    const int q = (w / unit - 1) / 2;
-    return q < 0 ? 0 : unit * (2 * q + 1);
+    return unit * (std::max(w / unit - 1, 0) / 2 * 2 + 1);
 }
 
 // Default LDS budgets of a phased workgroup: FP64 tiles hold four waves per
@@ -2546,7 +2547,7 @@ size_t ile_contract_lds_bytes(const ile_geom &g, ile_precision prec,
     const size_t e = prec == ILE_FP64 ? 8 : 4;
     if (tu.engine == ENG_PH && prec != ILE_BF16) {
         const int w = ph_wrow(g.n_det, g.n_lm, e, ph_budget(tu, e));
-        // a chunk has at least 16 bins
+        // a row is at least a unit, 16 values or more, a chunk one bin less
         if (w < 16) return (size_t)1 << 30;
         return ph_dyn_bytes(16, g.n_det, g.n_lm, w, e) + 2048;
     }
