@@ -1782,8 +1782,8 @@ __device__ __forceinline__ void ph_lphase(const TQ *X, int Jc, int o, double &m,
 }
 
 // PRE: the per-sample terms come from k_terms (the tile's block of the
-// terms, tile-major from position t0), else the tile forms them
-// (tile_prologue).
+// terms, tile-major from position t0; smp, shifts, U and V are null), else the
+// tile forms them (tile_prologue).
 // What bounds it: the FP64 matrix steps themselves (a variant without stores
 // and log-sum-exp runs its chunks at the matrix rate, 0.82 ms per chunk of 463
 // bins for 5e5 samples at 3 detectors and 21 modes), then, since they do not
@@ -1947,48 +1947,33 @@ __device__ __forceinline__ void contract_tile_ph(
         out[s_idx[al]] = s_ok[al] ? (M - s_q[al]) + log(S) - log((double)n_t) : NAN;
 }
 
-template <typename TQ, int TS, int NT, int ENG, bool DUMP>
-__device__ __forceinline__ void run_tile(
-    const ile_geom &g, int64_t base, const double *__restrict__ smp, int64_t N,
-    const int32_t *__restrict__ perm, const int32_t *__restrict__ shifts,
-    const TQ *__restrict__ Q, const double2 *__restrict__ U,
-    const double2 *__restrict__ V, double *__restrict__ out,
-    double *__restrict__ series)
-{
-    if constexpr (ENG == ENG_PH)
-        contract_tile_ph<TQ, TS, NT, DUMP, false>(g, base, smp, N, perm, shifts, Q, U, V,
-                                                  nullptr, 0, out, series);
-    else
-        contract_tile<TQ, TS, NT, ENG, DUMP>(g, base, smp, N, perm, shifts, Q, U, V, out, series);
-}
-
 // Waves per SIMD the register allocation must allow (the second bound of
 // __launch_bounds__): the eight-wave phased workgroups per CU that their LDS
 // admits, two for FP64 and three for FP32, are four and six waves per SIMD
 // (tiles that form the per-sample terms themselves need more registers than
 // six waves leave).
-template <typename TQ, int NT, int ENG, bool PRE = false> constexpr int contract_min_waves()
+template <typename TQ, int NT, bool PRE> constexpr int ph_min_waves()
 {
-    return ENG == ENG_PH && NT == 512 ? (sizeof(TQ) == 4 && PRE ? 6 : 4) : 1;
+    return NT == 512 ? (sizeof(TQ) == 4 && PRE ? 6 : 4) : 1;
 }
 
 template <typename TQ, int TS, int NT, int ENG, bool DUMP>
-__global__ __launch_bounds__(NT, (contract_min_waves<TQ, NT, ENG>())) void k_contract(
+__global__ __launch_bounds__(NT, 1) void k_contract(
     ile_geom g, const double *__restrict__ smp, int64_t N,
     const int32_t *__restrict__ perm, const int32_t *__restrict__ shifts,
     const TQ *__restrict__ Q, const double2 *__restrict__ U,
     const double2 *__restrict__ V, double *__restrict__ out,
     double *__restrict__ series)
 {
-    run_tile<TQ, TS, NT, ENG, DUMP>(g, (int64_t)blockIdx.x * TS, smp, N, perm, shifts,
-                                    Q, U, V, out, series);
+    contract_tile<TQ, TS, NT, ENG, DUMP>(g, (int64_t)blockIdx.x * TS, smp, N, perm, shifts, Q, U,
+                                         V, out, series);
 }
 
 // Persistent form over many intrinsic points: every workgroup takes
 // (point, tile) items from a queue in list order (the host sorts the list by
 // decreasing cost) until it is empty; every wave reaches the exit.
 template <typename TQ, int TS, int NT, int ENG>
-__global__ __launch_bounds__(NT, (contract_min_waves<TQ, NT, ENG>())) void k_contract_batched(
+__global__ __launch_bounds__(NT, 1) void k_contract_batched(
     const ile_geom *__restrict__ geoms, const ile_point_dev *__restrict__ pts,
     const int2 *__restrict__ items, int n_items, unsigned *counter)
 {
@@ -2002,9 +1987,8 @@ __global__ __launch_bounds__(NT, (contract_min_waves<TQ, NT, ENG>())) void k_con
         if (it >= n_items) break;
         const int2 w = items[it];
         const ile_point_dev &P = pts[w.x];
-        run_tile<TQ, TS, NT, ENG, false>(geoms[w.x], (int64_t)w.y * TS, P.smp, P.N,
-                                         P.perm, P.shifts, (const TQ *)P.Q, P.U, P.V,
-                                         P.out, nullptr);
+        contract_tile<TQ, TS, NT, ENG, false>(geoms[w.x], (int64_t)w.y * TS, P.smp, P.N, P.perm,
+                                              P.shifts, (const TQ *)P.Q, P.U, P.V, P.out, nullptr);
     }
 }
 
@@ -2016,16 +2000,16 @@ __global__ __launch_bounds__(NT, (contract_min_waves<TQ, NT, ENG>())) void k_con
 // are read through the scalar unit instead of being held in registers
 // across a queue loop.
 template <typename TQ, int TS, int NT, bool PRE>
-__global__ __launch_bounds__(NT, (contract_min_waves<TQ, NT, ENG_PH, PRE>())) void k_contract_items(
+__global__ __launch_bounds__(NT, (ph_min_waves<TQ, NT, PRE>())) void k_contract_items(
     const ile_geom *__restrict__ geoms, const ile_point_dev *__restrict__ pts,
     const int2 *__restrict__ items)
 {
     const int2 w = items[blockIdx.x];
     const ile_point_dev &P = pts[w.x];
     if (PRE)
-        contract_tile_ph<TQ, TS, NT, false, true>(geoms[w.x], (int64_t)w.y * TS, P.smp, P.N,
-                                                  P.perm, P.shifts, (const TQ *)P.Q, P.U, P.V,
-                                                  P.terms, 0, P.out, nullptr);
+        contract_tile_ph<TQ, TS, NT, false, true>(geoms[w.x], (int64_t)w.y * TS, nullptr, P.N,
+                                                  P.perm, nullptr, (const TQ *)P.Q, nullptr,
+                                                  nullptr, P.terms, 0, P.out, nullptr);
     else
         contract_tile_ph<TQ, TS, NT, false, false>(geoms[w.x], (int64_t)w.y * TS, P.smp, P.N,
                                                    P.perm, P.shifts, (const TQ *)P.Q, P.U, P.V,
@@ -2036,14 +2020,13 @@ __global__ __launch_bounds__(NT, (contract_min_waves<TQ, NT, ENG_PH, PRE>())) vo
 // tiles of tile positions t0 + 16 blockIdx.x .. (below N), their terms
 // tile-major from position t0.
 template <typename TQ, int NT, bool DUMP>
-__global__ __launch_bounds__(NT, (contract_min_waves<TQ, NT, ENG_PH, true>())) void k_contract_ph(
-    ile_geom g, const double *__restrict__ smp, int64_t N, const int32_t *__restrict__ perm,
-    const int32_t *__restrict__ shifts, const TQ *__restrict__ Q,
+__global__ __launch_bounds__(NT, (ph_min_waves<TQ, NT, true>())) void k_contract_ph(
+    ile_geom g, int64_t N, const int32_t *__restrict__ perm, const TQ *__restrict__ Q,
     const double *__restrict__ terms, int64_t t0, double *__restrict__ out,
     double *__restrict__ series)
 {
-    contract_tile_ph<TQ, 16, NT, DUMP, true>(g, t0 + (int64_t)blockIdx.x * 16, smp, N, perm,
-                                             shifts, Q, nullptr, nullptr, terms, t0, out,
+    contract_tile_ph<TQ, 16, NT, DUMP, true>(g, t0 + (int64_t)blockIdx.x * 16, nullptr, N, perm,
+                                             nullptr, Q, nullptr, nullptr, terms, t0, out,
                                              series);
 }
 
@@ -2367,8 +2350,7 @@ static hipError_t allow_dyn_lds(const void *fn, size_t dyn, size_t (&allowed)[64
 }
 
 template <typename TQ, int NT, bool DUMP>
-hipError_t launch_contract_ph(const ile_geom &g, const double *smp, int64_t N,
-                              const int32_t *perm, const int32_t *shifts,
+hipError_t launch_contract_ph(const ile_geom &g, int64_t N, const int32_t *perm,
                               const ile_sample_rec *rec, const void *Q, const double *uvt,
                               double *terms, int64_t cap, double *out, double *series, size_t dyn,
                               hipStream_t st)
@@ -2383,8 +2365,7 @@ hipError_t launch_contract_ph(const ile_geom &g, const double *smp, int64_t N,
         hipError_t e = launch_terms(g, rec, perm, uvt, t0, n, terms, st);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL((k_contract_ph<TQ, NT, DUMP>), dim3(nblk(n, 16)), dim3(NT), dyn, st, g,
-                           smp, N, perm, shifts, (const TQ *)Q, (const double *)terms, t0, out,
-                           series);
+                           N, perm, (const TQ *)Q, (const double *)terms, t0, out, series);
     }
     return hipGetLastError();
 }
@@ -2611,10 +2592,10 @@ hipError_t ile_launch_contract(const ile_geom &g, ile_precision prec,
             return hipErrorInvalidValue;
         const size_t dyn = ph_dyn_bytes(16, g.n_det, g.n_lm, gp.wrow, e);
 #define ILE_PH(TQ, NT)                                                                       \
-    return series ? launch_contract_ph<TQ, NT, true>(gp, smp, N, perm, shifts, rec, Q, uvt,    \
-                                                     terms, cap, out, series, dyn, st)         \
-                  : launch_contract_ph<TQ, NT, false>(gp, smp, N, perm, shifts, rec, Q, uvt,   \
-                                                      terms, cap, out, series, dyn, st)
+    return series ? launch_contract_ph<TQ, NT, true>(gp, N, perm, rec, Q, uvt, terms, cap,     \
+                                                     out, series, dyn, st)                     \
+                  : launch_contract_ph<TQ, NT, false>(gp, N, perm, rec, Q, uvt, terms, cap,    \
+                                                      out, series, dyn, st)
         if (prec == ILE_FP64) {
             if (tu.threads == 256) ILE_PH(double, 256);
             ILE_PH(double, 512);
