@@ -69,7 +69,7 @@ struct ile_ctx {
     DevBuf Q, U, V;
     DevBuf uvt;                     // upper triangles of U_h and V_s (see ile_launch_contract)
     DevBuf smp, out, lnp, lnq, shifts, keys, perm, hist, scan_tmp, errflag,
-        red_tmp, parts, res, series, terms, slot, rec, stage;
+        red_tmp, parts, res, series, terms, slot, rec, stage, stage1;
     DevBuf hP, hC, bins, hist_tmp;  // adaptive proposal state and scratch
     int hist_nb = 0;
     DevBuf trx, trw;                // training set of the learned sampler
@@ -297,10 +297,10 @@ ile_status first_series(ile_ctx *c, const double *Q, int rows, int n_lm, int64_t
 {
     const QParts P = q_parts(rows, n_q, kFirstStageBytes);
     ile_status s;
-    if ((s = ensure(c, c->stage, (size_t)16 * P.nr * P.ni))) return s;
+    if ((s = ensure(c, c->stage1, (size_t)16 * P.nr * P.ni))) return s;
     if ((s = ensure_flag(c))) return s;
     int32_t *flag = (int32_t *)c->fd_flag.p;
-    double *raw = (double *)c->stage.p;
+    double *raw = (double *)c->stage1.p;
     for (int r = 0; r < rows; r += P.nr)
         for (int64_t i = 0; i < n_q; i += P.ni) {
             const int m = std::min(P.nr, rows - r);
@@ -641,10 +641,12 @@ ile_status ile_set_data(ile_ctx *c, const double *Q, int64_t n_q, double t0_s,
     // series have no data to leave intact: part by part through a buffer
     // small enough to stay (to hold 16 MB for data that is set once would be
     // a waste, and to free them cost the next call 0.34 ms).  Further ones are
-    // checked where the staging buffer holds them whole, before the planar
-    // copy takes over from the data there, else on the host.
+    // checked where a staging buffer (that one, or a larger one that stays as
+    // well) holds them whole, before the planar copy takes over from the data
+    // there, else on the host.
     const bool planar = c->cfg.precision != ILE_BF16, first = planar && !c->have_data;
     const bool whole = planar && !first && 16 * nQ <= kStageBytes;
+    DevBuf &stage = whole && 16 * nQ <= c->stage1.bytes ? c->stage1 : c->stage;
     bool finite = false;
     HIP_TRY(c, hipSetDevice(c->cfg.device));
     if (first) {
@@ -653,11 +655,11 @@ ile_status ile_set_data(ile_ctx *c, const double *Q, int64_t n_q, double t0_s,
         if ((s = first_series(c, Q, nd * nl, nl, n_q, &bad))) return s;
         finite = !bad;
     } else if (whole) {
-        if ((s = ensure(c, c->stage, 16 * nQ))) return s;
+        if ((s = ensure(c, stage, 16 * nQ))) return s;
         if ((s = ensure_flag(c))) return s;
         WaitUnlessDone wait{c->stream};
-        HIP_TRY(c, hipMemcpyAsync(c->stage.p, Q, 16 * nQ, hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(c, ile_launch_finite((const double *)c->stage.p, (int64_t)nQ,
+        HIP_TRY(c, hipMemcpyAsync(stage.p, Q, 16 * nQ, hipMemcpyHostToDevice, c->stream));
+        HIP_TRY(c, ile_launch_finite((const double *)stage.p, (int64_t)nQ,
                                      (int32_t *)c->fd_flag.p, c->stream));
         HIP_TRY(c, ile_launch_fetch((const int32_t *)c->fd_flag.p, nullptr, (double *)c->hpin,
                                     c->stream));
@@ -737,15 +739,15 @@ ile_status ile_set_data(ile_ctx *c, const double *Q, int64_t n_q, double t0_s,
     if (planar && !first) {
         // (each part's copy follows the kernel that read the last)
         const QParts P = q_parts(nd * nl, n_q, kStageBytes);
-        if ((s = ensure(c, c->stage, (size_t)16 * P.nr * P.ni))) return s;
+        if ((s = ensure(c, stage, (size_t)16 * P.nr * P.ni))) return s;
         for (int r = 0; r < nd * nl; r += P.nr)
             for (int64_t i = 0; i < n_q; i += P.ni) {
                 const int m = std::min(P.nr, nd * nl - r);
                 const int64_t w = std::min<int64_t>(P.ni, n_q - i);
                 if (!whole)
-                    HIP_TRY(c, hipMemcpyAsync(c->stage.p, Q + 2 * ((size_t)r * n_q + i),
+                    HIP_TRY(c, hipMemcpyAsync(stage.p, Q + 2 * ((size_t)r * n_q + i),
                                               (size_t)16 * m * w, hipMemcpyHostToDevice, st));
-                HIP_TRY(c, ile_launch_planar((const double *)c->stage.p, r, m, i, w, nl, n_q,
+                HIP_TRY(c, ile_launch_planar((const double *)stage.p, r, m, i, w, nl, n_q,
                                              c->cfg.precision == ILE_FP64, c->Q.p, st));
             }
     } else if (!planar) {
@@ -1747,7 +1749,7 @@ void ile_destroy(ile_ctx *c)
                       &c->hP, &c->hC, &c->bins, &c->hist_tmp, &c->trx, &c->trw,
                       &c->hv_w, &c->hv_cdf, &c->hv_ws, &c->hv_part, &c->hv_flag, &c->hv_sel,
                       &c->fd_tmp, &c->fd_flag, &c->fd_in, &c->fd_out, &c->rom_A, &c->rom_Z,
-                      &c->uvt, &c->terms, &c->slot, &c->rec, &c->stage})
+                      &c->uvt, &c->terms, &c->slot, &c->rec, &c->stage, &c->stage1})
         release(*b);
     for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
     if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);

@@ -29,6 +29,7 @@ def test_first_data_gives_nothing_back(tmp_path, n_q, precision):
         data(c)
         again = [n for n in alloc("hipMalloc") if n > 1 << 10]
         assert again == ([raw] if not bf16 and raw > 4 << 20 else []), again
+        assert alloc("hipFree") == []
         data(c)
         assert alloc("hipFree") == [] and alloc("hipMalloc") == []
         c.close()
