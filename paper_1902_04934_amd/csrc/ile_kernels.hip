@@ -1068,10 +1068,10 @@ __device__ __forceinline__ void tri_mac(double e, double2 y, tri_acc (&A)[4])
         TRI_E("4", "5", "6", "7", "4", "6", "17", "18", "")
         TRI_E("8", "9", "10", "11", "8", "10", "17", "18", "")
         TRI_E("12", "13", "14", "15", "12", "14", "17", "18", "")
-        : "+v"(A[0].ur), "+v"(A[0].ui), "+v"(A[0].vr), "+v"(A[0].vi), "+v"(A[1].ur),
-          "+v"(A[1].ui), "+v"(A[1].vr), "+v"(A[1].vi), "+v"(A[2].ur), "+v"(A[2].ui),
-          "+v"(A[2].vr), "+v"(A[2].vi), "+v"(A[3].ur), "+v"(A[3].ui), "+v"(A[3].vr),
-          "+v"(A[3].vi)
+        : "+&v"(A[0].ur), "+&v"(A[0].ui), "+&v"(A[0].vr), "+&v"(A[0].vi), "+&v"(A[1].ur),
+          "+&v"(A[1].ui), "+&v"(A[1].vr), "+&v"(A[1].vi), "+&v"(A[2].ur), "+&v"(A[2].ui),
+          "+&v"(A[2].vr), "+&v"(A[2].vi), "+&v"(A[3].ur), "+&v"(A[3].ui), "+&v"(A[3].vr),
+          "+&v"(A[3].vi)
         : "v"(e), "v"(y.x), "v"(y.y));
 #endif
 }

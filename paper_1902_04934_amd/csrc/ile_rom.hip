@@ -32,9 +32,9 @@ __device__ __forceinline__ void rom_mac(double e, double2 u, double2 (&z)[8])
         ROM_R("4", "5", "5", "18", "17", "-") ROM_R("6", "7", "7", "18", "17", "-")
         ROM_R("8", "9", "9", "18", "17", "-") ROM_R("10", "11", "11", "18", "17", "-")
         ROM_R("12", "13", "13", "18", "17", "-") ROM_R("14", "15", "15", "18", "17", "-")
-        : "+v"(z[0].x), "+v"(z[0].y), "+v"(z[1].x), "+v"(z[1].y), "+v"(z[2].x), "+v"(z[2].y),
-          "+v"(z[3].x), "+v"(z[3].y), "+v"(z[4].x), "+v"(z[4].y), "+v"(z[5].x), "+v"(z[5].y),
-          "+v"(z[6].x), "+v"(z[6].y), "+v"(z[7].x), "+v"(z[7].y)
+        : "+&v"(z[0].x), "+&v"(z[0].y), "+&v"(z[1].x), "+&v"(z[1].y), "+&v"(z[2].x), "+&v"(z[2].y),
+          "+&v"(z[3].x), "+&v"(z[3].y), "+&v"(z[4].x), "+&v"(z[4].y), "+&v"(z[5].x), "+&v"(z[5].y),
+          "+&v"(z[6].x), "+&v"(z[6].y), "+&v"(z[7].x), "+&v"(z[7].y)
         : "v"(e), "v"(u.x), "v"(u.y));
 #endif
 }
