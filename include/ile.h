@@ -131,7 +131,9 @@ ile_status ile_create(const ile_config *cfg, ile_ctx **out);
  * the geocentre event time.  Copies the data to the device (converting Q to
  * the context precision).  ILE_E_NUMERIC if anything is non-finite or U_k
  * is not Hermitian to 1e-12 relative; ILE_E_RANGE if a sample with
- * |t_ref| <= t_ref_max could read outside [0, n_q). */
+ * |t_ref| <= t_ref_max could read outside [0, n_q).  Data refused so leaves
+ * the context with what it had; data that fails for the device or its memory
+ * may leave it without any. */
 ile_status ile_set_data(ile_ctx *ctx, const double *Q, int64_t n_q,
                         double t0_s, const double *U, const double *V,
                         const ile_detector *dets);

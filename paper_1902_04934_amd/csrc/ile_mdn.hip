@@ -375,7 +375,7 @@ __device__ __attribute__((noinline)) void hist_call(const double *P, const doubl
 // kernel's time was: its tanh and exponentials, a chain a lane waits for at
 // one wave per SIMD.  W2 comes from global memory, fetched ahead of the
 // layer that uses it, so that LDS holds two waves per SIMD.
-// 1e5 draws of the mixture take 241 us (596 with a full evaluation per pass and
+// 1e5 draws of the mixture take 242 us (596 with a full evaluation per pass and
 // one wave per SIMD; the draws are the same bit for bit).
 template <bool SAMPLE>
 __global__ __launch_bounds__(IT, 2) void k_mdn_infer(

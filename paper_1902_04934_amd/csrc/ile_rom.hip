@@ -2,9 +2,8 @@
 // c_lm,b(lambda) e_b(t) with c_lm,b(lambda) = sum_p A[lm][b][p] lambda^p.
 // Eq. (7) over the basis needs, per joint sample, the vector
 //   z_b = sum_lm c_lm,b(lambda) -2Y_lm(iota, phi)
-// in place of the harmonics; k_rom_z forms it (one thread per sample, the
-// harmonics in registers) and the contraction reads it through
-// ile_geom::ext_y.
+// in place of the harmonics; k_rom_z forms it (one lane per sample, the
+// harmonics in LDS) and the contraction reads it through ile_geom::ext_y.
 #include "ile_internal.h"
 
 #include <math.h>
