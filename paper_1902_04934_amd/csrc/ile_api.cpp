@@ -301,19 +301,25 @@ ile_status first_series(ile_ctx *c, const double *Q, int rows, int n_lm, int64_t
     if ((s = ensure_flag(c))) return s;
     int32_t *flag = (int32_t *)c->fd_flag.p;
     double *raw = (double *)c->stage1.p;
+    WaitUnlessDone wait{nullptr};
     for (int r = 0; r < rows; r += P.nr)
         for (int64_t i = 0; i < n_q; i += P.ni) {
             const int m = std::min(P.nr, rows - r);
             const int64_t w = std::min<int64_t>(P.ni, n_q - i);
-            if (r || i) HIP_TRY(c, hipStreamSynchronize(c->stream));   // the last part has been read
-            HIP_TRY(c, hipMemcpy(raw, Q + 2 * ((size_t)r * n_q + i), (size_t)16 * m * w,
-                                 hipMemcpyHostToDevice));
+            if (r || i)   // until the last part has been read
+                HIP_TRY(c, hipStreamSynchronize(c->stream));
+            // waited for: the kernels run on another stream, which may not follow
+            // the null stream
+            HIP_TRY(c, hipMemcpyAsync(raw, Q + 2 * ((size_t)r * n_q + i), (size_t)16 * m * w,
+                                      hipMemcpyHostToDevice, nullptr));
+            HIP_TRY(c, hipStreamSynchronize(nullptr));
             HIP_TRY(c, ile_launch_finite(raw, m * w, flag, c->stream));
             HIP_TRY(c, ile_launch_planar(raw, r, m, i, w, n_lm, n_q, c->cfg.precision == ILE_FP64,
                                          c->Q.p, c->stream));
         }
     HIP_TRY(c, ile_launch_fetch(flag, nullptr, (double *)c->hpin, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    wait.done = true;
     *bad = *(const int32_t *)c->hpin;
     if (*bad) HIP_TRY(c, hipMemsetAsync(flag, 0, 16, c->stream));
     return ILE_OK;
